@@ -1,43 +1,93 @@
 // Beam score update and per-request top-k (GRACE, Sec. 3.1, Sec. 3.3) for gfx950.
 //
-// scores: one wave per beam row.  The row's log-softmax over the vocabulary is
-//   added to the beam's accumulated score; filtered tokens score -inf.  The
-//   kernel also writes each row's best candidate score.
-// top-k:  per request, slices of its M*V candidates spread over several
-//   workgroups (maxima, histograms, gather), then one 1024-thread workgroup
-//   for the boundary bin and one for the final ranking.
-//   Candidates are totally ordered by an order-preserving 32-bit key of the
-//   score (descending; -0 == +0; NaN below -inf), then by flat index m*V + v
-//   (ascending), so the selection is unique.  Sampled path: a 4096-bin
-//   histogram, over a sixteenth of the candidates, of the scores in the
-//   64-unit window below the request's best score picks the bin above which
-//   about 1.25 k candidates are expected; one pass gathers every candidate in
-//   that bin and above and counts them, and the set is kept when it holds at
-//   least k and fits the list.  Otherwise the full path: the same histogram
-//   over every candidate finds the bin holding the k-th candidate, and only
-//   candidates in that bin and above are gathered.  When the k-th candidate lies
-//   outside the window or the gathered set would not fit, an exact radix
-//   select on the key (four 8-bit digits) and an index-ordered collection of
-//   the tied candidates take over.  Either way the k winners are sorted by
-//   (key desc, index asc): ranked by a counting sort over the window bins and
-//   a comparison inside each bin, or by a bitonic sort in LDS when a bin is crowded.
+// scores: one wave per beam row (or several rows), the row in registers.  The
+//   row's log-softmax over the vocabulary is added to the beam's accumulated
+//   score; filtered tokens score -inf.  The kernel also writes each row's best
+//   candidate score.
+// top-k:  candidates are totally ordered by an order-preserving 32-bit key of
+//   the score (descending; -0 == +0; NaN below -inf), then by flat index
+//   m*V + v (ascending), so the selection is unique.
+//   N <= 65536 candidates per request: one workgroup per request holds them all
+//   in registers, finds by a histogram of the 64-unit window below the best
+//   score the bin with the k-th candidate, and ranks that bin and above.
+//   More: a sample of the candidates picks a threshold above which somewhat
+//   more than k are expected (select), one pass over the candidates gathers
+//   everything at or above it (gather), and the gathered set, which holds the k
+//   best exactly when it has at least k members, is ranked (final).
+//   When fewer than k candidates are above -inf (dead beams), the rest are the
+//   -inf candidates of lowest index.  When the gathered set is too small or
+//   does not fit the list, an exact radix select on the key (digits of 12, 12
+//   and 8 bits) and an index-ordered collection of the tied candidates take over.
+//   Ranking: a counting sort over bins of the gathered range and a comparison
+//   inside each bin, or a bitonic sort in LDS when a bin is crowded.
+#include <float.h>
+#include <math.h>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace grace {
 
 // ---------------------------------------------------------------------------
-// candidate scores
+// wave reductions over 64 lanes, every lane gets the result.  Partners are
+// lanes l ^ 32, 16, 8, 4, 2, 1 in that order; all six steps stay in the vector
+// ALU (half and row swaps, row rotations, quad permutes) instead of going
+// through LDS.  A rotation by 4 within 16 lanes reaches l ^ 4 because lanes l
+// and l ^ 8 already agree.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
 }
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-  return x;
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+// The six steps for NR values of each lane at once (NR = 1, 2 or 4), sharing
+// the swaps and all later steps: row j's result ends in the lanes of group
+// lane_of_row<NR>(j) (all lanes for NR = 1, a half for 2, 16 lanes for 4).  Each
+// row's order of operations is that of NR = 1.
+template <int NR>
+__device__ __forceinline__ constexpr int lane_of_row(int j) {
+  return NR == 1 ? 0 : (NR == 2 ? 32 * j : 32 * (j & 1) + 16 * (j >> 1));
+}
+template <int NR>
+__device__ __forceinline__ int row_of_lane(int lane) {
+  return NR == 1 ? 0 : (NR == 2 ? lane >> 5 : (lane >> 5) + 2 * ((lane >> 4) & 1));
+}
+template <class Op>
+__device__ __forceinline__ float swap_halves(float a, float b, Op op) {
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return op(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+template <int NR, class Op>
+__device__ __forceinline__ float reduce_rows(const float (&v)[NR], Op op) {
+  static_assert(NR == 1 || NR == 2 || NR == 4, "rows per wave");
+  const float y = swap_halves(v[0], v[NR > 1 ? 1 : 0], op);
+  float w = y;
+  if constexpr (NR == 4) w = swap_halves(v[2], v[3], op);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(w), false, false);
+  float x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  x = op(x, dpp<0x128>(x));   // row_ror:8
+  x = op(x, dpp<0x124>(x));   // row_ror:4
+  x = op(x, dpp<0x4E>(x));    // quad_perm 2,3,0,1
+  return op(x, dpp<0xB1>(x)); // quad_perm 1,0,3,2
+}
+template <int NR>
+__device__ __forceinline__ float max_rows(const float (&v)[NR]) {
+  return reduce_rows<NR>(v, [](float a, float b) { return max3(a, b, b); });
+}
+template <int NR>
+__device__ __forceinline__ float sum_rows(const float (&v)[NR]) {
+  return reduce_rows<NR>(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float wave_max(float x) { return max_rows<1>({x}); }
+__device__ __forceinline__ float wave_sum(float x) { return sum_rows<1>({x}); }
+// x of lane l, in a scalar register
+__device__ __forceinline__ float lane_value(float x, int l) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), l));
 }
 
 template <class T>
@@ -49,16 +99,111 @@ __device__ __forceinline__ float load_logit<uint16_t>(const uint16_t* p) {
   return __uint_as_float((uint32_t)*p << 16);
 }
 
+// x where bit e of `bits` is set, else -inf (one bit-field extract, one bit select)
+__device__ __forceinline__ float keep_bit(float x, uint32_t bits, int e) {
+  const uint32_t m = (uint32_t)((int32_t)(bits << (31 - e)) >> 31);
+  return __uint_as_float((__float_as_uint(x) & m) | (0xff800000u & ~m));
+}
+
+constexpr int kHistBins = 4096;    // bins of the threshold and ranking histograms
+constexpr int kGatherCap = 8192;   // gathered candidates a request can rank
+
+// Workspace of one call.  Per request: the gathered list [kGatherCap] of
+// composites, S sample areas of kSampleArea fp16 (the last one doubles as the
+// select workgroups' common histogram), info [kInfo] = {threshold (float bits),
+// gathered count, unused, select workgroups done, unused...}.  S grows with the
+// candidates of a request, one area per 32768 up to 64.
+constexpr int kMaxSlices = 64;
+constexpr uint32_t kSliceTarget = 32768;
+constexpr int kInfo = 8;
+constexpr int kSampleArea = 2 * kHistBins;
+
+__host__ __device__ inline int topk_slices(uint32_t N) {
+  const uint32_t s = (N + kSliceTarget - 1) / kSliceTarget;
+  return (int)(s < 1 ? 1 : (s > (uint32_t)kMaxSlices ? (uint32_t)kMaxSlices : s));
+}
+
+struct TopkWs {
+  uint64_t* list = nullptr;
+  uint16_t* sample = nullptr;
+  int32_t* info = nullptr;
+  int S = 0;
+  TopkWs() = default;
+  __host__ __device__ TopkWs(void* ws, int B, int S_) : S(S_) {
+    char* p = (char*)ws;
+    list = (uint64_t*)p;
+    p += (size_t)B * kGatherCap * 8;
+    sample = (uint16_t*)p;
+    p += (size_t)B * S_ * kHistBins * 4 + (size_t)B * S_ * 4;
+    info = (int32_t*)p;
+  }
+  __host__ __device__ static size_t bytes(int B, int S_) {
+    return (size_t)B * kGatherCap * 8 + (size_t)B * S_ * kHistBins * 4 + (size_t)B * S_ * 4 +
+           (size_t)B * kInfo * 4;
+  }
+  __host__ __device__ int64_t sample_stride() const { return (int64_t)S * kSampleArea; }
+  __host__ __device__ int64_t sample_room() const { return (int64_t)(S - 1) * kSampleArea; }
+  __device__ __forceinline__ uint32_t* hist(int64_t b) const {
+    return (uint32_t*)(sample + b * sample_stride() + sample_room());
+  }
+};
+
+// Clears what the select workgroups of a request share (the score pass does it
+// where there is one).
+__device__ __forceinline__ void clear_shared(const TopkWs& ws, int64_t b, uint32_t first, uint32_t step) {
+  uint32_t* sum = ws.hist(b);
+  for (uint32_t i = first; i < (uint32_t)kHistBins; i += step) sum[i] = 0u;
+  if (first == 0) ws.info[b * kInfo + 3] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// candidate scores
+// ---------------------------------------------------------------------------
 constexpr int kScoreThreads = 256;
 
+// A score pass that keeps no candidate array writes a sample of it instead: of
+// every 2^lp consecutive tokens of a row the one at an offset that changes from
+// row to row (so that no token order biases it), ceil(V / 2^lp) per row, -inf
+// past the row's end and in three places behind a request's last row; 3 <= lp
+// <= 9.  Stored as fp16 differences from a score
+// near the request's best prefix (sample_ref): the sample only has to place a
+// threshold, which a difference of up to 16 gets to 1/128.
+struct SampleOut {
+  uint16_t* p = nullptr;     // [B][stride], request b's rows in order; null: no sample
+  int64_t stride = 0;
+  bool clear = false;        // also clear what the select workgroups share
+  TopkWs ws;
+  uint32_t per_row = 0;
+  int32_t lp = 0, M = 1;
+  FastDiv per_request{1};    // row -> request
+};
+__device__ __forceinline__ uint32_t sample_offset(uint32_t row, int lp) {
+  return (row * 0x9E3779B1u) >> (32 - lp);
+}
+// The best of up to 64 of the request's prefix scores, 0 if none is finite;
+// called by a whole wave.
+__device__ __forceinline__ float sample_ref(const float* prev, int32_t M) {
+  const int lane = threadIdx.x & 63;
+  const float p = prev[(int64_t)M * lane / 64];
+  const float m = wave_max(fabsf(p) < INFINITY ? p : -INFINITY);
+  return m > -INFINITY ? m : 0.f;
+}
+// Two fp32 values as fp16, rounded toward zero (monotonic; beyond the range to
+// its end, infinities kept).
+__device__ __forceinline__ uint32_t pack_f16x2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+}
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+
 // Generic row kernel (any V): lanes stride over the row.  CAND = false writes
-// only the row's log-sum-exp (lse_out) and best score, for a top-k that
-// recomputes each candidate from the logits.
+// only the row's log-sum-exp (lse_out) and an upper bound of its candidates
+// (row_max), for a top-k that recomputes each candidate from the logits.
 template <class T, bool CAND = true>
 __global__ void __launch_bounds__(kScoreThreads)
 beam_scores_kernel(const T* __restrict__ logits, const float* __restrict__ prev,
                    const uint32_t* __restrict__ mask, float* __restrict__ cand,
-                   float* __restrict__ row_max, float* __restrict__ lse_out, int32_t R, int32_t V) {
+                   float* __restrict__ row_max, float* __restrict__ lse_out, int32_t R, int32_t V,
+                   SampleOut smp) {
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * (kScoreThreads / 64) + (threadIdx.x >> 6);
   if (r >= R) return;   // whole waves
@@ -72,105 +217,248 @@ beam_scores_kernel(const T* __restrict__ logits, const float* __restrict__ prev,
   const float lse = mx + logf(z);
   const float p = prev[r];
   const int32_t words = (V + 31) >> 5;
-  float best = -INFINITY;
-  float* out = cand + r * V;
-  for (int v = lane; v < V; v += 64) {
+  auto score = [&](int v) {
     const bool ok = mask == nullptr || ((mask[r * words + (v >> 5)] >> (v & 31)) & 1u);
-    const float s = ok ? p + (load_logit(x + v) - lse) : -INFINITY;
-    if constexpr (CAND) out[v] = s;
-    best = fmaxf(best, s);
-  }
-  best = wave_max(best);
-  if (row_max != nullptr && lane == 0) row_max[r] = best;
-  if (!CAND && lane == 0) lse_out[r] = lse;
-}
-
-// The row sums of exp take the hardware exp2 of a log2(e)-scaled argument
-// (relative error about 1e-6 per term against 2^-24 for expf), which keeps
-// the pass from being bound by the vector ALU.
-// Row kernel for V a multiple of 8, V <= 512*NCH: each lane owns runs of 8
-// consecutive tokens (one 16-byte bf16 load or two fp32 loads per run), the
-// row stays in registers across the max, sum and output passes.
-template <int NCH>
-constexpr int score_rows_per_wave() { return NCH == 1 ? 4 : (NCH == 2 ? 2 : 1); }
-
-template <class T, int NCH, bool CAND = true>
-__global__ void __launch_bounds__(kScoreThreads)
-beam_scores_vec_kernel(const T* __restrict__ logits, const float* __restrict__ prev,
-                       const uint32_t* __restrict__ mask, float* __restrict__ cand,
-                       float* __restrict__ row_max, float* __restrict__ lse_out, int32_t R,
-                       int32_t V) {
-  // RPW rows per wave, all their loads issued before the first reduction
-  constexpr int RPW = score_rows_per_wave<NCH>();
-  const int lane = threadIdx.x & 63;
-  const int64_t r0 = ((int64_t)blockIdx.x * (kScoreThreads / 64) + (threadIdx.x >> 6)) * RPW;
-  const int32_t words = (V + 31) >> 5;
-  float f[RPW][NCH][8];
-  uint32_t bits[RPW][NCH];
-  float p[RPW];
-#pragma unroll
-  for (int j = 0; j < RPW; ++j) {
-    const int64_t r = r0 + j;
-    if (r >= R) continue;   // whole waves
-    const T* x = logits + r * V;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int v0 = c * 512 + 8 * lane;
-      if (v0 < V) {
-        if constexpr (sizeof(T) == 2) {
-          Chunk<BF16>::unpack(*(const u32x4*)(x + v0), f[j][c]);
-        } else {
-          Chunk<F32>::unpack(*(const u32x4*)(x + v0), f[j][c]);
-          Chunk<F32>::unpack(*(const u32x4*)(x + v0 + 4), f[j][c] + 4);
-        }
-        bits[j][c] = mask == nullptr ? 0xffu : (mask[r * words + (v0 >> 5)] >> (v0 & 31)) & 0xffu;
-      }
-    }
-    p[j] = prev[r];
-  }
-#pragma unroll
-  for (int j = 0; j < RPW; ++j) {
-    const int64_t r = r0 + j;
-    if (r >= R) continue;
-    float mx = -INFINITY;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-      if (c * 512 + 8 * lane < V) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, f[j][c][e]);
-      }
-    mx = wave_max(mx);
-    float z = 0.f;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-      if (c * 512 + 8 * lane < V) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) z += fast_exp2((f[j][c][e] - mx) * kLog2e);
-      }
-    z = wave_sum(z);
-    const float lse = mx + logf(z);
+    return ok ? p + (load_logit(x + v) - lse) : -INFINITY;
+  };
+  if constexpr (CAND) {
     float best = -INFINITY;
     float* out = cand + r * V;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int v0 = c * 512 + 8 * lane;
-      if (v0 >= V) continue;
-      float o[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        o[e] = ((bits[j][c] >> e) & 1u) ? p[j] + (f[j][c][e] - lse) : -INFINITY;
-        best = fmaxf(best, o[e]);
-      }
-      // streamed past the caches: the array is larger than L2 and MALL, and
-      // the top-k reads it back with streaming loads as well
-      if constexpr (CAND) {
-        __builtin_nontemporal_store(Chunk<F32>::pack(o), (u32x4*)(out + v0));
-        __builtin_nontemporal_store(Chunk<F32>::pack(o + 4), (u32x4*)(out + v0 + 4));
-      }
+    for (int v = lane; v < V; v += 64) {
+      const float s = score(v);
+      out[v] = s;
+      best = fmaxf(best, s);
     }
     best = wave_max(best);
     if (row_max != nullptr && lane == 0) row_max[r] = best;
-    if (!CAND && lane == 0) lse_out[r] = lse;
+  } else {
+    if (lane == 0) {
+      row_max[r] = p + (mx - lse);
+      lse_out[r] = lse;
+    }
+    if (smp.p == nullptr) return;
+    const uint32_t b = smp.per_request.div((uint32_t)r), m = (uint32_t)r - b * (uint32_t)smp.M;
+    const uint32_t h = sample_offset(m, smp.lp);
+    const float ref = sample_ref(prev + (int64_t)b * smp.M, smp.M);
+    uint16_t* out = smp.p + b * smp.stride + (int64_t)m * smp.per_row;
+    for (uint32_t i = lane; i < smp.per_row; i += 64) {
+      const uint32_t v = (i << smp.lp) + h;
+      out[i] = (uint16_t)pack_f16x2(v < (uint32_t)V ? score((int)v) - ref : -INFINITY, 0.f);
+    }
+    if (m == (uint32_t)smp.M - 1 && lane < 3) out[smp.per_row + lane] = 0xfc00u;
+    if (smp.clear) clear_shared(smp.ws, b, m * 64 + lane, (uint32_t)smp.M * 64);
+  }
+}
+
+// Row kernel with the row in registers across the max, sum and output passes:
+// NCH runs of 8 tokens per lane, V <= 512*NCH.  RUN = true (V a multiple of 8,
+// 16-byte aligned logits): a run is 8 consecutive tokens, one 16-byte bf16 load
+// or two fp32 loads; else its tokens are 64 apart, so that a wave's loads cover
+// consecutive tokens.  The sums of exp run over a lane's tokens in order and
+// then over the lanes as in the generic kernel.
+//
+// The row sums of exp take the hardware exp2 of a log2(e)-scaled argument
+// (relative error about 1e-6 per term against 2^-24 for expf), which keeps
+// the pass from being bound by the vector ALU.
+//
+// CAND = false: the candidates' upper bound prev + (max - lse) holds for every
+// token, as rounding is monotonic, so neither the filter nor the candidates are
+// needed for it.
+// Rows per wave.  A pass that writes the candidates is bound by those writes and
+// takes one (64 x 4096 x 512 bf16: 135 us with one row, 153 with two, 191 with
+// four, whose stores leave in bursts); without them the vector ALU counts, and
+// the reductions of four rows at once take it from 88 to 60 us.
+template <int NCH, bool CAND>
+constexpr int score_rows_per_wave() { return CAND ? 1 : (NCH == 1 ? 4 : (NCH == 2 ? 2 : 1)); }
+
+template <class T, int NCH, bool RUN, bool CAND>
+__global__ void __launch_bounds__(kScoreThreads)
+beam_scores_reg_kernel(const T* __restrict__ logits, const float* __restrict__ prev,
+                       const uint32_t* __restrict__ mask, float* __restrict__ cand,
+                       float* __restrict__ row_max, float* __restrict__ lse_out, int32_t R,
+                       int32_t V, SampleOut smp) {
+  // RPW rows per wave, all their loads issued before the first reduction, which
+  // runs over all of them at once
+  constexpr int RPW = score_rows_per_wave<NCH, CAND>();
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t r0 = ((int64_t)blockIdx.x * (kScoreThreads / 64) + wave) * RPW;
+  if (r0 >= R) return;   // whole waves
+  const int32_t words = (V + 31) >> 5;
+  const bool sampled = !CAND && smp.p != nullptr;
+  auto token = [&](int c, int e) { return RUN ? c * 512 + 8 * lane + e : (c * 8 + e) * 64 + lane; };
+  // rows past the last repeat it and are not written
+  auto row = [&](int j) { return min(r0 + j, (int64_t)R - 1); };
+  float f[RPW][NCH][8];
+  uint32_t bits[RPW][NCH];
+#pragma unroll
+  for (int j = 0; j < RPW; ++j) {
+    const int64_t r = row(j);
+    const T* x = logits + r * V;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      if constexpr (RUN) {
+        const int v0 = token(c, 0);
+        if (v0 < V) {
+          if constexpr (sizeof(T) == 2) {
+            Chunk<BF16>::unpack(*(const u32x4*)(x + v0), f[j][c]);
+          } else {
+            Chunk<F32>::unpack(*(const u32x4*)(x + v0), f[j][c]);
+            Chunk<F32>::unpack(*(const u32x4*)(x + v0 + 4), f[j][c] + 4);
+          }
+          if (CAND || sampled)
+            bits[j][c] = mask == nullptr ? 0xffu : mask[r * words + (v0 >> 5)] >> (v0 & 31);
+        }
+      } else {
+        bits[j][c] = 0u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int v = token(c, e);
+          if (v < V) {
+            f[j][c][e] = load_logit(x + v);
+            if constexpr (CAND)
+              bits[j][c] |= (mask == nullptr ? 1u : (mask[r * words + (v >> 5)] >> (v & 31)) & 1u) << e;
+          }
+        }
+      }
+    }
+  }
+  const int64_t r_lane = row(row_of_lane<RPW>(lane));   // the row whose results this lane gets
+  const float p_lane = prev[r_lane];
+  const bool writes = (lane & (64 / RPW - 1)) == 0 && r0 + row_of_lane<RPW>(lane) < R;
+  float part[RPW];
+#pragma unroll
+  for (int j = 0; j < RPW; ++j) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      if constexpr (RUN) {
+        if (token(c, 0) < V) {
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) mx = max3(mx, f[j][c][e], f[j][c][e + 1]);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (token(c, e) < V) mx = fmaxf(mx, f[j][c][e]);
+      }
+    }
+    part[j] = mx;
+  }
+  const float mx_lane = max_rows<RPW>(part);
+#pragma unroll
+  for (int j = 0; j < RPW; ++j) {
+    const float mx = lane_value(mx_lane, lane_of_row<RPW>(j));
+    float z = 0.f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      if constexpr (RUN) {
+        if (token(c, 0) < V) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) z += fast_exp2((f[j][c][e] - mx) * kLog2e);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (token(c, e) < V) z += fast_exp2((f[j][c][e] - mx) * kLog2e);
+      }
+    }
+    part[j] = z;
+  }
+  const float lse_lane = mx_lane + logf(sum_rows<RPW>(part));
+  if constexpr (CAND) {
+#pragma unroll
+    for (int j = 0; j < RPW; ++j) {
+      part[j] = -INFINITY;
+      if (r0 + j >= R) continue;   // whole waves
+      const float lse = lane_value(lse_lane, lane_of_row<RPW>(j));
+      const float p = lane_value(p_lane, lane_of_row<RPW>(j));
+      float best = -INFINITY;
+      float* out = cand + (r0 + j) * V;
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        float o[8];
+        // streamed past the caches: the array is larger than L2 and MALL, and
+        // the top-k reads it back with streaming loads as well
+        if constexpr (RUN) {
+          const int v0 = token(c, 0);
+          if (v0 >= V) continue;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = keep_bit(p + (f[j][c][e] - lse), bits[j][c], e);
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) best = fmaxf(best, fmaxf(o[e], o[e + 1]));
+          __builtin_nontemporal_store(Chunk<F32>::pack(o), (u32x4*)(out + v0));
+          __builtin_nontemporal_store(Chunk<F32>::pack(o + 4), (u32x4*)(out + v0 + 4));
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int v = token(c, e);
+            if (v < V) {
+              o[e] = keep_bit(p + (f[j][c][e] - lse), bits[j][c], e);
+              best = fmaxf(best, o[e]);
+              __builtin_nontemporal_store(o[e], out + v);
+            }
+          }
+        }
+      }
+      part[j] = best;
+    }
+    const float best_lane = max_rows<RPW>(part);
+    if (row_max != nullptr && writes) row_max[r_lane] = best_lane;
+  } else {
+    if (writes) {
+      row_max[r_lane] = p_lane + (mx_lane - lse_lane);
+      lse_out[r_lane] = lse_lane;
+    }
+    if (!sampled) return;
+    uint32_t b_ref = 0xffffffffu;
+    float ref = 0.f;
+#pragma unroll
+    for (int j = 0; j < RPW; ++j) {
+      if (r0 + j >= R) continue;
+      const uint32_t r = (uint32_t)(r0 + j);
+      const uint32_t b = smp.per_request.div(r), m = r - b * (uint32_t)smp.M;
+      if (b != b_ref) ref = sample_ref(prev + (int64_t)b * smp.M, smp.M);   // whole waves
+      b_ref = b;
+      const float lse = lane_value(lse_lane, lane_of_row<RPW>(j));
+      const float p = lane_value(p_lane, lane_of_row<RPW>(j));
+      const uint32_t h = sample_offset(m, smp.lp);
+      uint16_t* out = smp.p + b * smp.stride + (int64_t)m * smp.per_row;
+      if (m == (uint32_t)smp.M - 1 && lane < 3) out[smp.per_row + lane] = 0xfc00u;
+    if (smp.clear) clear_shared(smp.ws, b, m * 64 + lane, (uint32_t)smp.M * 64);
+      if constexpr (RUN) {
+        // one element of every 2^(lp-3)-th run; the RPW rows of a wave share
+        // out the eight elements, so that two (four, eight) remain to pick from
+        constexpr int kPick = 8 / RPW;
+        const uint32_t runs = 1u << (smp.lp - 3), q = h & (kPick - 1);
+        const auto pick = [](bool hi, float x, float y) { return hi ? y : x; };   // by value
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+          float t[kPick];
+#pragma unroll
+          for (int e = 0; e < kPick; ++e) t[e] = f[j][c][j * kPick + e];
+#pragma unroll
+          for (int w = 1; w < kPick; w *= 2)
+#pragma unroll
+            for (int e = 0; e + w < kPick; e += 2 * w) t[e] = pick(q & w, t[e], t[e + w]);
+          const uint32_t e = j * kPick + q, run = c * 64 + lane;
+          if ((run & (runs - 1)) == (h >> 3) && 8 * (run & ~(runs - 1)) < (uint32_t)V) {
+            const bool ok = 8 * run < (uint32_t)V && ((bits[j][c] >> e) & 1u);
+            out[(8 * run) >> smp.lp] =
+                (uint16_t)pack_f16x2(ok ? p + (t[0] - lse) - ref : -INFINITY, 0.f);
+          }
+        }
+      } else {
+        // from memory again: at most an eighth of the row, in cache
+        for (uint32_t i = lane; i < smp.per_row; i += 64) {
+          const uint32_t v = (i << smp.lp) + h;
+          float sc = -INFINITY;
+          if (v < (uint32_t)V && (mask == nullptr || ((mask[r * (int64_t)words + (v >> 5)] >> (v & 31)) & 1u)))
+            sc = p + (load_logit(logits + (int64_t)r * V + v) - lse) - ref;
+          out[i] = (uint16_t)pack_f16x2(sc, 0.f);
+        }
+      }
+    }
   }
 }
 
@@ -178,9 +466,8 @@ beam_scores_vec_kernel(const T* __restrict__ logits, const float* __restrict__ p
 // top-k
 // ---------------------------------------------------------------------------
 constexpr int kTopkThreads = 1024;
-constexpr int kHistBins = 4096;         // fast-path window bins
-constexpr float kWindow = 64.0f;        // fast-path window below the best score
-constexpr int kGatherCap = 8192;        // LDS entries for the exact sort
+constexpr float kWindow = 64.0f;        // small requests: threshold window below the best score
+constexpr uint32_t kSmallN = 65536;     // candidates one workgroup holds in registers
 
 // Order-preserving key: larger key = better candidate.  -0 maps to +0's key,
 // NaN to 0 (below -inf, whose key is 0x007fffff).
@@ -197,10 +484,11 @@ __device__ __forceinline__ uint64_t composite(uint32_t key, uint32_t idx) {
   return ((uint64_t)key << 32) | (uint64_t)(~idx);
 }
 
-__device__ __forceinline__ int window_bin(float x, float lo, float inv_w) {
-  if (!(x >= lo)) return 0;   // below the window, -inf and NaN
-  const float t = fminf((x - lo) * inv_w, (float)(kHistBins - 1));
-  return (int)t;
+// Bin of x in kHistBins equal steps of 1/inv_w up from lo; bin 0 also takes
+// everything below (and -inf and NaN).  Monotonic in x.
+__device__ __forceinline__ int step_bin(float x, float lo, float inv_w) {
+  const float t = (x - lo) * inv_w;
+  return t > 0.f ? (int)fminf(t, (float)(kHistBins - 1)) : 0;
 }
 
 // Add 1 to hist[bin] for every lane with pred set: one LDS atomic for the
@@ -216,20 +504,6 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, int bin, bool pred) {
   } else if (pred) {
     atomicAdd(&hist[bin], 1u);
   }
-}
-
-// Append composites of the lanes with pred set to list at *count (wave-aggregated).
-__device__ __forceinline__ void wave_append(uint64_t* list, uint32_t* count, bool pred,
-                                            uint64_t value, uint32_t cap) {
-  const uint64_t m = __ballot(pred);
-  if (m == 0) return;
-  const int lane = threadIdx.x & 63;
-  const int lead = (int)__builtin_ctzll(m);
-  uint32_t base = 0;
-  if (lane == lead) base = atomicAdd(count, (uint32_t)__popcll(m));
-  base = __shfl(base, lead);
-  const uint32_t pos = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-  if (pred && pos < cap) list[pos] = value;
 }
 
 // Bitonic sort of list[0, n) descending; n a power of two <= capacity.
@@ -251,69 +525,31 @@ __device__ void bitonic_desc(uint64_t* list, int n) {
   }
 }
 
-// Inclusive block scan of one uint32 per thread (1024 threads); returns the
-// exclusive prefix; *total receives the sum.
+// Inclusive scan over the 64 lanes (row shifts within 16 lanes, then row
+// broadcasts), in the vector ALU.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);   // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);   // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);   // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // row_bcast:31
+  return x;
+}
+
+// Exclusive prefix of one uint32 per thread over the block (1024 threads);
+// *total receives the sum.  Every wave scans the wave totals for itself.
 __device__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* scratch, uint32_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t v = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(v, o);
-    if (lane >= o) v += y;
-  }
+  const uint32_t v = wave_scan(x);
   if (lane == 63) scratch[wave] = v;
   __syncthreads();
-  if (wave == 0) {
-    uint32_t w = lane < kTopkThreads / 64 ? scratch[lane] : 0u;
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      const uint32_t y = __shfl_up(w, o);
-      if (lane >= o) w += y;
-    }
-    if (lane < kTopkThreads / 64) scratch[16 + lane] = w;
-  }
-  __syncthreads();
-  const uint32_t before = wave == 0 ? 0u : scratch[16 + wave - 1];
-  *total = scratch[16 + kTopkThreads / 64 - 1];
+  const uint32_t w = wave_scan(scratch[lane & (kTopkThreads / 64 - 1)]);   // lanes 0-15: the sums
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)w, kTopkThreads / 64 - 1);
+  const uint32_t before = wave == 0 ? 0u : (uint32_t)__shfl((int)w, wave - 1);
   __syncthreads();
   return before + v - x;
 }
-
-// ---- multi-workgroup fast path: slices of a request over several workgroups ----
-constexpr int kSliceThreads = 256;
-constexpr int kMaxSlices = 64;
-constexpr uint32_t kSliceTarget = 32768;   // candidates per slice (about)
-
-__host__ __device__ inline int topk_slices(uint32_t N) {
-  const uint32_t s = (N + kSliceTarget - 1) / kSliceTarget;
-  return (int)(s < 1 ? 1 : (s > (uint32_t)kMaxSlices ? (uint32_t)kMaxSlices : s));
-}
-
-// Workspace of one call (per request b): slice maxima [S], slice histograms
-// [S][kHistBins], info [kInfo] = {b*, count above b*, gathered count, fast
-// flag, done flag, unused...}, gathered list [kGatherCap] of composites.
-constexpr int kInfo = 8;
-struct TopkWs {
-  float* smax;
-  uint32_t* hist;
-  int32_t* info;
-  uint64_t* list;
-  int S;
-  __host__ __device__ TopkWs(void* ws, int B, int S_) : S(S_) {
-    char* p = (char*)ws;
-    list = (uint64_t*)p;
-    p += (size_t)B * kGatherCap * 8;
-    hist = (uint32_t*)p;
-    p += (size_t)B * S_ * kHistBins * 4;
-    smax = (float*)p;
-    p += (size_t)B * S_ * 4;
-    info = (int32_t*)p;
-  }
-  __host__ __device__ static size_t bytes(int B, int S_) {
-    return (size_t)B * kGatherCap * 8 + (size_t)B * S_ * kHistBins * 4 + (size_t)B * S_ * 4 +
-           (size_t)B * kInfo * 4;
-  }
-};
 
 // Where the top-k reads candidate scores: the array the score kernel wrote,
 // or each score recomputed from the logits with the same operations and the
@@ -324,6 +560,11 @@ struct CandArray {
     const float* p;
     __device__ __forceinline__ float operator[](uint32_t i) const { return p[i]; }
     __device__ __forceinline__ float nt(uint32_t i) const { return __builtin_nontemporal_load(&p[i]); }
+    // candidates i .. i+7 (i and N multiples of 8, p 16-byte aligned)
+    __device__ __forceinline__ void load8(uint32_t i, float (&x)[8]) const {
+      Chunk<F32>::unpack(*(const u32x4*)(p + i), x);
+      Chunk<F32>::unpack(*(const u32x4*)(p + i + 4), x + 4);
+    }
   };
   __device__ __forceinline__ Row request(int64_t b, uint32_t N) const {
     return Row{cand + b * (int64_t)N};
@@ -354,6 +595,46 @@ struct CandFromLogits {
       return ok ? prev[r] + (load_logit(logits + r * V + v) - lse[r]) : -INFINITY;
     }
     __device__ __forceinline__ float nt(uint32_t i) const { return (*this)[i]; }
+    // what the E candidates from flat index i on, of beam m, are made of: their
+    // logits as stored, the row's prefix score and log-sum-exp
+    template <int E>
+    struct Raw {
+      u32x4 w[E > 1 ? E * sizeof(T) / 16 : 1];
+      float p, l;
+      __device__ __forceinline__ void logits(float (&f)[E]) const {
+        if constexpr (E == 1) {
+          f[0] = __uint_as_float(w[0].x);
+        } else if constexpr (sizeof(T) == 2) {
+          Chunk<BF16>::unpack(w[0], f);
+        } else {
+          Chunk<F32>::unpack(w[0], f);
+          Chunk<F32>::unpack(w[1], f + 4);
+        }
+      }
+    };
+    template <int E>
+    __device__ __forceinline__ void load_raw(uint32_t i, uint32_t m, Raw<E>& raw) const {
+      const T* x = logits + r0 * V + i;
+      if constexpr (E == 1) {
+        raw.w[0].x = __float_as_uint(load_logit(x));
+      } else {
+        raw.w[0] = *(const u32x4*)x;
+        if constexpr (sizeof(T) == 4) raw.w[1] = *(const u32x4*)(x + 4);
+      }
+      raw.p = prev[r0 + m];
+      raw.l = lse[r0 + m];
+    }
+    // and their scores
+    template <int E>
+    __device__ __forceinline__ void finish(uint32_t i, uint32_t m, const Raw<E>& raw, float (&x)[E]) const {
+      float f[E];
+      raw.logits(f);
+      const uint32_t v = i - m * (uint32_t)V;
+      const int32_t words = (V + 31) >> 5;
+      const uint32_t bits = mask == nullptr ? 0xffu : mask[(r0 + m) * words + (v >> 5)] >> (v & 31);
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[e] = keep_bit(raw.p + (f[e] - raw.l), bits, e);
+    }
     // candidates i .. i+7 (i and V multiples of 8, so one row): one 16-byte
     // run of logits, as the score kernel's 8-token runs
     __device__ __forceinline__ void load8(uint32_t i, float (&x)[8]) const {
@@ -380,391 +661,16 @@ struct CandFromLogits {
   }
 };
 
-// Slice s of a request's N candidates; slices start on multiples of 8.
-__device__ __forceinline__ void slice_range(uint32_t N, int S, int s, uint32_t& i0, uint32_t& i1) {
-  const uint32_t per = ((N + S - 1) / S + 7u) & ~7u;
-  i0 = min(N, (uint32_t)s * per);
-  i1 = min(N, i0 + per);
-}
-
-__device__ float block_max_256(float x, float* scratch) {
-  x = wave_max(x);
-  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = x;
-  __syncthreads();
-  x = fmaxf(fmaxf(scratch[0], scratch[1]), fmaxf(scratch[2], scratch[3]));
-  __syncthreads();
-  return x;
-}
-
-template <class Src>
-__global__ void __launch_bounds__(kSliceThreads)
-topk_slice_max_kernel(Src src, const float* __restrict__ row_max,
-                      int32_t M, int32_t V, TopkWs ws) {
-  __shared__ float scratch[4];
-  const int s = blockIdx.x;
-  const int64_t b = blockIdx.y;
-  const uint32_t N = (uint32_t)M * (uint32_t)V;
-  uint32_t i0, i1;
-  slice_range(N, ws.S, s, i0, i1);
-  float best = -INFINITY;
-  if (row_max != nullptr) {
-    if (i1 > i0)
-      for (uint32_t m = i0 / V + threadIdx.x; m <= (i1 - 1) / V; m += kSliceThreads)
-        best = fmaxf(best, row_max[b * M + m]);
-  } else {
-    const auto c = src.request(b, N);
-    for (uint32_t i = i0 + threadIdx.x; i < i1; i += kSliceThreads) best = fmaxf(best, c[i]);
-  }
-  best = block_max_256(best, scratch);
-  if (threadIdx.x == 0) ws.smax[b * ws.S + s] = best;
-}
-
-// The request's best score: the maximum of its slice maxima (S <= 64, one per
-// lane), in every lane of the calling wave.
-__device__ __forceinline__ float request_best(const TopkWs& ws, int64_t b) {
-  const int lane = threadIdx.x & 63;
-  return wave_max(lane < ws.S ? ws.smax[b * ws.S + lane] : -INFINITY);
-}
-
-// VEC8: eight consecutive candidates per thread through Src::Row::load8
-// (V a multiple of 8).
-template <class Src, bool VEC8>
-__global__ void __launch_bounds__(kSliceThreads)
-topk_slice_hist_kernel(Src src, int32_t M, int32_t V, TopkWs ws) {
-  __shared__ uint32_t hist[kHistBins];
-  const int s = blockIdx.x;
-  const int64_t b = blockIdx.y;
-  if (ws.info[b * kInfo + 4] != 0) return;   // the sampled path succeeded
-  const uint32_t N = (uint32_t)M * (uint32_t)V;
-  for (int i = threadIdx.x; i < kHistBins; i += kSliceThreads) hist[i] = 0u;
-  __syncthreads();
-  const float best = request_best(ws, b);
-  if (best == best && best > -INFINITY && best < INFINITY) {
-    const float lo = best - kWindow, inv_w = (float)kHistBins / kWindow;
-    uint32_t i0, i1;
-    slice_range(N, ws.S, s, i0, i1);
-    const auto c = src.request(b, N);
-    if constexpr (VEC8) {
-      // four runs of eight in flight per thread
-      constexpr uint32_t kBatch = 8 * kSliceThreads;
-      for (uint32_t j0 = i0; j0 < i1; j0 += 4 * kBatch) {
-        float x[4][8];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const uint32_t i = j0 + u * kBatch + 8 * threadIdx.x;
-          if (i < i1) {
-            c.load8(i, x[u]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[u][e] = -INFINITY;
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int bin = window_bin(x[u][e], lo, inv_w);
-            if (bin > 0) atomicAdd(&hist[bin], 1u);
-          }
-      }
-    } else
-    // four candidates in flight per thread (streaming loads); one LDS atomic
-    // per counted candidate
-    for (uint32_t j0 = i0; j0 < i1; j0 += 4 * kSliceThreads) {
-      float x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t i = j0 + u * kSliceThreads + threadIdx.x;
-        x[u] = i < i1 ? c.nt(i) : -INFINITY;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int bin = window_bin(x[u], lo, inv_w);
-        if (bin > 0) atomicAdd(&hist[bin], 1u);
-      }
-    }
-  }
-  __syncthreads();
-  uint32_t* out = ws.hist + (b * ws.S + s) * (int64_t)kHistBins;
-  for (int i = threadIdx.x; i < kHistBins; i += kSliceThreads) out[i] = hist[i];
-}
-
-// The sample: of every group of 16 consecutive 128-byte chunks (512
-// candidates) of a request's flat candidate array, the one chunk picked by a
-// multiplicative hash of the group index (so that neither a row's token order
-// nor the row length biases it).  A sixteenth of the candidates.
-__device__ __forceinline__ uint32_t sample_chunk(uint32_t group) {
-  return 16u * group + ((group * 0x9E3779B1u) >> 28);
-}
-
-// Histogram of the sampled candidates of kSampleGroup consecutive slices, in
-// the same window and bins as the full slice histograms (written to the
-// buffer of slice blockIdx.x; the sum then runs over the first
-// sample_slices(S) buffers).
-constexpr int kSampleGroup = 8;
-__host__ __device__ inline int sample_slices(int S) { return (S + kSampleGroup - 1) / kSampleGroup; }
-
-template <class Src, bool VEC8>
-__global__ void __launch_bounds__(kSliceThreads)
-topk_sample_hist_kernel(Src src, int32_t M, int32_t V, TopkWs ws) {
-  __shared__ uint32_t hist[kHistBins];
-  const int s = blockIdx.x;
-  const int64_t b = blockIdx.y;
-  const uint32_t N = (uint32_t)M * (uint32_t)V;
-  for (int i = threadIdx.x; i < kHistBins; i += kSliceThreads) hist[i] = 0u;
-  __syncthreads();
-  const float best = request_best(ws, b);
-  if (best == best && best > -INFINITY && best < INFINITY) {
-    const float lo = best - kWindow, inv_w = (float)kHistBins / kWindow;
-    uint32_t i0, i1, j0, j1;
-    slice_range(N, ws.S, s * kSampleGroup, i0, j1);
-    slice_range(N, ws.S, min(s * kSampleGroup + kSampleGroup, ws.S) - 1, j0, i1);
-    const auto c = src.request(b, N);
-    if constexpr (VEC8) {
-      // four lanes per sampled chunk (runs of eight), four groups in flight
-      constexpr int kSlots = kSliceThreads / 4;
-      const int q = threadIdx.x >> 2, part = threadIdx.x & 3;
-      const uint32_t g0 = i0 >> 9, g1 = (i1 + 511) >> 9;
-      for (uint32_t gg = g0 + q; gg < g1; gg += 4 * kSlots) {
-        float x[4][8];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const uint32_t g = gg + u * kSlots;
-          const uint32_t i = 32u * sample_chunk(g) + 8 * part;
-          if (g < g1 && i >= i0 && i < i1) {
-            c.load8(i, x[u]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[u][e] = -INFINITY;
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int bin = window_bin(x[u][e], lo, inv_w);
-            if (bin > 0) atomicAdd(&hist[bin], 1u);
-          }
-      }
-    } else {
-    // one sampled chunk per 32-lane half-wave and group, eight groups in flight
-    const int half = threadIdx.x >> 5, l = threadIdx.x & 31;
-    constexpr int kHalves = kSliceThreads / 32;
-    const uint32_t g0 = i0 >> 9, g1 = (i1 + 511) >> 9;
-    for (uint32_t gg = g0 + half; gg < g1; gg += 8 * kHalves) {
-      float x[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t g = gg + u * kHalves;
-        const uint32_t i = 32u * sample_chunk(g) + l;
-        x[u] = g < g1 && i >= i0 && i < i1 ? c.nt(i) : -INFINITY;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int bin = window_bin(x[u], lo, inv_w);
-        if (bin > 0) atomicAdd(&hist[bin], 1u);
-      }
-    }
-    }
-  }
-  __syncthreads();
-  uint32_t* out = ws.hist + (b * ws.S + s) * (int64_t)kHistBins;
-  for (int i = threadIdx.x; i < kHistBins; i += kSliceThreads) out[i] = hist[i];
-}
-
-// Sum of the first n_slices slice histograms of a request, bins [256 p,
-// 256 p + 256) per workgroup, written over slice 0's histogram (each bin is
-// read and written by one thread only).
-constexpr int kReduceBins = 256;
-__global__ void __launch_bounds__(kReduceBins)
-topk_hist_reduce_kernel(TopkWs ws, int32_t n_slices, int32_t skip_if_done) {
-  const int64_t b = blockIdx.y;
-  if (skip_if_done && ws.info[b * kInfo + 4] != 0) return;
-  const int bin = blockIdx.x * kReduceBins + threadIdx.x;
-  uint32_t* h = ws.hist + b * ws.S * (int64_t)kHistBins + bin;
-  // eight slices in flight per thread
-  uint32_t part[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-  int j = 0;
-  for (; j + 8 <= n_slices; j += 8)
-#pragma unroll
-    for (int u = 0; u < 8; ++u) part[u] += h[(int64_t)(j + u) * kHistBins];
-  for (; j < n_slices; ++j) part[0] += h[(int64_t)j * kHistBins];
-  h[0] = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
-}
-
-// SAMPLED: the histogram holds a sixteenth of the candidates.  The chosen bin
-// is the highest whose sample count from the top reaches 1.25 k / 16, so that
-// about 1.25 k candidates are expected at or above it; no fit check here, as
-// the gather counts them exactly and topk_verify_kernel decides.
-template <bool SAMPLED>
-__global__ void __launch_bounds__(kTopkThreads)
-topk_boundary_kernel(int32_t k_req, TopkWs ws) {
-  __shared__ uint32_t scan[64];
-  const int tid = threadIdx.x;
-  const int64_t b = blockIdx.x;
-  if (!SAMPLED && ws.info[b * kInfo + 4] != 0) return;   // the sampled path succeeded
-  const int32_t k = SAMPLED ? (5 * k_req + 63) / 64 : k_req;
-  __shared__ int32_t par[2];
-  if (tid < 2) par[tid] = 0;
-  // thread 0 owns the top 4 bins, in descending order
-  const int t_rev = kTopkThreads - 1 - tid;
-  uint32_t own[4] = {0u, 0u, 0u, 0u}, s4 = 0;
-  const uint32_t* h = ws.hist + b * ws.S * (int64_t)kHistBins;   // the request's total
-#pragma unroll
-  for (int e = 0; e < 4; ++e) own[e] = h[4 * t_rev + 3 - e];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) s4 += own[e];
-  __syncthreads();
-  uint32_t total;
-  const uint32_t before = block_exclusive_scan(s4, scan, &total);
-  if (before < (uint32_t)k && before + s4 >= (uint32_t)k) {
-    uint32_t run = before;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (run < (uint32_t)k && run + own[e] >= (uint32_t)k) {
-        par[0] = 4 * t_rev + 3 - e;
-        par[1] = (int32_t)run;
-        // fast only if everything in bins >= b* fits the gather list
-        par[0] = (par[0] > 0 && (SAMPLED || run + own[e] <= (uint32_t)kGatherCap)) ? par[0] : 0;
-      }
-      run += own[e];
-    }
-  }
-  __syncthreads();
-  const float best = request_best(ws, b);   // whole waves
-  if (tid == 0) {
-    const bool finite = best == best && best > -INFINITY && best < INFINITY;
-    const bool fast = finite && total >= (uint32_t)k && par[0] > 0;
-    ws.info[b * kInfo + 0] = par[0];
-    ws.info[b * kInfo + 1] = par[1];
-    ws.info[b * kInfo + 2] = 0;          // gather counter
-    ws.info[b * kInfo + 3] = fast ? 1 : 0;
-    if (SAMPLED) ws.info[b * kInfo + 4] = 0;   // done flag of this call
-  }
-}
-
-// After the gather at the sampled bin: the gathered set holds the k best
-// exactly when at least k candidates lie at or above that bin; it is usable
-// when it also fits the list.  Otherwise the full histogram path runs.
-__global__ void __launch_bounds__(64)
-topk_verify_kernel(int32_t B, int32_t k, TopkWs ws) {
-  const int64_t b = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (b >= B) return;
-  int32_t* info = ws.info + b * kInfo;
-  const uint32_t n = (uint32_t)info[2];
-  const bool ok = info[3] != 0 && n >= (uint32_t)k && n <= (uint32_t)kGatherCap;
-  info[4] = ok ? 1 : 0;
-}
-
-// Gathered candidates are staged in LDS and flushed to the request's list
-// with one global atomic per flush (same-address global atomics serialise).
-constexpr int kStage = 2048;
-
-template <class Src, bool VEC8>
-__global__ void __launch_bounds__(kSliceThreads)
-topk_gather_kernel(Src src, int32_t M, int32_t V, TopkWs ws) {
-  constexpr int kCap = VEC8 ? 2 * kStage : kStage;
-  __shared__ uint64_t stage[kCap];
-  __shared__ uint32_t n_stage, base;
-  const int s = blockIdx.x;
-  const int64_t b = blockIdx.y;
-  // whole workgroup: no fast path, or the sampled path already succeeded
-  if (ws.info[b * kInfo + 3] == 0 || ws.info[b * kInfo + 4] != 0) return;
-  const int bstar = ws.info[b * kInfo + 0];
-  const uint32_t N = (uint32_t)M * (uint32_t)V;
-  const float best = request_best(ws, b);
-  const float lo = best - kWindow, inv_w = (float)kHistBins / kWindow;
-  // every candidate in bin b* or above lies at or above the lower edge of bin
-  // b* - 1 (a whole bin of slack against rounding): waves with no candidate
-  // there skip the bin computation
-  const float thr = lo + (float)(bstar - 1) * (kWindow / (float)kHistBins);
-  uint32_t i0, i1;
-  slice_range(N, ws.S, s, i0, i1);
-  const auto c = src.request(b, N);
-  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 2];
-  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
-  if (threadIdx.x == 0) n_stage = 0;
-  __syncthreads();
-  auto flush = [&]() {
-    __syncthreads();
-    const uint32_t n = n_stage;
-    if (n > 0) {
-      if (threadIdx.x == 0) base = atomicAdd(count, n);
-      __syncthreads();
-      const uint32_t b0 = base;
-      for (uint32_t j = threadIdx.x; j < n; j += kSliceThreads)
-        if (b0 + j < (uint32_t)kGatherCap) list[b0 + j] = stage[j];
-      __syncthreads();
-      if (threadIdx.x == 0) n_stage = 0;
-    }
-    __syncthreads();
-  };
-  if constexpr (VEC8) {
-    // runs of eight per thread, four batches in flight: each batch is staged
-    // (at most kBatch entries, flushed before the stage can overflow) and the
-    // batch four ahead is loaded in its registers
-    constexpr uint32_t kBatch = 8 * kSliceThreads;
-    float x[4][8];
-    auto load_batch = [&](uint32_t j, float (&y)[8]) __attribute__((always_inline)) {
-      const uint32_t i = j + 8 * threadIdx.x;
-      if (i < i1) {
-        c.load8(i, y);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) y[e] = -INFINITY;
-      }
-    };
-#pragma unroll
-    for (int u = 0; u < 4; ++u) load_batch(i0 + u * kBatch, x[u]);
-    for (uint32_t j0 = i0; j0 < i1; j0 += 4 * kBatch) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t i = j0 + u * kBatch + 8 * threadIdx.x;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if (__ballot(x[u][e] >= thr) == 0) continue;   // whole wave
-          const int bin = window_bin(x[u][e], lo, inv_w);
-          wave_append(stage, &n_stage, i < i1 && bin >= bstar,
-                      composite(order_key(x[u][e]), i + e), kCap);
-        }
-        __syncthreads();
-        if (n_stage > (uint32_t)(kCap - kBatch)) flush();
-        load_batch(j0 + (u + 4) * kBatch, x[u]);
-      }
-    }
-  } else {
-    for (uint32_t j0 = i0; j0 < i1; j0 += 4 * kSliceThreads) {
-      float x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t i = j0 + u * kSliceThreads + threadIdx.x;
-        x[u] = i < i1 ? c.nt(i) : -INFINITY;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (__ballot(x[u] >= thr) == 0) continue;   // whole wave
-        const uint32_t i = j0 + u * kSliceThreads + threadIdx.x;
-        const int bin = window_bin(x[u], lo, inv_w);
-        wave_append(stage, &n_stage, i < i1 && bin >= bstar, composite(order_key(x[u]), i), kCap);
-      }
-      // at most 4 * kSliceThreads more per iteration: flush before the stage can overflow
-      __syncthreads();
-      if (n_stage > (uint32_t)(kCap - 4 * kSliceThreads)) flush();
-    }
-  }
-  flush();
-}
-
 struct TopkShared {
-  uint32_t hist[256];
   uint64_t list[kGatherCap];
-  uint32_t scan[64];
-  int32_t ipar[4];
-  // fast path: members per window bin (counted from the top bin down), then
-  // the first position of each bin in the bin-ordered list
+  // members per bin (counted from the top bin down), then the first position
+  // of each bin in the bin-ordered list; the threshold histograms use the first
   uint32_t bin_count[kHistBins];
   uint32_t bin_start[kHistBins];
-  uint32_t max_count;
+  uint32_t scan[64];
+  float fscan[2 * kTopkThreads / 64];
+  int32_t ipar[4];
+  uint32_t max_count, n_list;
 };
 
 // Bins at most this full are ranked by comparing a candidate with the other
@@ -777,229 +683,863 @@ __device__ __forceinline__ float key_score(uint32_t key) {
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
-// Final selection: sort the gathered candidates (fast path), or an exact radix
-// select over all the request's candidates (fallback), then emit k in order.
-template <class Src>
-__global__ void __launch_bounds__(kTopkThreads)
-topk_final_kernel(Src src, int32_t M, int32_t V, int32_t k,
-                  TopkWs ws, int32_t* __restrict__ parents, int32_t* __restrict__ tokens,
-                  float* __restrict__ scores) {
-  __shared__ TopkShared sh;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t b = blockIdx.x;
-  const uint32_t N = (uint32_t)M * (uint32_t)V;
-  const auto c = src.request(b, N);
-  if (tid < 4) sh.ipar[tid] = 0;
+__device__ __forceinline__ float block_max(float x, float* scratch) {
+  x = wave_max(x);
+  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = x;
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  x = wave_max(lane < kTopkThreads / 64 ? scratch[lane] : -INFINITY);
+  __syncthreads();
+  return x;
+}
 
-  uint32_t n_sel;
-  if (ws.info[b * kInfo + 3] != 0) {
-    n_sel = (uint32_t)ws.info[b * kInfo + 2];
-    const uint64_t* list = ws.list + b * (int64_t)kGatherCap;
-    // ---- rank by window bin: a counting sort over the bins, then each
-    // candidate's place inside its bin from the bin's other members ----
-    constexpr int kPer = kGatherCap / kTopkThreads;
-    for (int i = tid; i < kHistBins; i += kTopkThreads) sh.bin_count[i] = 0u;
-    if (tid == 0) sh.max_count = 0u;
-    __syncthreads();
-    const float best = request_best(ws, b);
-    const float lo = best - kWindow, inv_w = (float)kHistBins / kWindow;
-    uint64_t v[kPer];
-    uint32_t rb[kPer], slot[kPer];
+__device__ __forceinline__ void clear_bins(uint32_t* bins) {
+  for (int i = threadIdx.x; i < kHistBins; i += kTopkThreads) bins[i] = 0u;
+}
+
+// The highest bin b >= 1 of hist with at least `want` counts in bins >= b, or 0
+// when bins >= 1 hold fewer.  hist is complete (a barrier since its last update).
+// Ends with a barrier.
+__device__ int boundary_bin(const uint32_t* hist, uint32_t want, uint32_t* scan, int32_t* ipar) {
+  const int tid = threadIdx.x;
+  if (tid == 0) ipar[0] = 0;
+  // thread 0 owns the top 4 bins, in descending order
+  const int t_rev = kTopkThreads - 1 - tid;
+  uint32_t own[4], s4 = 0;
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      const uint32_t i = (uint32_t)(tid + j * kTopkThreads);
-      if (i < n_sel) {
-        v[j] = list[i];
-        // the bin the gather saw: the key is the candidate's score, exactly
-        rb[j] = (uint32_t)(kHistBins - 1 - window_bin(key_score((uint32_t)(v[j] >> 32)), lo, inv_w));
-        slot[j] = atomicAdd(&sh.bin_count[rb[j]], 1u);
-      }
-    }
-    __syncthreads();
-    {
-      uint32_t c4[4], s4 = 0, mx = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        c4[e] = sh.bin_count[4 * tid + e];
-        s4 += c4[e];
-        mx = max(mx, c4[e]);
-      }
-      if (mx > 0) atomicMax(&sh.max_count, mx);
-      uint32_t total;
-      uint32_t run = block_exclusive_scan(s4, sh.scan, &total);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sh.bin_start[4 * tid + e] = run;
-        run += c4[e];
-      }
-    }
-    __syncthreads();
-    if (sh.max_count <= kRankBinCap) {
-      // members of a bin that starts at or past k are not among the k best
-#pragma unroll
-      for (int j = 0; j < kPer; ++j)
-        if ((uint32_t)(tid + j * kTopkThreads) < n_sel && sh.bin_start[rb[j]] < (uint32_t)k)
-          sh.list[sh.bin_start[rb[j]] + slot[j]] = v[j];
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        if ((uint32_t)(tid + j * kTopkThreads) >= n_sel) continue;
-        const uint32_t s0 = sh.bin_start[rb[j]], n = sh.bin_count[rb[j]];
-        if (s0 >= (uint32_t)k) continue;
-        uint32_t pos = s0;
-        for (uint32_t e = 0; e < n; ++e) pos += sh.list[s0 + e] > v[j] ? 1u : 0u;
-        if (pos < (uint32_t)k) {
-          const uint32_t key = (uint32_t)(v[j] >> 32), idx = ~(uint32_t)(v[j] & 0xffffffffull);
-          parents[b * k + pos] = (int32_t)(idx / (uint32_t)V);
-          tokens[b * k + pos] = (int32_t)(idx % (uint32_t)V);
-          scores[b * k + pos] = key == 0x80000000u ? c[idx] : key_score(key);
-        }
-      }
-      return;
-    }
-    // a crowded bin: the bitonic sort below
-    for (uint32_t i = tid; i < n_sel; i += kTopkThreads) sh.list[i] = list[i];
-    __syncthreads();
-  } else {
-    // ---- exact radix select on the key, four 8-bit digits ----
-    uint32_t prefix = 0, remaining = (uint32_t)k;
-    for (int pass = 0; pass < 4; ++pass) {
-      const int shift = 24 - 8 * pass;
-      const uint32_t pmask = pass == 0 ? 0u : (0xffffffffu << (shift + 8));
-      for (int i = tid; i < 256; i += kTopkThreads) sh.hist[i] = 0u;
-      __syncthreads();
-      for (uint32_t i0 = 0; i0 < N; i0 += kTopkThreads) {
-        const uint32_t i = i0 + tid;
-        const bool live = i < N;
-        const uint32_t key = live ? order_key(c[i]) : 0u;
-        hist_add(sh.hist, (int)((key >> shift) & 255u), live && (key & pmask) == prefix);
-      }
-      __syncthreads();
-      if (wave == 0) {
-        // digits from 255 down: 4 per lane, lane 0 owns 255..252
-        uint32_t own[4], s4 = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          own[j] = sh.hist[255 - 4 * lane - j];
-          s4 += own[j];
-        }
-        uint32_t inc = s4;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint32_t y = __shfl_up(inc, o);
-          if (lane >= o) inc += y;
-        }
-        const uint32_t before = inc - s4;
-        if (before < remaining && inc >= remaining) {
-          uint32_t run = before;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (run < remaining && run + own[j] >= remaining) {
-              sh.ipar[0] = 255 - 4 * lane - j;
-              sh.ipar[1] = (int32_t)run;
-            }
-            run += own[j];
-          }
-        }
-      }
-      __syncthreads();
-      prefix |= (uint32_t)sh.ipar[0] << shift;
-      remaining -= (uint32_t)sh.ipar[1];
-      __syncthreads();
-    }
-    // prefix is the k-th key T; `remaining` candidates equal to T are taken,
-    // lowest index first, after the k - remaining candidates above T.
-    const uint32_t T = prefix, need = remaining, gt_total = (uint32_t)k - remaining;
-    uint32_t gt_base = 0, eq_base = 0;
-    for (uint32_t i0 = 0; i0 < N && (gt_base < gt_total || eq_base < need);
-         i0 += 4 * kTopkThreads) {
-      uint32_t keys[4], ngt = 0, neq = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t i = i0 + 4 * tid + j;
-        const bool in = i < N;
-        keys[j] = in ? order_key(c[i]) : 0u;
-        ngt += in && keys[j] > T;
-        neq += in && keys[j] == T;
-      }
-      uint32_t total;
-      const uint32_t pre = block_exclusive_scan((neq << 16) | ngt, sh.scan, &total);
-      uint32_t pg = gt_base + (pre & 0xffffu), pe = eq_base + (pre >> 16);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t i = i0 + 4 * tid + j;
-        if (i >= N) continue;
-        if (keys[j] > T) {
-          sh.list[pg++] = composite(keys[j], i);
-        } else if (keys[j] == T) {
-          if (pe < need) sh.list[gt_total + pe] = composite(keys[j], i);
-          ++pe;
-        }
-      }
-      gt_base += total & 0xffffu;
-      eq_base += total >> 16;
-    }
-    __syncthreads();
-    n_sel = (uint32_t)k;
+  for (int e = 0; e < 4; ++e) {
+    own[e] = 4 * t_rev + 3 - e > 0 ? hist[4 * t_rev + 3 - e] : 0u;
+    s4 += own[e];
   }
+  uint32_t total;
+  const uint32_t before = block_exclusive_scan(s4, scan, &total);
+  if (before < want && before + s4 >= want) {
+    uint32_t run = before;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (run < want && run + own[e] >= want) ipar[0] = 4 * t_rev + 3 - e;
+      run += own[e];
+    }
+  }
+  __syncthreads();
+  const int b = ipar[0];
+  __syncthreads();
+  return b;
+}
 
-  // ---- sort the selected candidates, best first; emit the first k ----
+// Calls put(composite) for each of a lane's candidates x[0..7] (flat indices
+// i ..) at or above thr: few lanes have any, and most of those one.
+template <int E, class Put>
+__device__ __forceinline__ void for_hits(const float (&x)[E], uint32_t i, float thr, Put put) {
+  uint32_t hits = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) hits |= x[e] >= thr ? 1u << e : 0u;
+  if (hits == 0) return;
+  put.reserve((uint32_t)__popc(hits));
+  do {
+    const int e = __ffs(hits) - 1;
+    hits &= hits - 1;
+    float y = x[0];
+#pragma unroll
+    for (int q = 1; q < E; ++q) y = e == q ? x[q] : y;
+    put(composite(order_key(y), i + e));
+  } while (hits != 0);
+}
+
+// To a list in LDS: one LDS atomic per lane with candidates.
+struct PutList {
+  uint64_t* list;
+  uint32_t* count;
+  uint32_t cap, pos = 0;
+  __device__ __forceinline__ void reserve(uint32_t n) { pos = atomicAdd(count, n); }
+  __device__ __forceinline__ void operator()(uint64_t v) {
+    if (pos < cap) list[pos] = v;
+    ++pos;
+  }
+};
+
+struct TopkOut {
+  int32_t* parents;
+  int32_t* tokens;
+  float* scores;
+  FastDiv per_row;   // flat index -> beam
+  int32_t V;
+  __device__ __forceinline__ void put(int64_t at, uint32_t idx, float score) const {
+    const uint32_t m = per_row.div(idx);
+    parents[at] = (int32_t)m;
+    tokens[at] = (int32_t)(idx - m * (uint32_t)V);
+    scores[at] = score;
+  }
+};
+
+// The selected composites sh.list[0, n), n >= k or all there are, sorted best
+// first; the first min(n, k) are emitted.
+template <class Row>
+__device__ void sort_and_emit(TopkShared& sh, uint32_t n, int32_t k, int64_t out0, const Row& c,
+                              const TopkOut& out) {
   uint32_t n2 = 1;
-  while (n2 < n_sel) n2 <<= 1;
-  for (uint32_t i = n_sel + tid; i < n2; i += kTopkThreads) sh.list[i] = 0ull;
+  while (n2 < n) n2 <<= 1;
+  for (uint32_t i = n + threadIdx.x; i < n2; i += kTopkThreads) sh.list[i] = 0ull;
   __syncthreads();
   bitonic_desc(sh.list, (int)n2);
-  for (int j = tid; j < k; j += kTopkThreads) {
+  for (uint32_t j = threadIdx.x; j < min(n, (uint32_t)k); j += kTopkThreads) {
     const uint32_t idx = ~(uint32_t)(sh.list[j] & 0xffffffffull);
-    parents[b * k + j] = (int32_t)(idx / (uint32_t)V);
-    tokens[b * k + j] = (int32_t)(idx % (uint32_t)V);
-    scores[b * k + j] = c[idx];
+    out.put(out0 + j, idx, c[idx]);
   }
 }
 
-// The score kernels; with CAND = false they write lse_out instead of cand.
-// Both modes pick the same kernel for a given V, so the log-sum-exp (and so
-// every recomputed candidate) matches the written candidates bit for bit.
+// Bound by the chain of LDS passes of one workgroup per request (64 requests,
+// 6144 gathered, k = 4096: 26 us with bins of 1/64 in a 64-unit window and
+// scattered outputs, 15 us with bins of the gathered range and whole lines).
+// Ranks n <= kGatherCap gathered candidates above -inf (thread t holds numbers
+// t, t + 1024, ... in v) and emits the first min(n, k): a counting sort over
+// equal steps of their range, then each candidate's place inside its bin from
+// the bin's other members.
+template <class Row>
+__device__ void rank_and_emit(TopkShared& sh, uint64_t (&v)[kGatherCap / kTopkThreads], uint32_t n,
+                              int32_t k, int64_t out0, const Row& c, const TopkOut& out) {
+  constexpr int kPer = kGatherCap / kTopkThreads;
+  const int tid = threadIdx.x;
+  float hi = -INFINITY, lo_neg = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if ((uint32_t)(tid + j * kTopkThreads) < n) {
+      const float x = key_score((uint32_t)(v[j] >> 32));
+      hi = fmaxf(hi, x);
+      lo_neg = fmaxf(lo_neg, -x);
+    }
+  clear_bins(sh.bin_count);
+  if (tid == 0) sh.max_count = 0u;
+  // both maxima at once
+  const float m2 = max_rows<2>({hi, lo_neg});
+  if ((tid & 31) == 0) sh.fscan[tid >> 5] = m2;
+  __syncthreads();
+  {
+    const float y = sh.fscan[tid & 31];   // waves' hi at even, lo_neg at odd places
+    const bool odd = tid & 1;
+    const float both = max_rows<2>({odd ? -INFINITY : y, odd ? y : -INFINITY});
+    hi = lane_value(both, 0);
+    lo_neg = lane_value(both, 32);
+  }
+  const float lo = -lo_neg;
+  // an infinite range or a single value: one bin
+  const float range = hi - lo;
+  const float inv_w = range > 0.f && range < INFINITY ? (float)kHistBins / range : 0.f;
+  uint32_t rb[kPer], slot[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    if ((uint32_t)(tid + j * kTopkThreads) < n) {
+      rb[j] = (uint32_t)(kHistBins - 1 -
+                         step_bin(key_score((uint32_t)(v[j] >> 32)), lo, inv_w));
+      slot[j] = atomicAdd(&sh.bin_count[rb[j]], 1u);
+    }
+  }
+  __syncthreads();
+  {
+    uint32_t c4[4], s4 = 0, mx = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      c4[e] = sh.bin_count[4 * tid + e];
+      s4 += c4[e];
+      mx = max(mx, c4[e]);
+    }
+    if (mx > 1) atomicMax(&sh.max_count, mx);
+    uint32_t total;
+    uint32_t run = block_exclusive_scan(s4, sh.scan, &total);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sh.bin_start[4 * tid + e] = run;
+      run += c4[e];
+    }
+  }
+  __syncthreads();
+  const bool crowded = sh.max_count > kRankBinCap;
+  // members of a bin that starts at or past k are not among the k best
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t i = (uint32_t)(tid + j * kTopkThreads);
+    if (i >= n) continue;
+    if (crowded) sh.list[i] = v[j];
+    else if (sh.bin_start[rb[j]] < (uint32_t)k) sh.list[sh.bin_start[rb[j]] + slot[j]] = v[j];
+  }
+  __syncthreads();
+  if (crowded) {
+    sort_and_emit(sh, n, k, out0, c, out);
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    slot[j] = 0xffffffffu;
+    if ((uint32_t)(tid + j * kTopkThreads) >= n) continue;
+    const uint32_t s0 = sh.bin_start[rb[j]], nb = sh.bin_count[rb[j]];
+    if (s0 >= (uint32_t)k) continue;
+    uint32_t pos = s0;
+    for (uint32_t e = 0; e < nb; ++e) pos += sh.list[s0 + e] > v[j] ? 1u : 0u;
+    slot[j] = pos;
+  }
+  // back to LDS in rank order, so that the outputs leave as whole lines
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (slot[j] < (uint32_t)k) sh.list[slot[j]] = v[j];
+  __syncthreads();
+  for (uint32_t j = tid; j < min(n, (uint32_t)k); j += kTopkThreads) {
+    const uint32_t key = (uint32_t)(sh.list[j] >> 32), idx = ~(uint32_t)(sh.list[j] & 0xffffffffull);
+    // the key is the score, but for -0, which has +0's key
+    out.put(out0 + j, idx, key == 0x80000000u ? c[idx] : key_score(key));
+  }
+}
+
+// Candidates i .. i+7 of a request (-inf past N; i a multiple of 8).
+template <bool VEC8, class Row>
+__device__ __forceinline__ void load_run(const Row& c, uint32_t i, uint32_t N, float (&x)[8]) {
+  if constexpr (VEC8) {
+    if (i < N) {   // N is a multiple of 8
+      c.load8(i, x);
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = -INFINITY;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = i + e < N ? c[i + e] : -INFINITY;
+  }
+}
+
+// Fills positions n .. k-1 with the candidates that are not above -inf: the
+// -inf ones by index, then the NaN ones by index.
+template <bool VEC8, class Row>
+__device__ void fill_dead(TopkShared& sh, uint32_t n, int32_t k, uint32_t N, int64_t out0,
+                          const Row& c, const TopkOut& out) {
+  for (int pass = 0; pass < 2 && n < (uint32_t)k; ++pass) {
+    for (uint32_t i0 = 0; i0 < N && n < (uint32_t)k; i0 += 8 * kTopkThreads) {
+      const uint32_t i = i0 + 8 * threadIdx.x;
+      float x[8];
+      load_run<VEC8>(c, i, N, x);
+      uint32_t cnt = 0;
+      bool hit[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        hit[e] = i + e < N && (pass == 0 ? x[e] == -INFINITY : x[e] != x[e]);
+        cnt += hit[e] ? 1u : 0u;
+      }
+      uint32_t total;
+      uint32_t pos = n + block_exclusive_scan(cnt, sh.scan, &total);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (hit[e]) {
+          if (pos < (uint32_t)k) out.put(out0 + pos, i + e, x[e]);
+          ++pos;
+        }
+      n += total;
+    }
+  }
+}
+
+// Exact selection of any request: a radix select on the key (digits of 12, 12
+// and 8 bits) over all the candidates, an index-ordered collection of the ties with
+// the k-th, and a bitonic sort.  Eight candidates per thread and step.
+template <bool VEC8, class Row>
+__device__ void exact_select(TopkShared& sh, int32_t k, uint32_t N, int64_t out0, const Row& c,
+                             const TopkOut& out) {
+  const int tid = threadIdx.x;
+  uint32_t* hist = sh.bin_count;
+  constexpr uint32_t kStep = 8 * kTopkThreads;
+  uint32_t prefix = 0, remaining = (uint32_t)k;
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 20 : (pass == 1 ? 8 : 0), bits = pass == 2 ? 8 : 12;
+    const uint32_t pmask = pass == 0 ? 0u : 0xffffffffu << (shift + bits);
+    __syncthreads();
+    clear_bins(hist);
+    __syncthreads();
+    for (uint32_t i0 = 0; i0 < N; i0 += kStep) {
+      const uint32_t i = i0 + 8 * tid;
+      float x[8];
+      load_run<VEC8>(c, i, N, x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t key = order_key(x[e]);
+        hist_add(hist, (int)((key >> shift) & ((1u << bits) - 1u)), i + e < N && (key & pmask) == prefix);
+      }
+    }
+    __syncthreads();
+    // digits from the top down: 4 per thread, thread 0 owns the highest
+    uint32_t own[4], s4 = 0, total;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      own[j] = hist[kHistBins - 1 - 4 * tid - j];
+      s4 += own[j];
+    }
+    const uint32_t before = block_exclusive_scan(s4, sh.scan, &total);
+    if (before < remaining && before + s4 >= remaining) {
+      uint32_t run = before;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (run < remaining && run + own[j] >= remaining) {
+          sh.ipar[0] = kHistBins - 1 - 4 * tid - j;
+          sh.ipar[1] = (int32_t)run;
+        }
+        run += own[j];
+      }
+    }
+    __syncthreads();
+    prefix |= (uint32_t)sh.ipar[0] << shift;
+    remaining -= (uint32_t)sh.ipar[1];
+  }
+  __syncthreads();
+  // prefix is the k-th key T; `remaining` candidates equal to T are taken,
+  // lowest index first, after the k - remaining candidates above T.
+  const uint32_t T = prefix, need = remaining, gt_total = (uint32_t)k - remaining;
+  uint32_t gt_base = 0, eq_base = 0;
+  for (uint32_t i0 = 0; i0 < N && (gt_base < gt_total || eq_base < need); i0 += kStep) {
+    const uint32_t i = i0 + 8 * tid;
+    float x[8];
+    load_run<VEC8>(c, i, N, x);
+    uint32_t keys[8], ngt = 0, neq = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool in = i + e < N;
+      keys[e] = order_key(x[e]);
+      ngt += in && keys[e] > T;
+      neq += in && keys[e] == T;
+    }
+    // at most 8192 of either in a step: two 16-bit counts in one scan
+    uint32_t total;
+    const uint32_t pre = block_exclusive_scan((neq << 16) | ngt, sh.scan, &total);
+    uint32_t pg = gt_base + (pre & 0xffffu), pe = eq_base + (pre >> 16);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (i + e >= N) continue;
+      if (keys[e] > T) {
+        sh.list[pg++] = composite(keys[e], i + e);
+      } else if (keys[e] == T) {
+        if (pe < need) sh.list[gt_total + pe] = composite(keys[e], i + e);
+        ++pe;
+      }
+    }
+    gt_base += total & 0xffffu;
+    eq_base += total >> 16;
+  }
+  __syncthreads();
+  sort_and_emit(sh, (uint32_t)k, k, out0, c, out);
+}
+
+// ---- N <= kSmallN: one workgroup per request ----
+// Bound by latency: one read of the candidates (from L2: at most 128 KiB of
+// bf16 logits), then a chain of LDS passes.  RUNS runs of 8 per thread.
+template <class Src, bool VEC8, int RUNS>
+__global__ void __launch_bounds__(kTopkThreads)
+topk_small_kernel(Src src, uint32_t N, int32_t k, TopkOut out) {
+  __shared__ TopkShared sh;
+  const int tid = threadIdx.x;
+  const int64_t b = blockIdx.x, out0 = b * k;
+  const auto c = src.request(b, N);
+  float x[RUNS][8];
+#pragma unroll
+  for (int j = 0; j < RUNS; ++j) load_run<VEC8>(c, (uint32_t)(j * kTopkThreads + tid) * 8, N, x[j]);
+  float thr = -FLT_MAX;
+  bool exact = false;
+  if (tid == 0) sh.n_list = 0u;
+  if (N > (uint32_t)kGatherCap) {
+    clear_bins(sh.bin_count);
+    float mx = -INFINITY;
+    uint32_t live = 0;
+#pragma unroll
+    for (int j = 0; j < RUNS; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        mx = fmaxf(mx, x[j][e]);
+        live += x[j][e] > -INFINITY ? 1u : 0u;
+      }
+    const float best = block_max(mx, sh.fscan);
+    uint32_t n_live;
+    block_exclusive_scan(live, sh.scan, &n_live);
+    // fewer than k above -inf: all of them are gathered (k <= kGatherCap)
+    if (n_live >= (uint32_t)k) {
+      const float lo = best - kWindow, inv_w = (float)kHistBins / kWindow;
+      // the k-th best of the threads' own best is at or below the k-th best of
+      // all (if there are k threads): only what is above enters the histogram
+      int first = 1;
+      const int own = step_bin(mx, lo, inv_w);
+      if (k <= kTopkThreads) {
+        if (own > 0) atomicAdd(&sh.bin_count[own], 1u);
+        __syncthreads();
+        first = max(1, boundary_bin(sh.bin_count, (uint32_t)k, sh.scan, sh.ipar));
+        clear_bins(sh.bin_count);
+        __syncthreads();
+      }
+      if (own >= first) {
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int bin = step_bin(x[j][e], lo, inv_w);
+            if (bin >= first) atomicAdd(&sh.bin_count[bin], 1u);
+          }
+      }
+      __syncthreads();
+      const int bin = boundary_bin(sh.bin_count, (uint32_t)k, sh.scan, sh.ipar);
+      exact = bin == 0 || !(best < INFINITY);   // also NaN
+      // the lowest score of the bin and above, to the exact bin
+      if (!exact) {
+        float low_neg = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j)
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (step_bin(x[j][e], lo, inv_w) >= bin) low_neg = fmaxf(low_neg, -x[j][e]);
+        thr = -block_max(low_neg, sh.fscan);
+      }
+    }
+  }
+  __syncthreads();
+  if (!exact) {
+#pragma unroll
+    for (int j = 0; j < RUNS; ++j)
+      for_hits<8>(x[j], (uint32_t)(j * kTopkThreads + tid) * 8, thr,
+                  PutList{sh.list, &sh.n_list, (uint32_t)kGatherCap});
+    __syncthreads();
+    const uint32_t n = sh.n_list;
+    if (n <= (uint32_t)kGatherCap) {
+      uint64_t v[kGatherCap / kTopkThreads];
+#pragma unroll
+      for (int j = 0; j < kGatherCap / kTopkThreads; ++j)
+        v[j] = (uint32_t)(tid + j * kTopkThreads) < n ? sh.list[tid + j * kTopkThreads] : 0ull;
+      __syncthreads();
+      rank_and_emit(sh, v, n, k, out0, c, out);
+      if (n < (uint32_t)k) fill_dead<VEC8>(sh, n, k, N, out0, c, out);
+      return;
+    }
+    __syncthreads();
+  }
+  exact_select<VEC8>(sh, k, N, out0, c, out);
+}
+
+// ---- more candidates: select, gather, final ----
+
+// Samples of a request, four at a time as packed fp16 differences from ref(b):
+// as the score pass stored them, or one 32-candidate chunk of every 2^lp
+// consecutive ones (picked by a hash of the group index, so that neither a
+// row's token order nor the row length biases it), read from the candidates.
+struct StoredSample {
+  const uint16_t* p;
+  int64_t stride;
+  uint32_t n;
+  const float* prev;
+  int32_t M;
+  struct Row {
+    const u32x2* p;
+    uint32_t n;
+    // the score pass put -inf behind the last sample, up to a whole four
+    __device__ __forceinline__ u32x2 load4(uint32_t j, float) const {
+      const u32x2 w = p[min(j, n - 1) >> 2];
+      return j < n ? w : u32x2{0xfc00fc00u, 0xfc00fc00u};   // -inf
+    }
+  };
+  __device__ __forceinline__ Row request(int64_t b, uint32_t) const {
+    return Row{(const u32x2*)(p + b * stride), n};
+  }
+  __device__ __forceinline__ float ref(const Row&, int64_t b, float*) const {
+    return sample_ref(prev + b * M, M);
+  }
+};
+template <class Src>
+struct ChunkSample {
+  Src src;
+  int32_t lp;
+  uint32_t n;   // a multiple of 32
+  struct Row {
+    typename Src::Row c;
+    int32_t lp;
+    uint32_t n, N;
+    // flat index of sample j (past 2^32: past any candidate)
+    __device__ __forceinline__ uint64_t index(uint32_t j) const {
+      const uint32_t g = j >> 5, chunk = (g << lp) + ((g * 0x9E3779B1u) >> (32 - lp));
+      return 32ull * chunk + (j & 31);
+    }
+    __device__ __forceinline__ float at(uint32_t j) const {
+      const uint64_t i = index(j);
+      return j < n && i < N ? c.nt((uint32_t)i) : -INFINITY;
+    }
+    __device__ __forceinline__ u32x2 load4(uint32_t j, float ref) const {
+      const uint64_t i = index(j);   // j a multiple of 4: one chunk
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = j < n && i + e < N ? c.nt((uint32_t)i + e) - ref : -INFINITY;
+      return u32x2{pack_f16x2(x[0], x[1]), pack_f16x2(x[2], x[3])};
+    }
+  };
+  __device__ __forceinline__ Row request(int64_t b, uint32_t N) const {
+    return Row{src.request(b, N), lp, n, N};
+  }
+  // the best of the first samples, 0 if none is finite
+  __device__ __forceinline__ float ref(const Row& row, int64_t, float* scratch) const {
+    const float x = row.at(threadIdx.x);
+    const float m = block_max(fabsf(x) < INFINITY ? x : -INFINITY, scratch);
+    return m > -INFINITY ? m : 0.f;
+  }
+};
+
+// Threshold of each request: the score above which about `want` samples lie, by
+// a histogram of the differences from ref in [-kBelow, kAbove).  A workgroup
+// takes kSelectSamples samples (one CU reads from beyond its L2 at some 20 GB/s,
+// so a sample of 256 KiB takes 27 us on one CU and 8 us on eight); the last one
+// of a request to finish sums the workgroups' histograms.  The want-th best of
+// the threads' own best samples bounds the threshold from below, so that only
+// the few samples above that are counted.  A request with fewer than `want`
+// samples in the window gathers everything above -inf.
+constexpr float kBelow = 112.0f, kAbove = 16.0f;
+constexpr uint32_t kSelectSamples = 16384;
+
+template <class Smp>
+__global__ void __launch_bounds__(kTopkThreads)
+topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
+  __shared__ uint32_t hist[kHistBins];
+  __shared__ uint32_t scan[64];
+  __shared__ float fscan[kTopkThreads / 64];
+  __shared__ int32_t ipar[2];
+  constexpr int U = kSelectSamples / (4 * kTopkThreads);   // loads of four samples per thread
+  constexpr float kInvW = (float)kHistBins / (kBelow + kAbove);
+  const int tid = threadIdx.x;
+  const int64_t b = blockIdx.y;
+  const auto sample = smp.request(b, N);
+  const float ref = smp.ref(sample, b, fscan);
+  float x[U][4];
+  float mx = -INFINITY;
+  {
+    u32x2 w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      w[u] = sample.load4(blockIdx.x * kSelectSamples + 4 * (u * kTopkThreads + tid), ref);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const f16x2 lo = __builtin_bit_cast(f16x2, w[u].x), hi = __builtin_bit_cast(f16x2, w[u].y);
+      x[u][0] = (float)lo.x;
+      x[u][1] = (float)lo.y;
+      x[u][2] = (float)hi.x;
+      x[u][3] = (float)hi.y;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, x[u][e]);
+    }
+  }
+  clear_bins(hist);
+  __syncthreads();
+  const int own = step_bin(mx, -kBelow, kInvW);
+  if (own > 0) atomicAdd(&hist[own], 1u);
+  __syncthreads();
+  const int first = max(1, boundary_bin(hist, want, scan, ipar));   // 1: the whole window
+  clear_bins(hist);
+  __syncthreads();
+  if (own >= first) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int bin = step_bin(x[u][e], -kBelow, kInvW);
+        if (bin >= first) atomicAdd(&hist[bin], 1u);
+      }
+  }
+  __syncthreads();
+  int32_t* info = ws.info + b * kInfo;
+  if (gridDim.x > 1) {
+    // every workgroup's bins from the request's threshold up are complete, as
+    // its `first` is at or below the threshold
+    // The shared counts are touched by device-scope read-modify-writes only,
+    // which all XCDs perform at one place, so a wait for this workgroup's own
+    // to be done orders them before its ticket; a device-wide fence here, which
+    // writes back the L2, made the kernel 20 times slower.
+    uint32_t* sum = ws.hist(b);
+    for (int i = tid; i < kHistBins; i += kTopkThreads)
+      if (hist[i] != 0u)
+        (void)__hip_atomic_fetch_add(&sum[i], hist[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0)
+      ipar[0] = __hip_atomic_fetch_add(&info[3], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (ipar[0] != (int32_t)gridDim.x - 1) return;   // whole workgroup
+    for (int i = tid; i < kHistBins; i += kTopkThreads)
+      hist[i] = __hip_atomic_fetch_add(&sum[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+  }
+  const int bin = boundary_bin(hist, want, scan, ipar);
+  if (tid == 0) {
+    // about the bin's lower edge
+    info[0] = __float_as_int(bin > 0 ? ref + ((float)bin / kInvW - kBelow) : -FLT_MAX);
+    info[1] = 0;   // gathered count
+  }
+}
+
+__global__ void __launch_bounds__(kTopkThreads) topk_clear_kernel(TopkWs ws) {
+  clear_shared(ws, blockIdx.x, threadIdx.x, kTopkThreads);
+}
+
+constexpr int kGatherThreads = 256;
+constexpr int kStage = 1024;   // LDS entries of a gather workgroup
+
+// A workgroup's staged candidates: flushed with one global atomic (same-address
+// global atomics serialise); what does not fit the stage goes to the list directly.
+struct GatherStage {
+  uint64_t entry[kStage];
+  uint32_t n, base;
+};
+struct PutStage {
+  GatherStage& st;
+  uint64_t* list;
+  uint32_t* count;
+  uint32_t pos = 0, direct = 0;
+  __device__ __forceinline__ void reserve(uint32_t n) {
+    pos = atomicAdd(&st.n, n);
+    const uint32_t first = max(pos, (uint32_t)kStage);
+    if (pos + n > first) direct = atomicAdd(count, pos + n - first);
+  }
+  __device__ __forceinline__ void operator()(uint64_t v) {
+    if (pos < (uint32_t)kStage) {
+      st.entry[pos] = v;
+    } else {
+      if (direct < (uint32_t)kGatherCap) list[direct] = v;
+      ++direct;
+    }
+    ++pos;
+  }
+};
+__device__ __forceinline__ void gather_flush(GatherStage& st, uint64_t* list, uint32_t* count) {
+  __syncthreads();
+  const uint32_t n = min(st.n, (uint32_t)kStage);
+  if (n == 0) return;   // whole workgroup
+  if (threadIdx.x == 0) st.base = atomicAdd(count, n);
+  __syncthreads();
+  const uint32_t b0 = st.base;
+  for (uint32_t j = threadIdx.x; j < n; j += kGatherThreads)
+    if (b0 + j < (uint32_t)kGatherCap) list[b0 + j] = st.entry[j];
+}
+
+// Gather over a written candidate array (16 x 1000 x 509 fp32, 33 MB: 31 -> 12
+// us, the former form had a barrier per step and 256 workgroups): workgroup s of request b takes
+// candidates [s * per, (s + 1) * per), per a multiple of 1024.  Bound by the
+// read of the array: VEC (16-byte aligned requests, N a multiple of 8) four
+// candidates per load, four loads in flight; else eight single ones.
+template <bool VEC>
+__global__ void __launch_bounds__(kGatherThreads)
+topk_gather_array_kernel(CandArray src, uint32_t N, uint32_t per, TopkWs ws) {
+  __shared__ GatherStage st;
+  const int64_t b = blockIdx.y;
+  const int32_t* info = ws.info + b * kInfo;
+  const float thr = __int_as_float(info[0]);
+  const auto c = src.request(b, N);
+  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
+  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 1];
+  if (threadIdx.x == 0) st.n = 0u;
+  __syncthreads();
+  const uint64_t i0 = (uint64_t)blockIdx.x * per;
+  const uint64_t i1 = min((uint64_t)N, i0 + per);
+  if constexpr (VEC) {
+    for (uint64_t j0 = i0; j0 < i1; j0 += 16 * kGatherThreads) {
+      float x[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint64_t i = j0 + 4 * (u * kGatherThreads + threadIdx.x);
+        u32x4 q = {0xff800000u, 0xff800000u, 0xff800000u, 0xff800000u};
+        if (i < i1) q = __builtin_nontemporal_load((const u32x4*)(c.p + i));   // N is a multiple of 4
+        Chunk<F32>::unpack(q, x[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        for_hits<4>(x[u], (uint32_t)(j0 + 4 * (u * kGatherThreads + threadIdx.x)), thr,
+                    PutStage{st, list, count});
+    }
+  } else {
+    for (uint64_t j0 = i0; j0 < i1; j0 += 8 * kGatherThreads) {
+      float x[8][1];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint64_t i = j0 + u * kGatherThreads + threadIdx.x;
+        x[u][0] = i < i1 ? c.nt((uint32_t)i) : -INFINITY;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        for_hits<1>(x[u], (uint32_t)(j0 + u * kGatherThreads + threadIdx.x), thr,
+                    PutStage{st, list, count});
+    }
+  }
+  gather_flush(st, list, count);
+}
+
+// Gather over candidates recomputed from the logits.  A wave takes up to 64
+// rows and reads only those whose upper bound reaches the threshold: at 64
+// requests x 4096 beams x 512 tokens 31 % of the rows hold all of the 6144 best
+// candidates.  2^ll lanes per row (RUN: runs of 8 tokens per lane, else single
+// tokens), 4 row pieces in flight.  Few lanes hold a candidate: the lanes whose
+// best logit, filtered or not, reaches the threshold queue their run, and the
+// workgroup then takes the queued runs apart with all lanes busy (64 x 4096 x
+// 512: reading every row 136 us, these rows 51, with the queue 27).
+constexpr int kQueue = 2048;
+
+template <class T, bool RUN>
+__global__ void __launch_bounds__(kGatherThreads)
+topk_gather_rows_kernel(CandFromLogits<T> src, const float* __restrict__ row_max, int32_t rows_per_wave,
+                        int32_t ll, uint32_t N, TopkWs ws) {
+  constexpr int kWaves = kGatherThreads / 64, E = RUN ? 8 : 1, U = 4;
+  __shared__ GatherStage st;
+  __shared__ uint32_t queue[RUN ? kQueue : 1];
+  __shared__ uint32_t n_queue;
+  __shared__ uint8_t rows[kWaves][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t b = blockIdx.y;
+  const int32_t* info = ws.info + b * kInfo;
+  const int64_t m0 = ((int64_t)blockIdx.x * kWaves + wave) * rows_per_wave;
+  const float bound = lane < rows_per_wave && m0 + lane < src.M ? row_max[b * src.M + m0 + lane] : -INFINITY;
+  const float thr = __int_as_float(info[0]);
+  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
+  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 1];
+  if (threadIdx.x == 0) st.n = n_queue = 0u;
+  const uint64_t act = __ballot(bound >= thr);
+  if (bound >= thr) rows[wave][__popcll(act & ((1ull << lane) - 1ull))] = (uint8_t)lane;
+  __syncthreads();
+  const int n_act = (int)__popcll(act);
+  const auto c = src.request(b, N);
+  const int32_t V = src.V;
+  const int lpr = 1 << ll, rpp = 64 >> ll;             // lanes per row, rows per piece
+  const int sub = lane >> ll, sl = lane & (lpr - 1);
+  int idx0 = 0, v0 = 0;   // the next piece: first row (index into rows), first token
+  while (idx0 < n_act) {
+    typename CandFromLogits<T>::Row::template Raw<E> raw[U];
+    uint32_t at[U], m[U];
+    bool live[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int idx = idx0 + sub, v = v0 + sl * E;
+      live[u] = idx < n_act && v < V;
+      if (live[u]) {
+        m[u] = (uint32_t)m0 + rows[wave][idx];
+        at[u] = m[u] * (uint32_t)V + (uint32_t)v;
+        c.template load_raw<E>(at[u], m[u], raw[u]);
+      }
+      v0 += lpr * E;
+      if (v0 >= V) {
+        v0 = 0;
+        idx0 += rpp;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!live[u]) continue;
+      float f[E];
+      raw[u].logits(f);
+      float top = f[0];
+      if constexpr (E > 1) {
+        top = max3(top, f[1], f[2]);
+        top = max3(top, f[3], f[4]);
+        top = max3(top, f[5], f[6]);
+        top = max3(top, f[7], f[7]);
+      }
+      if (!(raw[u].p + (top - raw[u].l) >= thr)) continue;
+      if constexpr (RUN) {
+        const uint32_t pos = atomicAdd(&n_queue, 1u);
+        if (pos < (uint32_t)kQueue) {
+          queue[pos] = at[u];
+          continue;
+        }
+      }
+      float x[E];
+      c.template finish<E>(at[u], m[u], raw[u], x);
+      for_hits<E>(x, at[u], thr, PutStage{st, list, count});
+    }
+  }
+  if constexpr (RUN) {
+    __syncthreads();
+    const uint32_t n = min(n_queue, (uint32_t)kQueue);
+    for (uint32_t j = threadIdx.x; j < n; j += kGatherThreads) {
+      float x[8];
+      c.load8(queue[j], x);
+      for_hits<8>(x, queue[j], thr, PutStage{st, list, count});
+    }
+  }
+  gather_flush(st, list, count);
+}
+
+// Final selection: rank the gathered candidates, or the exact selection over
+// all the request's candidates.
+template <class Src, bool VEC8>
+__global__ void __launch_bounds__(kTopkThreads)
+topk_final_kernel(Src src, uint32_t N, int32_t k, TopkWs ws, TopkOut out) {
+  __shared__ TopkShared sh;
+  constexpr int kPer = kGatherCap / kTopkThreads;
+  const int tid = threadIdx.x;
+  const int64_t b = blockIdx.x, out0 = b * k;
+  const auto c = src.request(b, N);
+  const int32_t* info = ws.info + b * kInfo;
+  const float thr = __int_as_float(info[0]);
+  const uint32_t n = (uint32_t)info[1];
+  // all candidates at or above thr are in the list; it holds the k best when
+  // they are at least k, or when they are all there are above -inf
+  if (n <= (uint32_t)kGatherCap && (n >= (uint32_t)k || thr == -FLT_MAX)) {
+    const uint64_t* list = ws.list + b * (int64_t)kGatherCap;
+    uint64_t v[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const uint32_t i = (uint32_t)(tid + j * kTopkThreads);
+      v[j] = i < n ? list[i] : 0ull;
+    }
+    rank_and_emit(sh, v, n, k, out0, c, out);
+    if (n < (uint32_t)k) fill_dead<VEC8>(sh, n, k, N, out0, c, out);
+    return;
+  }
+  exact_select<VEC8>(sh, k, N, out0, c, out);
+}
+
+// The score kernels; with CAND = false they write lse_out, the rows' upper
+// bounds and the sample instead of cand.  Both modes pick the same kernel for a
+// given V, so the log-sum-exp (and so every recomputed candidate) matches the
+// written candidates bit for bit.
 template <bool CAND>
 static void launch_scores_mode(const void* logits, const float* prev, const uint32_t* mask,
                                float* cand, float* row_max, float* lse_out, int32_t R, int32_t V,
-                               bool bf16, hipStream_t stream) {
-  const int64_t blocks = ((int64_t)R + kScoreThreads / 64 - 1) / (kScoreThreads / 64);
-  const dim3 grid((unsigned)blocks), block(kScoreThreads);
+                               bool bf16, const SampleOut& smp, hipStream_t stream) {
   constexpr int64_t kWaves = kScoreThreads / 64;
-#define GRACE_SC(TT, NCH)                                                                       \
-  hipLaunchKernelGGL((beam_scores_vec_kernel<TT, NCH, CAND>),                                   \
-                     dim3((unsigned)(((int64_t)R + kWaves * score_rows_per_wave<NCH>() - 1) /    \
-                                     (kWaves * score_rows_per_wave<NCH>()))),                    \
-                     block, 0, stream, (const TT*)logits, prev, mask, cand, row_max, lse_out, R, V)
-  // 16-byte runs need V a multiple of 8 and 16-byte aligned logits
-  if (V % 8 == 0 && V <= 4096 && ((uintptr_t)logits & 15) == 0) {
-    const int nch = (V + 511) / 512;
+#define GRACE_SC(TT, NCH, RUN)                                                                  \
+  hipLaunchKernelGGL((beam_scores_reg_kernel<TT, NCH, RUN, CAND>),                              \
+                     dim3((unsigned)(((int64_t)R + kWaves * score_rows_per_wave<NCH, CAND>() - 1) /    \
+                                     (kWaves * score_rows_per_wave<NCH, CAND>()))),                    \
+                     dim3(kScoreThreads), 0, stream, (const TT*)logits, prev, mask, cand,        \
+                     row_max, lse_out, R, V, smp)
+#define GRACE_SC_NCH(TT, RUN)               \
+  do {                                      \
+    if (nch == 1) GRACE_SC(TT, 1, RUN);     \
+    else if (nch == 2) GRACE_SC(TT, 2, RUN); \
+    else if (nch <= 4) GRACE_SC(TT, 4, RUN); \
+    else GRACE_SC(TT, 8, RUN);              \
+  } while (0)
+  // rows of up to 4096 tokens fit the registers; 16-byte runs need V a
+  // multiple of 8 and 16-byte aligned logits
+  const bool run = V % 8 == 0 && ((uintptr_t)logits & 15) == 0;
+  const int nch = (V + 511) / 512;
+  if (V <= 4096) {
     if (bf16) {
-      if (nch == 1) GRACE_SC(uint16_t, 1);
-      else if (nch == 2) GRACE_SC(uint16_t, 2);
-      else if (nch <= 4) GRACE_SC(uint16_t, 4);
-      else GRACE_SC(uint16_t, 8);
+      if (run) GRACE_SC_NCH(uint16_t, true);
+      else GRACE_SC_NCH(uint16_t, false);
     } else {
-      if (nch == 1) GRACE_SC(float, 1);
-      else if (nch == 2) GRACE_SC(float, 2);
-      else if (nch <= 4) GRACE_SC(float, 4);
-      else GRACE_SC(float, 8);
+      if (run) GRACE_SC_NCH(float, true);
+      else GRACE_SC_NCH(float, false);
     }
-  } else if (bf16) {
-    hipLaunchKernelGGL((beam_scores_kernel<uint16_t, CAND>), grid, block, 0, stream,
-                       (const uint16_t*)logits, prev, mask, cand, row_max, lse_out, R, V);
-  } else {
-    hipLaunchKernelGGL((beam_scores_kernel<float, CAND>), grid, block, 0, stream,
-                       (const float*)logits, prev, mask, cand, row_max, lse_out, R, V);
+    return;
   }
+  const int64_t blocks = ((int64_t)R + kWaves - 1) / kWaves;
+  if (bf16) {
+    hipLaunchKernelGGL((beam_scores_kernel<uint16_t, CAND>), dim3((unsigned)blocks), dim3(kScoreThreads),
+                       0, stream, (const uint16_t*)logits, prev, mask, cand, row_max, lse_out, R, V, smp);
+  } else {
+    hipLaunchKernelGGL((beam_scores_kernel<float, CAND>), dim3((unsigned)blocks), dim3(kScoreThreads), 0,
+                       stream, (const float*)logits, prev, mask, cand, row_max, lse_out, R, V, smp);
+  }
+#undef GRACE_SC_NCH
 #undef GRACE_SC
 }
 
 hipError_t launch_beam_scores(const void* logits, const float* prev, const uint32_t* mask,
                               float* cand, float* row_max, int32_t R, int32_t V, bool bf16,
                               hipStream_t stream) {
-  launch_scores_mode<true>(logits, prev, mask, cand, row_max, nullptr, R, V, bf16, stream);
+  launch_scores_mode<true>(logits, prev, mask, cand, row_max, nullptr, R, V, bf16, SampleOut{}, stream);
   return hipGetLastError();
 }
 
@@ -1007,73 +1547,157 @@ size_t beam_topk_workspace_bytes(int32_t B, int32_t M, int32_t V) {
   return TopkWs::bytes(B, topk_slices((uint32_t)M * (uint32_t)V));
 }
 
+// N <= kSmallN
 template <class Src, bool VEC8>
-static hipError_t launch_topk_src(Src src, const float* row_max, int32_t B, int32_t M, int32_t V,
-                                  int32_t k, void* workspace, int32_t* parents, int32_t* tokens,
-                                  float* scores, hipStream_t stream) {
-  const int S = topk_slices((uint32_t)M * (uint32_t)V);
-  const TopkWs ws(workspace, B, S);
-  const dim3 slices((unsigned)S, (unsigned)B);
-  hipLaunchKernelGGL(topk_slice_max_kernel<Src>, slices, dim3(kSliceThreads), 0, stream, src, row_max,
-                     M, V, ws);
-  // sampled path: a histogram of a sixteenth of the candidates picks a bin,
-  // one full pass gathers everything at or above it, and the count decides
-  hipLaunchKernelGGL((topk_sample_hist_kernel<Src, VEC8>), dim3((unsigned)sample_slices(S), (unsigned)B),
-                     dim3(kSliceThreads), 0, stream, src, M, V, ws);
-  hipLaunchKernelGGL(topk_hist_reduce_kernel, dim3(kHistBins / kReduceBins, (unsigned)B),
-                     dim3(kReduceBins), 0, stream, ws, sample_slices(S), 0);
-  hipLaunchKernelGGL(topk_boundary_kernel<true>, dim3((unsigned)B), dim3(kTopkThreads), 0, stream,
-                     k, ws);
-  hipLaunchKernelGGL((topk_gather_kernel<Src, VEC8>), slices, dim3(kSliceThreads), 0, stream, src,
-                     M, V, ws);
-  hipLaunchKernelGGL(topk_verify_kernel, dim3((unsigned)((B + 63) / 64)), dim3(64), 0, stream, B, k,
-                     ws);
-  // full path, for the requests whose sampled bin did not hold the k best
-  hipLaunchKernelGGL((topk_slice_hist_kernel<Src, VEC8>), slices, dim3(kSliceThreads), 0, stream,
-                     src, M, V, ws);
-  hipLaunchKernelGGL(topk_hist_reduce_kernel, dim3(kHistBins / kReduceBins, (unsigned)B),
-                     dim3(kReduceBins), 0, stream, ws, S, 1);
-  hipLaunchKernelGGL(topk_boundary_kernel<false>, dim3((unsigned)B), dim3(kTopkThreads), 0, stream,
-                     k, ws);
-  hipLaunchKernelGGL((topk_gather_kernel<Src, VEC8>), slices, dim3(kSliceThreads), 0, stream, src,
-                     M, V, ws);
-  hipLaunchKernelGGL(topk_final_kernel<Src>, dim3((unsigned)B), dim3(kTopkThreads), 0, stream, src, M,
-                     V, k, ws, parents, tokens, scores);
+static hipError_t launch_topk_small(const Src& src, int32_t B, uint32_t N, int32_t k,
+                                    const TopkOut& out, hipStream_t stream) {
+  const dim3 grid((unsigned)B), block(kTopkThreads);
+  const uint32_t runs = (N + 8 * kTopkThreads - 1) / (8 * kTopkThreads);
+  if (runs <= 1)
+    hipLaunchKernelGGL((topk_small_kernel<Src, VEC8, 1>), grid, block, 0, stream, src, N, k, out);
+  else if (runs <= 4)
+    hipLaunchKernelGGL((topk_small_kernel<Src, VEC8, 4>), grid, block, 0, stream, src, N, k, out);
+  else
+    hipLaunchKernelGGL((topk_small_kernel<Src, VEC8, 8>), grid, block, 0, stream, src, N, k, out);
   return hipGetLastError();
 }
 
-hipError_t launch_beam_topk(const float* cand, const float* row_max, int32_t B, int32_t M,
-                            int32_t V, int32_t k, void* workspace, int32_t* parents,
-                            int32_t* tokens, float* scores, hipStream_t stream) {
-  return launch_topk_src<CandArray, false>(CandArray{cand}, row_max, B, M, V, k, workspace, parents,
-                                           tokens, scores, stream);
+// Candidates to expect above the threshold, from samples of one in 2^lp: k and
+// eight standard deviations of a sampled count of k, at most 3/4 of the list (as
+// many deviations are left above that).
+static double gather_target(int32_t k, int lp) {
+  return (double)k + 8.0 * sqrt((double)k * (double)(1u << lp));
+}
+static uint32_t samples_wanted(int32_t k, int lp) {
+  const uint32_t t = (uint32_t)fmin(gather_target(k, lp), 0.75 * kGatherCap);
+  const uint32_t w = (t + (1u << lp) - 1) >> lp;
+  return w < 1 ? 1 : w;
+}
+// A sample of one in 2^lp is as good as a larger one while the expected
+// candidates stay within 2.5 k and the list: fewer samples to read cost less than
+// the few more candidates to rank.
+static bool sample_suffices(int32_t k, int lp) {
+  const double t = gather_target(k, lp);
+  return t <= 0.75 * kGatherCap && t <= fmax(2.5 * k, 1024.0);
+}
+
+constexpr uint32_t kSampleTarget = 131072;   // samples per request: eight select workgroups
+
+static unsigned select_blocks(uint32_t n) { return (n + kSelectSamples - 1) / kSelectSamples; }
+
+template <class Smp>
+static void launch_select(const Smp& smp, int32_t B, uint32_t N, int32_t k, int lp, const TopkWs& ws,
+                          hipStream_t stream) {
+  hipLaunchKernelGGL(topk_select_kernel<Smp>, dim3(select_blocks(smp.n), (unsigned)B), dim3(kTopkThreads),
+                     0, stream, smp, N, samples_wanted(k, lp), ws);
+}
+
+template <class Src>
+static void launch_select_chunks(const Src& src, int32_t B, uint32_t N, int32_t k, const TopkWs& ws,
+                                 hipStream_t stream) {
+  int lp = 3;
+  while (lp < 8 && ((N >> lp) > kSampleTarget ||
+                    ((N >> lp) > kSelectSamples && sample_suffices(k, lp + 1))))
+    ++lp;
+  const uint32_t group = 32u << lp, groups = (uint32_t)(((uint64_t)N + group - 1) / group);
+  if (select_blocks(32u * groups) > 1)
+    hipLaunchKernelGGL(topk_clear_kernel, dim3((unsigned)B), dim3(kTopkThreads), 0, stream, ws);
+  launch_select(ChunkSample<Src>{src, lp, 32u * groups}, B, N, k, lp, ws, stream);
+}
+
+template <bool VEC8>
+static hipError_t launch_topk_array(const CandArray& src, int32_t B, uint32_t N, int32_t k,
+                                    void* workspace, const TopkOut& out, hipStream_t stream) {
+  if (N <= kSmallN) return launch_topk_small<CandArray, VEC8>(src, B, N, k, out, stream);
+  const TopkWs ws(workspace, B, topk_slices(N));
+  launch_select_chunks(src, B, N, k, ws, stream);
+  // 16384 candidates (64 KiB) per workgroup, fewer while the chip is not full
+  uint32_t per = 16384;
+  while (per > 4096 && (uint64_t)B * N / per < 2048) per >>= 1;
+  hipLaunchKernelGGL(topk_gather_array_kernel<VEC8>, dim3((N + per - 1) / per, (unsigned)B),
+                     dim3(kGatherThreads), 0, stream, src, N, per, ws);
+  hipLaunchKernelGGL((topk_final_kernel<CandArray, VEC8>), dim3((unsigned)B), dim3(kTopkThreads), 0,
+                     stream, src, N, k, ws, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_beam_topk(const float* cand, const float*, int32_t B, int32_t M, int32_t V,
+                            int32_t k, void* workspace, int32_t* parents, int32_t* tokens,
+                            float* scores, hipStream_t stream) {
+  const uint32_t N = (uint32_t)M * (uint32_t)V;
+  const CandArray src{cand};
+  const TopkOut out{parents, tokens, scores, FastDiv((uint32_t)V), V};
+  // 16-byte loads need every request's candidates on a 16-byte boundary
+  if (N % 8 == 0 && ((uintptr_t)cand & 15) == 0)
+    return launch_topk_array<true>(src, B, N, k, workspace, out, stream);
+  return launch_topk_array<false>(src, B, N, k, workspace, out, stream);
 }
 
 size_t beam_step_workspace_bytes(int32_t B, int32_t M, int32_t V) {
   return beam_topk_workspace_bytes(B, M, V) + (size_t)B * M * 8;
 }
 
+template <class T, bool RUN>
+static hipError_t launch_step(const void* logits, const float* prev, const uint32_t* mask, int32_t B,
+                              int32_t M, int32_t V, int32_t k, void* workspace,
+                              const TopkOut& out, hipStream_t stream) {
+  const int32_t R = B * M;
+  const uint32_t N = (uint32_t)M * (uint32_t)V;
+  const int S = topk_slices(N);
+  const TopkWs ws(workspace, B, S);
+  // after the top-k workspace: the rows' log-sum-exp and upper bounds
+  float* lse = (float*)((char*)workspace + TopkWs::bytes(B, S));
+  float* row_max = lse + R;
+  const CandFromLogits<T> src{(const T*)logits, prev, mask, lse, M, V, FastDiv((uint32_t)V)};
+  constexpr bool bf16 = sizeof(T) == 2;
+  if (N <= kSmallN) {
+    launch_scores_mode<false>(logits, prev, mask, nullptr, row_max, lse, R, V, bf16, SampleOut{}, stream);
+    return launch_topk_small<CandFromLogits<T>, RUN>(src, B, N, k, out, stream);
+  }
+  // the sample of the score pass: one token in eight, or in more where that
+  // does not fit its area or the target, or where fewer do
+  SampleOut smp;
+  for (int lp = 3; lp <= 9 && V >= (1 << lp); ++lp) {
+    const uint64_t per_row = ((uint64_t)V + (1u << lp) - 1) >> lp, n = per_row * M;
+    if (n + 3 > (uint64_t)ws.sample_room()) continue;
+    smp = SampleOut{ws.sample, ws.sample_stride(), select_blocks((uint32_t)n) > 1, ws, (uint32_t)per_row, lp,
+                    M, FastDiv((uint32_t)M)};
+    if (n <= kSelectSamples || (n <= kSampleTarget && !sample_suffices(k, lp + 1))) break;
+  }
+  launch_scores_mode<false>(logits, prev, mask, nullptr, row_max, lse, R, V, bf16, smp, stream);
+  if (smp.p != nullptr)
+    launch_select(StoredSample{smp.p, smp.stride, smp.per_row * (uint32_t)M, prev, M}, B, N, k, smp.lp, ws,
+                  stream);
+  else
+    launch_select_chunks(src, B, N, k, ws, stream);
+  // lanes per row: as many as its runs (tokens) need, at most a wave; rows per
+  // wave: up to 64, fewer while that leaves the chip without waves
+  constexpr int E = RUN ? 8 : 1;
+  int ll = 0;
+  while (ll < 6 && (E << ll) < V) ++ll;
+  int32_t rpw = 64;
+  while (rpw > 4 && (int64_t)B * ((M + rpw - 1) / rpw) < 8192) rpw >>= 1;
+  const int32_t per_block = rpw * (kGatherThreads / 64);
+  hipLaunchKernelGGL((topk_gather_rows_kernel<T, RUN>), dim3((unsigned)((M + per_block - 1) / per_block), (unsigned)B),
+                     dim3(kGatherThreads), 0, stream, src, row_max, rpw, ll, N, ws);
+  hipLaunchKernelGGL((topk_final_kernel<CandFromLogits<T>, RUN>), dim3((unsigned)B), dim3(kTopkThreads), 0,
+                     stream, src, N, k, ws, out);
+  return hipGetLastError();
+}
+
 hipError_t launch_beam_step(const void* logits, const float* prev, const uint32_t* mask,
                             int32_t B, int32_t M, int32_t V, int32_t k, bool bf16, void* workspace,
                             int32_t* parents, int32_t* tokens, float* scores,
                             hipStream_t stream) {
-  const int32_t R = B * M;
-  // the top-k workspace, then the rows' log-sum-exp and best scores
-  float* lse = (float*)((char*)workspace + beam_topk_workspace_bytes(B, M, V));
-  float* row_max = lse + R;
-  launch_scores_mode<false>(logits, prev, mask, nullptr, row_max, lse, R, V, bf16, stream);
-  const FastDiv per_row((uint32_t)V);
-#define GRACE_STEP(TT, VEC)                                                                      \
-  return launch_topk_src<CandFromLogits<TT>, VEC>(                                               \
-      CandFromLogits<TT>{(const TT*)logits, prev, mask, lse, M, V, per_row}, row_max, B, M, V, k, \
-      workspace, parents, tokens, scores, stream)
+  const TopkOut out{parents, tokens, scores, FastDiv((uint32_t)V), V};
   // runs of eight: V a multiple of 8 and 16-byte aligned logits
-  const bool vec = V % 8 == 0 && ((uintptr_t)logits & 15) == 0;
+  const bool run = V % 8 == 0 && ((uintptr_t)logits & 15) == 0;
+#define GRACE_STEP(TT, RUN) return launch_step<TT, RUN>(logits, prev, mask, B, M, V, k, workspace, out, stream)
   if (bf16) {
-    if (vec) GRACE_STEP(uint16_t, true);
+    if (run) GRACE_STEP(uint16_t, true);
     GRACE_STEP(uint16_t, false);
   }
-  if (vec) GRACE_STEP(float, true);
+  if (run) GRACE_STEP(float, true);
   GRACE_STEP(float, false);
 #undef GRACE_STEP
 }

@@ -172,6 +172,77 @@ def test_beam_step_equals_scores_then_topk(gpu, i):
     assert torch.equal(s1.view(torch.int32), s2.view(torch.int32)), "scores (bitwise)"
 
 
+# Selection paths of the top-k: (B, M, V, k, structure).  Up to 65536 candidates
+# per request stay in one workgroup's registers (8192 of them without a
+# threshold); beyond that a sampled threshold, a gather and a ranking, or the
+# exact selection when the gathered set is too small or too large.
+SELECT_CASES = [
+    (3, 16, 512, 100, "normal"),        # 8192: all gathered
+    (2, 8200, 1, 4096, "normal"),       # just past it, one token per row
+    (2, 128, 512, 4096, "normal"),      # 65536: the last of the register path
+    (2, 129, 512, 4096, "normal"),      # the first of the sampled path
+    (1, 130, 509, 1000, "normal"),      # tokens 64 apart, rows of no whole run
+    (2, 20000, 7, 500, "normal"),       # rows shorter than any sampling step
+    (1, 2049, 512, 4096, "normal"),     # eight select workgroups
+    (1, 2100, 509, 4096, "ordered"),    # the same, every row sorted by token
+    (2, 300, 512, 2000, "dead"),        # fewer than k above -inf, then NaN rows
+    (2, 300, 512, 2000, "nan"),
+    (2, 600, 256, 3000, "wide"),        # k-th best far below the sampled window
+    (2, 300, 512, 64, "chunk"),         # the k best where the sample does not see them
+    (2, 300, 512, 1000, "equal"),       # all tied: more than the list holds
+    (2, 300, 512, 1000, "inf"),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", SELECT_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_beam_selection_paths_bit_exact(gpu, case, dtype):
+    """grace_beam_step and grace_beam_topk (with and without the row maxima, and
+    for the step with logits off the 16-byte alignment) against the oracle's
+    order of the library's own candidate scores: the same fp32 values, so bit for bit."""
+    B, M, V, k, kind = case
+    R = B * M
+    _log(f"[beam select] {dtype} B={B} M={M} V={V} k={k} {kind}")
+    rng = np.random.default_rng(R + V)
+    logits = W.beam_logits(31, 2, R, V, "f32")
+    prev = W.beam_prev_scores(31, 2, R)
+    mask = None
+    if kind == "ordered":
+        logits = torch.sort(logits, dim=1).values
+    elif kind == "dead":
+        mask = W.beam_mask(31, 2, R, V, keep=0.6 * k / (M * V))
+    elif kind == "nan":
+        prev[rng.random(R) < 0.9] = np.nan
+        mask = W.beam_mask(31, 2, R, V, keep=0.02)
+    elif kind == "wide":
+        prev = prev * np.float32(200)
+        mask = W.beam_mask(31, 2, R, V, keep=0.1)
+    elif kind == "chunk":
+        prev[:] = -40.0
+        prev[::M] = 0.0
+    elif kind == "equal":
+        logits[:], prev[:] = 0.5, -3.0
+    elif kind == "inf":
+        prev[::7] = np.inf
+    logits, prev = logits.to(W.TORCH_DTYPES[dtype]).to(gpu), torch.from_numpy(prev).to(gpu)
+    shifted = torch.empty((R * V + 1,), dtype=logits.dtype, device=gpu)[1:].view(R, V)
+    shifted.copy_(logits)
+    mask = _mask_tensor(mask, gpu)
+    for what, x in (("aligned", logits), ("shifted", shifted)):
+        cand, rmax = G.grace_beam_scores(x, prev, mask)
+        runs = {"step": G.grace_beam_step(x, prev, B, M, k, mask=mask),
+                "topk": G.grace_beam_topk(cand, B, M, k, row_max=rmax),
+                "topk, no hint": G.grace_beam_topk(cand, B, M, k)}
+        torch.cuda.synchronize()
+        rp, rt, rs = BO.beam_topk(cand.cpu().numpy(), B, M, V, k)
+        for name, (par, tok, sc) in runs.items():
+            assert np.array_equal(par.cpu().numpy(), rp), (what, name, "parents")
+            assert np.array_equal(tok.cpu().numpy(), rt), (what, name, "tokens")
+            sc = sc.cpu().numpy()
+            same = (sc.view(np.uint32) == rs.view(np.uint32)) | (np.isnan(sc) & np.isnan(rs))
+            assert same.all(), (what, name, "scores (bitwise)")
+
+
 DYN = [
     dict(dtype="bf16", B=3, H=2, d=64, widths=(1, 5, 12, 12)),
     dict(dtype="f32", B=2, H=3, d=32, widths=(1, 4, 9, 7, 9)),
