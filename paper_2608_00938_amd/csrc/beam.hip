@@ -525,18 +525,6 @@ __device__ void bitonic_desc(uint64_t* list, int n) {
   }
 }
 
-// Inclusive scan over the 64 lanes (row shifts within 16 lanes, then row
-// broadcasts), in the vector ALU.
-__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // row_shr:1
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);   // row_shr:2
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);   // row_shr:4
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);   // row_shr:8
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // row_bcast:15
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // row_bcast:31
-  return x;
-}
-
 // Exclusive prefix of one uint32 per thread over the block (1024 threads);
 // *total receives the sum.  Every wave scans the wave totals for itself.
 __device__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* scratch, uint32_t* total) {

@@ -69,6 +69,34 @@ def test_gtm_mask_sampled_parity_medium(gpu, medium, level):
         assert np.array_equal(got[r], want), f"row {r}"
 
 
+@pytest.mark.parametrize("V,B,M", [(512, 8, 1), (512, 3, 2731), (512, 5, 27001), (4096, 2, 65537)],
+                         ids=["beam_per_group", "groups_of_4", "groups_of_64", "words_limit"])
+def test_gtm_mask_group_sizes(gpu, V, B, M):
+    """Beams per workgroup from 1 to 64, workgroups that straddle requests, the
+    root's many children beside leaves and dead beams: rows at the request
+    boundaries and at random against the oracle."""
+    ix, us = W.gtm_index(9, 2000, V=V), W.gtm_users(9, B, L_max=8)
+    us["n_loc"][-1] = 0                       # no location: nothing allowed
+    gi, gu = G.GtmIndex(ix, gpu), G.GtmUsers(us, gpu)
+    rng = np.random.default_rng(V + M)
+    lf = ix["level_first"]
+    nodes = rng.integers(1, lf[-1], size=B * M).astype(np.int32)
+    nodes[rng.random(B * M) < 0.1] = -1
+    nodes[:: max(1, M // 5)] = 0
+    _log(f"[gtm groups] V={V} {B}x{M}")
+    err = torch.zeros(1, dtype=torch.int32, device=gpu)
+    got = _mask_np(G.grace_gtm_mask(gi, gu, torch.from_numpy(nodes).to(gpu), B, M, err_flag=err))
+    assert int(err.item()) == 0
+    edges = [b * M + o for b in range(1, B) for o in range(-3, 4)]
+    rows = np.unique(np.clip(np.concatenate([edges, rng.choice(B * M, size=min(B * M, 60))]), 0, B * M - 1))
+    for r in rows.astype(int):
+        b = r // M
+        sub = {"bitmask": us["bitmask"][b:b + 1], "bloom": us["bloom"][b:b + 1],
+               "n_loc": us["n_loc"][b:b + 1]}
+        want = GO.pack_mask(GO.gtm_mask(ix, sub, nodes[r:r + 1], 1, 1))[0]
+        assert np.array_equal(got[r], want), f"row {r}"
+
+
 def test_gtm_mask_flags_bad_index_data(gpu, small):
     ix, us = small
     bad = dict(ix)
