@@ -22,8 +22,9 @@
 // every global access instruction covers full rows instead of 16-byte pieces
 // of 32 rows.
 //
-// fp32 path (VALU, cross_attn_f32_kernel).  d/32 lanes per beam, K/V tiles in
-// LDS read as broadcasts, fp32 FMAs throughout.
+// fp32 path (cross_attn_f32_kernel).  The same transposed products in fp32
+// (v_mfma_f32_32x32x2_f32), operands straight from memory, with the running
+// maximum of the definition; small grids split the keys over a workgroup's waves.
 #include <type_traits>
 
 #include "common.hpp"
@@ -45,81 +46,184 @@ __device__ __forceinline__ void request_span(const int32_t* off, int32_t b, int3
 }
 
 // ---------------------------------------------------------------------------
-// fp32 VALU kernel.  G = d/32 consecutive lanes share a beam, each holding 32
-// dims of its query and output accumulator (at most 64 live values per lane
-// at any d); partial dot products meet in a DPP group sum.  K/V tiles sit in
-// LDS and are read as broadcasts across the beams of the workgroup.
+// fp32 kernel.  Each wave owns 32 beams and computes, per 32-key tile,
+//   S^T = K Q^T       A: lane = key l % 32, dims 8j + 4 (l / 32) + 0..3 of step j
+//                     (one 16-byte load each); B: the same dims of beam l % 32,
+//                     held in registers;
+//   P = exp2(c (S^T - m))  with the running maximum m of the beam (lane l % 32
+//                     of both halves), O and the row sum rescaled when it moves;
+//   O^T += V^T P^T    B = P^T as the S^T registers hold it: register 4g + i of
+//                     half hi is key 8g + 4hi + i; A: that key's value, dim l % 32
+//                     of each 32-wide block (one 128-byte row piece per half wave).
+// Bound by the matrix core's fp32 rate (a 32x32x2 product takes 64 cycles for two
+// 256-byte operand registers), so operands come from memory without LDS: 16 KiB
+// per wave and 4096 cycles at d = 64.  A tile's values are loaded before its
+// score products and the next tile's keys before its value products.  8 requests
+// x 250 beams x 8 heads x 64, 33..300 keys: the VALU kernel this replaces, one LDS
+// read per FMA, 89 us, this 19 us; 32 x 1024 x 8 x 64, 512 keys: 1198 and
+// 353 us (97 of the 157 TFLOP/s peak).
+//
+// NS waves share 32 beams, wave s taking the key tiles s, s + NS, ...; their
+// partial results meet in LDS.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(64)
+constexpr int kF32Waves = 4;
+// four floats in memory, which need not lie on a 16-byte boundary
+typedef f32x4 __attribute__((aligned(4))) f32x4_a4;
+
+template <int D, int NS>
+__global__ void __launch_bounds__(kF32Waves * 64, D == 128 ? 1 : 2)
 cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                       const float* __restrict__ v, const int32_t* __restrict__ off,
                       float* __restrict__ out, int32_t M, int32_t H, int32_t sum_L,
                       int32_t n_mt, float c) {
-  constexpr int TILE = 32;
-  constexpr int G = D / 32;          // lanes per beam
-  constexpr int kBeams = 64 / G;     // beams per workgroup
-  __shared__ float ks[TILE][D];
-  __shared__ float vs[TILE][D];
+  constexpr int kGroups = kF32Waves / NS;   // 32-beam groups per workgroup
+  constexpr int kJ = D / 8, kDB = D / 32;
+  constexpr int kStride = D + 4;            // floats per beam row in LDS
+  __shared__ __attribute__((aligned(16))) float o_lds[kF32Waves][32][kStride];
+  __shared__ float ml_lds[kF32Waves][2][32];
   const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
   const int32_t mt = tile % n_mt;
   const int32_t bh = tile / n_mt;
   const int32_t h = bh % H, b = bh / H;
-  const int part = threadIdx.x % G;  // dims part*32 .. part*32+31
-  const int32_t m = mt * kBeams + threadIdx.x / G;
   int32_t o0, L;
   request_span(off, b, sum_L, o0, L);
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int split = wave % NS, group = wave / NS;
+  const int32_t m0 = (mt * kGroups + group) * 32;
+  const bool active = m0 < M;
   const int64_t E = (int64_t)H * D;
-  const int64_t row = (int64_t)b * M + m;
-  const int64_t col = (int64_t)h * D + part * 32;
+  const int32_t n = (L + 31) / 32;
+  const float* const kh = k + (int64_t)o0 * E + h * D + 4 * hi;   // + key * E + 8 j
+  const float* const vh = v + (int64_t)o0 * E + h * D;            // + key * E + 32 db + l32
 
-  float qr[32], acc[32];
+  f32x16 o[kDB];
 #pragma unroll
-  for (int e = 0; e < 32; ++e) {
-    qr[e] = m < M ? q[row * E + col + e] : 0.f;
-    acc[e] = 0.f;
-  }
+  for (int db = 0; db < kDB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
-  for (int32_t t0 = 0; t0 < L; t0 += TILE) {
-    const int32_t n = min(TILE, L - t0);
-    __syncthreads();
-    for (int i = threadIdx.x; i < TILE * D; i += 64) {
-      const int key = i / D, cc = i % D;
-      const int64_t src = (int64_t)(o0 + t0 + (key < n ? key : n - 1)) * E + h * D + cc;
-      GRACE_DCHECK(o0 + t0 + (key < n ? key : n - 1) < sum_L, kDbgRow);
-      ks[key][cc] = k[src];
-      vs[key][cc] = v[src];
+  if (active && split < n) {
+    const int32_t m = min(m0 + l32, M - 1);   // beams past M repeat the last, never stored
+    f32x4 qf[kJ], kf[kJ];
+    const float* const qrow = q + ((int64_t)b * M + m) * E + h * D + 4 * hi;
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) qf[j] = *(const f32x4_a4*)(qrow + 8 * j);
+    // keys past L repeat the last and get weight 0
+    auto load_k = [&](int32_t t) __attribute__((always_inline)) {
+      const int32_t key = min(t * 32 + l32, L - 1);
+      GRACE_DCHECK(o0 + key < sum_L, kDbgRow);
+      const float* const row = kh + (int64_t)key * E;
+#pragma unroll
+      for (int j = 0; j < kJ; ++j) kf[j] = *(const f32x4_a4*)(row + 8 * j);
+    };
+    load_k(split);
+    for (int32_t t = split; t < n; t += NS) {
+      const int32_t t0 = t * 32;
+      float vf[16][kDB];
+      if (t0 + 32 <= L) {
+        const uint32_t lane_off = (uint32_t)(4 * hi) * (uint32_t)E + (uint32_t)l32;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float* const row = vh + (int64_t)(t0 + 8 * (r >> 2) + (r & 3)) * E;   // uniform
+#pragma unroll
+          for (int db = 0; db < kDB; ++db) vf[r][db] = row[lane_off + 32 * db];
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int32_t key = min(t0 + 8 * (r >> 2) + 4 * hi + (r & 3), L - 1);
+          const float* const row = vh + (int64_t)key * E + l32;
+#pragma unroll
+          for (int db = 0; db < kDB; ++db) vf[r][db] = row[32 * db];
+        }
+      }
+      // two chains of products
+      f32x16 s0 = {}, s1 = {};
+#pragma unroll
+      for (int j = 0; j < kJ; ++j) {
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e + 1], qf[j][e + 1], s1, 0, 0, 0);
+        }
+      }
+      if (t + NS < n) load_k(t + NS);
+      float mx = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s0[r] += s1[r];
+        if (t0 + 32 > L && t0 + 8 * (r >> 2) + 4 * hi + (r & 3) >= L) s0[r] = -INFINITY;
+        mx = fmaxf(mx, s0[r]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float m_new = fmaxf(m_run, mx);
+      if (__any(m_new != m_run)) {
+        const float alpha = fast_exp2((m_run - m_new) * c);
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+        m_run = m_new;
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = fast_exp2((s0[r] - m_run) * c);
+        l_run += p;   // this half's keys
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[r][db], p, o[db], 0, 0, 0);
+      }
     }
-    __syncthreads();
-    float s[TILE];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < TILE; ++j) {
-      float a = 0.f;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) a = __builtin_fmaf(qr[e], ks[j][part * 32 + e], a);
-      a = group_sum<G>(a);
-      s[j] = j < n ? a : -INFINITY;
-      mx = fmaxf(mx, s[j]);
-    }
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = fast_exp2((m_run - m_new) * c);
-    m_run = m_new;
-    l_run *= alpha;
-#pragma unroll
-    for (int e = 0; e < 32; ++e) acc[e] *= alpha;
-#pragma unroll
-    for (int j = 0; j < TILE; ++j) {
-      const float p = fast_exp2((s[j] - m_new) * c);
-      l_run += p;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) acc[e] = __builtin_fmaf(p, vs[j][part * 32 + e], acc[e]);
-    }
+    l_run += __shfl_xor(l_run, 32);
   }
-  if (m < M) {
+
+  // Output through LDS as beam rows: lane holds dims 32 db + 8 g + 4 hi + 0..3
+  // of beam l32.  With one wave per beam group it only reads back its own rows.
+  if (NS == 1) {
     const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
 #pragma unroll
-    for (int e = 0; e < 32; ++e) out[row * E + col + e] = acc[e] * inv;
+    for (int db = 0; db < kDB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[db][r] *= inv;
+  }
+#pragma unroll
+  for (int db = 0; db < kDB; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *(f32x4*)&o_lds[wave][l32][32 * db + 8 * g + 4 * hi] =
+          f32x4{o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]};
+  if (NS > 1 && hi == 0) {
+    ml_lds[wave][0][l32] = m_run;
+    ml_lds[wave][1][l32] = l_run;
+  }
+  __syncthreads();
+  // the group's NS waves share out its 32 rows
+  constexpr int kLanesPerRow = D / 4, kRowsPerPass = 64 / kLanesPerRow;
+  constexpr int kRows = 32 / NS;
+#pragma unroll
+  for (int i = 0; i < kRows / kRowsPerPass; ++i) {
+    const int row = split * kRows + i * kRowsPerPass + lane / kLanesPerRow, col = 4 * (lane % kLanesPerRow);
+    f32x4 acc;
+    if constexpr (NS == 1) {
+      acc = *(const f32x4*)&o_lds[wave][row][col];
+    } else {
+      float mm = -INFINITY, ll = 0.f;
+#pragma unroll
+      for (int w = 0; w < NS; ++w) mm = fmaxf(mm, ml_lds[group * NS + w][0][row]);
+      acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NS; ++w) {
+        // a wave without keys has weight exp2(-inf) = 0
+        const float l_w = ml_lds[group * NS + w][1][row];
+        const float f = l_w > 0.f ? fast_exp2((ml_lds[group * NS + w][0][row] - mm) * c) : l_w;
+        ll += f * l_w;
+        acc += f * *(const f32x4*)&o_lds[group * NS + w][row][col];
+      }
+      acc *= ll > 0.f ? 1.0f / ll : 0.f;
+    }
+    if (m0 + row < M) *(f32x4_a4*)(out + ((int64_t)b * M + m0 + row) * E + h * D + col) = acc;
   }
 }
 
@@ -930,19 +1034,28 @@ hipError_t launch_cross_attn(const void* q, const void* enc_k, const void* enc_v
     if (d == 128) GRACE_X(128)
 #undef GRACE_X
   } else {
-#define GRACE_X(DD)                                                                          \
-  {                                                                                          \
-    const int32_t n_mt = (M + 64 / (DD / 32) - 1) / (64 / (DD / 32));                       \
-    const int64_t grid = (int64_t)B * H * n_mt;                                             \
-    hipLaunchKernelGGL(cross_attn_f32_kernel<DD>, dim3((unsigned)grid), dim3(64), 0, stream, \
-                       (const float*)q, (const float*)enc_k, (const float*)enc_v, enc_off,   \
-                       (float*)out, M, H, sum_L, n_mt, c);                                   \
-    return hipGetLastError();                                                                \
+    // Beams of a workgroup: 128, or 64 or 32 with the keys split over two or four
+    // waves while that leaves fewer than two workgroups per CU.
+    int ns = 1;
+    while (ns < kF32Waves && (int64_t)B * H * ((M + 128 / ns - 1) / (128 / ns)) < 512) ns *= 2;
+    const int32_t n_mt = (M + 128 / ns - 1) / (128 / ns);
+    const int64_t grid = (int64_t)B * H * n_mt;
+#define GRACE_XN(DD, NS)                                                                          \
+  hipLaunchKernelGGL((cross_attn_f32_kernel<DD, NS>), dim3((unsigned)grid), dim3(kF32Waves * 64), \
+                     0, stream, (const float*)q, (const float*)enc_k, (const float*)enc_v,        \
+                     enc_off, (float*)out, M, H, sum_L, n_mt, c)
+#define GRACE_X(DD)              \
+  {                              \
+    if (ns == 1) GRACE_XN(DD, 1); \
+    else if (ns == 2) GRACE_XN(DD, 2); \
+    else GRACE_XN(DD, 4);        \
+    return hipGetLastError();    \
   }
     if (d == 32) GRACE_X(32)
     if (d == 64) GRACE_X(64)
     if (d == 128) GRACE_X(128)
 #undef GRACE_X
+#undef GRACE_XN
   }
   return hipErrorInvalidValue;
 }

@@ -311,6 +311,46 @@ def test_edge_shapes_full_parity(gpu, i, fused):
     _full_check(dec)
 
 
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("B,M,H", [(5, 33, 3), (8, 130, 12), (8, 387, 16)], ids=["split4", "split2", "whole"])
+def test_cross_f32_key_splits(gpu, B, M, H, d):
+    """The fp32 kernel with the keys of a beam group split over four, two or one
+    of a workgroup's waves, against the fp64 oracle: lengths from none over a
+    single key to several tiles (so that waves run out of tiles), beam counts off
+    the 32-beam group, operands off the 16-byte alignment, and scores large enough
+    that a maximum is needed.  Tolerance: fp32 rounding of sums of up to 200 terms
+    and of exp2 arguments of magnitude up to 100 (2^-24 * 100 = 6e-6 relative)."""
+    rng = np.random.default_rng(B * M + d)
+    lengths = np.array(([0, 1, 31, 32, 33, 64, 130, 200] * 2)[:B])
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    _log(f"[cross f32 splits] B={B} M={M} H={H} d={d} L={lengths.tolist()}")
+
+    def odd(a):   # one element past a 16-byte boundary
+        t = torch.empty((a.size + 1,), dtype=torch.float32, device=gpu)[1:].view(a.shape)
+        return t.copy_(torch.from_numpy(a))
+
+    q = (3 * rng.standard_normal((B * M, H, d))).astype(np.float32)
+    k = (2 * rng.standard_normal((off[-1], H, d))).astype(np.float32)
+    v = rng.standard_normal((off[-1], H, d)).astype(np.float32)
+    out = odd(np.full_like(q, np.nan))
+    G.grace_cross_attn(odd(q), odd(k), odd(v), torch.from_numpy(off).to(gpu), M, out=out)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(M - 3, B * M, M), rng.choice(B * M, size=min(B * M, 120))]))
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    worst = 0.0
+    for b in range(B):
+        mine = rows[rows // M == b]
+        if mine.size == 0:
+            continue
+        one = np.array([0, lengths[b]])
+        ref = oracle.cross_attn(q[mine].astype(np.float64), k[off[b]:off[b + 1]].astype(np.float64),
+                                v[off[b]:off[b + 1]].astype(np.float64), one, mine.size, 1.0 / math.sqrt(d))
+        worst = max(worst, float(np.abs(got[mine] - ref).max()))
+    _log(f"  max|err| = {worst:.3e}")
+    assert worst <= 2e-5
+
+
 def _random_shape(i):
     """Seeded random small workload: any dtype, head dim, ragged or fixed encoder
     lengths (including tails shorter than a key tile), beam counts off the tile
