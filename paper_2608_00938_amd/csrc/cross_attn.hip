@@ -910,7 +910,8 @@ cross_attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
                   j == 0 ? (mx[mb] > C::kShiftHi || mx[mb] < C::kShiftLo) : mx[mb] > C::kShiftHi;
               const float ns = need ? shift[mb] + mx[mb] : shift[mb];
               const float delta = ns - shift[mb];
-              alpha[mb] = fast_exp2(-delta);
+              // nothing to rescale at the first step (where 2^-delta may overflow)
+              alpha[mb] = j == 0 ? 0.f : fast_exp2(-delta);
               shift[mb] = ns;
 #pragma unroll
               for (int r = 0; r < 16; ++r) sc[mb][r] -= delta;

@@ -351,6 +351,41 @@ def test_cross_f32_key_splits(gpu, B, M, H, d):
     assert worst <= 2e-5
 
 
+@pytest.mark.parametrize("kind", ["plain", "wide", "steps", "tiny"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("H", [2, 48], ids=["split_keys", "whole_keys"])
+def test_cross_bf16_both_kernels(gpu, H, d, kind):
+    """The kernel that splits the keys over a workgroup's waves (grids that fit the
+    chip at once) and the one that does not, on the same kinds of input: lengths
+    from none over a single key to several tiles of every wave, a beam count off
+    the tiles; ordinary scores, scores that need the exponent shift (wide),
+    scores that need it in some 32-key tiles only, so that the waves disagree
+    (steps), and all far below zero (tiny)."""
+    lengths = [0, 1, 31, 33, 64, 97, 300] if H == 2 else [300, 1, 97]
+    B, M = len(lengths), 130 if H == 2 else 300
+    if H == 2 and d == 128:
+        lengths, B = lengths[2:], 5           # 5 * 2 * 5 workgroups
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    g = torch.Generator().manual_seed(700 + d + H)
+    q = torch.randn((B * M, H, d), generator=g)
+    k = torch.randn((int(off[-1]), H, d), generator=g)
+    v = torch.randn((int(off[-1]), H, d), generator=g).to(torch.bfloat16)
+    if kind == "wide":
+        q, k = 4 * q, 4 * k
+    elif kind == "steps":
+        tile = np.concatenate([np.arange(L) // 32 for L in lengths])
+        q, k = 2 * q, 2 * k * torch.from_numpy(np.array([1.0, 12.0, 0.05])[tile % 3])[:, None, None].float()
+    elif kind == "tiny":   # every score near -200 exp2 units
+        q, k = q.abs() + 3, -(k.abs() + 3)
+        k *= 200 / 1.44 / (q[:1].mean() * k.abs().mean() * math.sqrt(d))
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    _log(f"[cross both] H={H} d={d} {kind} L={list(lengths)}")
+    out = G.grace_cross_attn(q.to(gpu), k.to(gpu), v.to(gpu), torch.from_numpy(off).to(gpu), M)
+    torch.cuda.synchronize()
+    ref = oracle.cross_attn(_np(q), _np(k), _np(v), off, M, 1 / math.sqrt(d))
+    _check_close(_np(out), ref, "bf16", f"cross H={H} d={d} {kind}")
+
+
 def _random_shape(i):
     """Seeded random small workload: any dtype, head dim, ragged or fixed encoder
     lengths (including tails shorter than a key tile), beam counts off the tile
