@@ -1000,6 +1000,260 @@ cross_attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
   }
 }
 
+// ---------------------------------------------------------------------------
+// bf16 kernel for small grids: the four waves of a workgroup share 32 beams and
+// split the keys, wave s taking the 32-key tiles s, s + 4, ...  Bound by latency:
+// with 256-beam tiles a few requests leave most CUs idle and each workgroup a
+// serial chain of all the key tiles; here there are 4 to 8 times the workgroups
+// and a quarter of the chain.  8 requests x 256 beams x 8 heads x 64: 8.8 -> 6.6 us
+// at 256 keys, 20.8 -> 12.8 at 1024; 1 x 100 x 8 x 64, 256 keys: 7.8 -> 4.7 (64 beams
+// per workgroup instead of 32: 6.9, 13.3 and 6.5).  Each wave streams its own tiles into LDS of its own (two
+// buffers, no barrier before the end) and runs the safe pass of the kernel above
+// step by step: the same products, the same exponent shift, which stays at zero
+// for ordinary scores.  The waves' partial O and row sums meet in LDS in fp32.
+// ---------------------------------------------------------------------------
+template <int N>
+__device__ __forceinline__ void wait_vmem() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Workgroups of it that fit a CU (their LDS).  Not pipelined within a wave, it
+// loses to the kernel above as soon as they do not all fit the chip at once: 8 x
+// 512 x 8 x 64, 256 keys (1024 workgroups): 10.8 against 8.9 us; 8 x 256 x 8 x 128
+// (512): 13.6 against 9.9.
+template <int D>
+constexpr int kSplitPerCu = D == 32 ? 4 : (D == 64 ? 2 : 1);
+constexpr int kCus = 256;
+
+template <int D>
+__global__ void __launch_bounds__(256, kSplitPerCu<D>)
+cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                             const uint16_t* __restrict__ v, const int32_t* __restrict__ off,
+                             uint16_t* __restrict__ out, int32_t B, int32_t M, int32_t H,
+                             int32_t sum_L, int32_t n_mt, float c) {
+  using C = Cfg<D>;
+  constexpr int NS = 4, MB = 1;                   // waves, 32-beam blocks
+  constexpr int kTileBytes = 32 * C::kRowBytes;
+  constexpr int kLoads = kTileBytes / 1024;       // loads per wave, tile and tensor
+  constexpr int kWaveBytes = 4 * kTileBytes;      // two buffers of K and V
+  constexpr int kRows = MB * 32, kStride = D + 4; // floats per beam row of a partial O
+  constexpr int kLdsBytes = NS * (kWaveBytes > kRows * kStride * 4 ? kWaveBytes : kRows * kStride * 4);
+  __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
+  __shared__ float part_shift[NS][kRows], part_l[NS][kRows];
+
+  int32_t mt, b, h;
+  work_item(blockIdx.x, gridDim.x, n_mt, B, H, mt, b, h);
+  int32_t o0, L;
+  request_span(off, b, sum_L, o0, L);
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t E = H * D;
+  const int32_t m0 = mt * kRows;
+  const int32_t n = (L + 31) / 32;
+  char* const mine = lds + wave * kWaveBytes;
+
+  // queries (B of S^T): 8 consecutive d of beam l32 of block mb per 16-wide step
+  typedef u32x4 __attribute__((aligned(2))) u32x4_a2;
+  bf16x8 qf[MB][C::kKS];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int32_t m = min(m0 + mb * 32 + l32, M - 1);   // beams past M repeat the last, never stored
+    const uint16_t* const row = q + (b * M + m) * E + h * D + 8 * hi;
+#pragma unroll
+    for (int ks = 0; ks < C::kKS; ++ks)
+      qf[mb][ks] = __builtin_bit_cast(bf16x8, *(const u32x4_a2*)(row + 16 * ks));
+  }
+
+  // tile t of K and V into buffer buf of this wave
+  uint32_t dma_off[kLoads];
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    const int sl = i * 64 + lane, key = sl / C::kCPR;
+    const int chunk = (sl % C::kCPR) ^ tile_swizzle<D>(key);
+    dma_off[i] = ((uint32_t)key * (uint32_t)E + (uint32_t)(h * D + chunk * 8)) * 2u;
+  }
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(mine));
+  auto issue = [&](int32_t t, int buf) __attribute__((always_inline)) {
+    const int32_t t0 = t * 32;
+    const uint16_t* const kt = k + (o0 + t0) * E;
+    const uint16_t* const vt = v + (o0 + t0) * E;
+    const uint32_t dst = lds0 + buf * 2 * kTileBytes;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int over = (i * 64 + lane) / C::kCPR - (L - 1 - t0);   // > 0: past the last token
+      const uint32_t o = over > 0 ? dma_off[i] - (uint32_t)over * (uint32_t)E * 2u : dma_off[i];
+      GRACE_DCHECK(o0 + t0 + (i * 64 + lane) / C::kCPR - (over > 0 ? over : 0) < sum_L, kDbgRow);
+      load_to_lds(kt, o, dst + i * 1024);
+      load_to_lds(vt, o, dst + kTileBytes + i * 1024);
+    }
+  };
+
+  bf16x8 sum_a[MB];   // row-sum operands, as in the kernel above
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const uint32_t w = (lane & 15) == 2 * mb + ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
+    sum_a[mb] = __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
+  }
+  uint32_t k_rd[C::kKS], v_rd[2][C::kDB];
+#pragma unroll
+  for (int ks = 0; ks < C::kKS; ++ks) k_rd[ks] = lds0 + C::slot(l32, 2 * ks + hi) * 16;
+  {
+    const int g4 = lane >> 4, gi = lane & 15;
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int db = 0; db < C::kDB; ++db) {
+        const int dcol = db * 32 + 16 * (g4 & 1) + 4 * (gi & 3);
+        const int row = 8 * w + 4 * (g4 >> 1) + (gi >> 2);
+        v_rd[w][db] = lds0 + kTileBytes + C::slot(row, dcol >> 3) * 16 + (dcol & 7) * 2;
+      }
+  }
+  typedef __attribute__((address_space(3))) char lds_char;
+
+  f32x16 o[C::kDB][MB];
+  f32x4 lsum = {0.f, 0.f, 0.f, 0.f};
+  float shift[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    shift[mb] = 0.f;
+#pragma unroll
+    for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[db][mb][r] = 0.f;
+  }
+
+  if (wave < n) issue(wave, 0);
+  for (int32_t t = wave, buf = 0; t < n; t += NS, buf ^= 1) {
+    // the buffer filled next was read a tile ago: those reads are complete
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (t + NS < n) {
+      issue(t + NS, buf ^ 1);
+      wait_vmem<2 * kLoads>();   // tile t has landed, the next may still fly
+    } else {
+      wait_vmem<0>();
+    }
+    const int base = buf * 2 * kTileBytes;
+    f32x16 sc[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sc[mb][r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < C::kKS; ++ks) {
+      const bf16x8 kf = __builtin_bit_cast(
+          bf16x8, *(const __attribute__((address_space(3))) u32x4*)((lds_char*)(uintptr_t)k_rd[ks] + base));
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+        sc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[mb][ks], sc[mb], 0, 0, 0);
+    }
+    float mx[MB];
+    bool move = false;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sc[mb][r] = __builtin_fmaf(sc[mb][r], c, -shift[mb]);
+        if (t * 32 + 32 > L && t * 32 + 8 * (r >> 2) + 4 * hi + (r & 3) >= L) sc[mb][r] = -INFINITY;
+      }
+      float m1 = max3(sc[mb][0], sc[mb][1], sc[mb][2]);
+#pragma unroll
+      for (int r = 3; r + 1 < 16; r += 2) m1 = max3(m1, sc[mb][r], sc[mb][r + 1]);
+      mx[mb] = max_with_other_half(max3(m1, sc[mb][15], sc[mb][15]));
+      move |= mx[mb] > C::kShiftHi || (t < NS && mx[mb] < C::kShiftLo);
+    }
+    if (__any(move)) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const bool need = mx[mb] > C::kShiftHi || (t < NS && mx[mb] < C::kShiftLo);
+        const float delta = need ? mx[mb] : 0.f;
+        // nothing to rescale at the wave's first tile (where 2^-delta may overflow)
+        const float alpha = t < NS ? 0.f : fast_exp2(-delta);
+        shift[mb] += delta;
+        const float alpha_hi = __shfl_xor(alpha, 16);
+        lsum[2 * mb] *= alpha;
+        lsum[2 * mb + 1] *= alpha_hi;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[mb][r] -= delta;
+#pragma unroll
+        for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[db][mb][r] *= alpha;
+      }
+    }
+#pragma unroll
+    for (int kc = 0; kc < 2; ++kc) {
+      bf16x8 vf[C::kDB];
+#pragma unroll
+      for (int db = 0; db < C::kDB; ++db) {
+        i16x4 half[2];
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+          half[w] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (__attribute__((address_space(3))) i16x4*)((lds_char*)(uintptr_t)v_rd[w][db] + base +
+                                                           kc * 16 * C::kRowBytes));
+        vf[db] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(half[0], half[1], 0, 1, 2, 3, 4, 5, 6, 7));
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        u32x4 u;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+          u[w] = pack_bf16x2(fast_exp2(sc[mb][8 * kc + 2 * w]), fast_exp2(sc[mb][8 * kc + 2 * w + 1]));
+        const bf16x8 p = __builtin_bit_cast(bf16x8, u);
+#pragma unroll
+        for (int db = 0; db < C::kDB; ++db)
+          o[db][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], p, o[db][mb], 0, 0, 0);
+        lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sum_a[mb], p, lsum, 0, 0, 0);
+      }
+    }
+  }
+
+  // partial results to LDS, over the tiles (every wave is past its last read)
+  __syncthreads();
+  float* const part = (float*)lds;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const float s_lo = __shfl(lsum[2 * mb], l32 & 15), s_hi = __shfl(lsum[2 * mb + 1], l32 & 15);
+    if (hi == 0) {
+      part_shift[wave][mb * 32 + l32] = shift[mb];
+      part_l[wave][mb * 32 + l32] = l32 < 16 ? s_lo : s_hi;
+    }
+#pragma unroll
+    for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *(f32x4*)(part + ((wave * kRows + mb * 32 + l32) * kStride + 32 * db + 8 * g + 4 * hi)) =
+            f32x4{o[db][mb][4 * g], o[db][mb][4 * g + 1], o[db][mb][4 * g + 2], o[db][mb][4 * g + 3]};
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kRows * C::kCPR; i += 256) {
+    const int row = i / C::kCPR, col = 8 * (i % C::kCPR);
+    if (m0 + row >= M) break;   // rows ascend
+    float top = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NS; ++w)
+      if (w < n) top = fmaxf(top, part_shift[w][row]);   // the waves that had keys
+    float l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NS; ++w) {
+      if (w >= n) break;
+      const float f = fast_exp2(part_shift[w][row] - top);
+      l = __builtin_fmaf(f, part_l[w][row], l);
+#pragma unroll
+      for (int e = 0; e < 8; e += 4) {
+        const f32x4 x = *(const f32x4*)(part + ((w * kRows + row) * kStride + col + e));
+#pragma unroll
+        for (int z = 0; z < 4; ++z) acc[e + z] = __builtin_fmaf(f, x[z], acc[e + z]);
+      }
+    }
+    const float inv = l > 0.f ? 1.0f / l : 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] *= inv;
+    GRACE_DCHECK(b * M + m0 + row < B * M, kDbgRow);
+    *(u32x4_a2*)(out + (b * M + m0 + row) * E + h * D + col) = Chunk<BF16>::pack(acc);
+  }
+}
+
 hipError_t debug_take_cross(uint32_t* acc) {
 #ifdef GRACE_DEBUG
   uint32_t tmp[kDbgKinds] = {};
@@ -1024,6 +1278,13 @@ hipError_t launch_cross_attn(const void* q, const void* enc_k, const void* enc_v
   {                                                                                           \
     const int32_t n_mt = (M + Cfg<DD>::kBlockM - 1) / Cfg<DD>::kBlockM;                    \
     const int64_t grid = (int64_t)B * H * n_mt;                                              \
+    const int32_t n_ms = (M + 31) / 32;                                                       \
+    if ((int64_t)B * H * n_ms <= kCus * kSplitPerCu<DD>) {                                    \
+      hipLaunchKernelGGL(cross_attn_bf16_split_kernel<DD>, dim3((unsigned)(B * H * n_ms)),    \
+                         dim3(256), 0, stream, (const uint16_t*)q, (const uint16_t*)enc_k,    \
+                         (const uint16_t*)enc_v, enc_off, (uint16_t*)out, B, M, H, sum_L, n_ms, c); \
+      return hipGetLastError();                                                               \
+    }                                                                                         \
     hipLaunchKernelGGL(cross_attn_bf16_kernel<DD>, dim3((unsigned)grid),                 \
                        dim3(Cfg<DD>::kThreads), 0, stream, (const uint16_t*)q,               \
                        (const uint16_t*)enc_k, (const uint16_t*)enc_v, enc_off, (uint16_t*)out, \
