@@ -405,3 +405,12 @@ def test_binding_raises_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(G, "_LIB_PATH", str(tmp_path / "missing.so"))
     with pytest.raises(RuntimeError, match="missing"):
         G.library()
+
+
+def test_host_tensors_are_refused():
+    """The stream lookup by raw handle has none for a tensor in host memory: the
+    call raises before it reaches the library."""
+    torch = pytest.importorskip("torch")
+    q = torch.zeros((4, 2, 64))
+    with pytest.raises((ValueError, RuntimeError)):
+        G.grace_cross_attn(q, q, q, torch.tensor([0, 4], dtype=torch.int32), 4)
