@@ -45,6 +45,33 @@ __device__ __forceinline__ void request_span(const int32_t* off, int32_t b, int3
   L = e - a;
 }
 
+// Work item of workgroup i: (beam tile mt, request b, head h).  Workgroup i
+// runs on XCD x = i % 8.  When the head count is a multiple of 8, XCD x takes
+// the heads h = x (mod 8) of every request, so each XCD gets the same mix of
+// encoder lengths (the same work for ragged requests), and walks the requests
+// starting at request x*B/8, so that at any time the XCDs read different
+// requests' rows.  All beam tiles of one (request, head) run back to back on
+// one XCD, whose L2 then serves that head's K/V to all of them.
+__device__ __forceinline__ void work_item(uint32_t i, uint32_t n, int32_t n_mt, int32_t B,
+                                          int32_t H, int32_t& mt, int32_t& b, int32_t& h) {
+  constexpr uint32_t kXcds = 8;
+  if (H % kXcds != 0) {
+    const uint32_t tile = xcd_remap(i, n);
+    mt = (int32_t)(tile % (uint32_t)n_mt);
+    const uint32_t bh = tile / (uint32_t)n_mt;
+    h = (int32_t)(bh % (uint32_t)H);
+    b = (int32_t)(bh / (uint32_t)H);
+    return;
+  }
+  const uint32_t x = i % kXcds, k = i / kXcds;
+  const uint32_t hpx = (uint32_t)H / kXcds;            // heads per XCD and request
+  const uint32_t p = k / (uint32_t)n_mt;                // (request, head) pair of this XCD
+  mt = (int32_t)(k % (uint32_t)n_mt);
+  const uint32_t shift = x * (((uint32_t)B + kXcds - 1) / kXcds);
+  b = (int32_t)((p / hpx + shift) % (uint32_t)B);
+  h = (int32_t)((p % hpx) * kXcds + x);
+}
+
 // ---------------------------------------------------------------------------
 // fp32 kernel.  Each wave owns 32 beams and computes, per 32-key tile,
 //   S^T = K Q^T       A: lane = key l % 32, dims 8j + 4 (l / 32) + 0..3 of step j
@@ -74,17 +101,15 @@ template <int D, int NS>
 __global__ void __launch_bounds__(kF32Waves * 64, D == 128 ? 1 : 2)
 cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                       const float* __restrict__ v, const int32_t* __restrict__ off,
-                      float* __restrict__ out, int32_t M, int32_t H, int32_t sum_L,
+                      float* __restrict__ out, int32_t B, int32_t M, int32_t H, int32_t sum_L,
                       int32_t n_mt, float c) {
   constexpr int kGroups = kF32Waves / NS;   // 32-beam groups per workgroup
   constexpr int kJ = D / 8, kDB = D / 32;
   constexpr int kStride = D + 4;            // floats per beam row in LDS
   __shared__ __attribute__((aligned(16))) float o_lds[kF32Waves][32][kStride];
   __shared__ float ml_lds[kF32Waves][2][32];
-  const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
-  const int32_t mt = tile % n_mt;
-  const int32_t bh = tile / n_mt;
-  const int32_t h = bh % H, b = bh / H;
+  int32_t mt, b, h;
+  work_item(blockIdx.x, gridDim.x, n_mt, B, H, mt, b, h);
   int32_t o0, L;
   request_span(off, b, sum_L, o0, L);
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
@@ -387,33 +412,6 @@ __device__ __forceinline__ void wait_vmem_upto(int n) {
     case 7: asm volatile("s_waitcnt vmcnt(7)" ::: "memory"); break;
     default: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
   }
-}
-
-// Work item of workgroup i: (beam tile mt, request b, head h).  Workgroup i
-// runs on XCD x = i % 8.  When the head count is a multiple of 8, XCD x takes
-// the heads h = x (mod 8) of every request, so each XCD gets the same mix of
-// encoder lengths (the same work for ragged requests), and walks the requests
-// starting at request x*B/8, so that at any time the XCDs read different
-// requests' rows.  All beam tiles of one (request, head) run back to back on
-// one XCD, whose L2 then serves that head's K/V to all of them.
-__device__ __forceinline__ void work_item(uint32_t i, uint32_t n, int32_t n_mt, int32_t B,
-                                          int32_t H, int32_t& mt, int32_t& b, int32_t& h) {
-  constexpr uint32_t kXcds = 8;
-  if (H % kXcds != 0) {
-    const uint32_t tile = xcd_remap(i, n);
-    mt = (int32_t)(tile % (uint32_t)n_mt);
-    const uint32_t bh = tile / (uint32_t)n_mt;
-    h = (int32_t)(bh % (uint32_t)H);
-    b = (int32_t)(bh / (uint32_t)H);
-    return;
-  }
-  const uint32_t x = i % kXcds, k = i / kXcds;
-  const uint32_t hpx = (uint32_t)H / kXcds;            // heads per XCD and request
-  const uint32_t p = k / (uint32_t)n_mt;                // (request, head) pair of this XCD
-  mt = (int32_t)(k % (uint32_t)n_mt);
-  const uint32_t shift = x * (((uint32_t)B + kXcds - 1) / kXcds);
-  b = (int32_t)((p / hpx + shift) % (uint32_t)B);
-  h = (int32_t)((p % hpx) * kXcds + x);
 }
 
 template <int D>
@@ -1305,7 +1303,7 @@ hipError_t launch_cross_attn(const void* q, const void* enc_k, const void* enc_v
 #define GRACE_XN(DD, NS)                                                                          \
   hipLaunchKernelGGL((cross_attn_f32_kernel<DD, NS>), dim3((unsigned)grid), dim3(kF32Waves * 64), \
                      0, stream, (const float*)q, (const float*)enc_k, (const float*)enc_v,        \
-                     enc_off, (float*)out, M, H, sum_L, n_mt, c)
+                     enc_off, (float*)out, B, M, H, sum_L, n_mt, c)
 #define GRACE_X(DD)              \
   {                              \
     if (ns == 1) GRACE_XN(DD, 1); \
