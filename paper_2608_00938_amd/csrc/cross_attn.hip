@@ -365,11 +365,17 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // its even 8-key groups and beam c+16 in its odd ones, so A rows with ones on
 // the even (odd) groups give the sums of beam c (c+16).
 // ---------------------------------------------------------------------------
-template <int D>
+// MB: 32-beam blocks per wave.  Two where they fit the registers (d = 32, 64); one
+// halves a workgroup's beams to 128, for grids that then have at most a workgroup
+// per CU (8 x 512 x 8 x 64: 128 -> 256 workgroups, 9.1 -> 7.2 us at 256 keys, 21.4 ->
+// 16.2 at 1024) and for requests of at most 128 beams (128 x 64 x 8 x 64: 20.7 -> 18.8).
+// With more workgroups two blocks per wave win, as each K or V fragment read from
+// LDS then feeds two products (16 x 1024 x 8 x 64, 256 keys: 14.5 against 18.4).
+template <int D, int MB = (D == 128 ? 1 : 2)>
 struct Cfg {
   static constexpr int kWaves = 4;
   static constexpr int kThreads = kWaves * 64;
-  static constexpr int kMB = D == 128 ? 1 : 2;         // 32-beam blocks per wave
+  static constexpr int kMB = MB;         // 32-beam blocks per wave
   static constexpr int kBlockM = kWaves * kMB * 32;    // beams per workgroup
   static constexpr int kTileN = D == 128 ? 32 : 64;    // keys per LDS tile
   static constexpr int kSub = kTileN / 32;             // 32-key steps per tile
@@ -414,13 +420,13 @@ __device__ __forceinline__ void wait_vmem_upto(int n) {
   }
 }
 
-template <int D>
-__global__ void __launch_bounds__(Cfg<D>::kThreads, 2)
+template <int D, int MB>
+__global__ void __launch_bounds__(256, 2)
 cross_attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                             const uint16_t* __restrict__ v, const int32_t* __restrict__ off,
                             uint16_t* __restrict__ out, int32_t B, int32_t M, int32_t H,
                             int32_t sum_L, int32_t n_mt, float c) {
-  using C = Cfg<D>;
+  using C = Cfg<D, MB>;
   __shared__ __attribute__((aligned(16))) char lds[C::kLdsBytes];
   char* const kbuf0 = lds;                              // K ring: 4 tiles
   char* const vbuf0 = lds + C::kNBuf * C::kTileBytes;   // V ring: 4 tiles
@@ -1030,7 +1036,7 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
                              uint16_t* __restrict__ out, int32_t B, int32_t M, int32_t H,
                              int32_t sum_L, int32_t n_mt, float c) {
   using C = Cfg<D>;
-  constexpr int NS = 4, MB = 1;                   // waves, 32-beam blocks
+  constexpr int NS = 4, MB = 1;                   // waves; 32-beam blocks
   constexpr int kTileBytes = 32 * C::kRowBytes;
   constexpr int kLoads = kTileBytes / 1024;       // loads per wave, tile and tensor
   constexpr int kWaveBytes = 4 * kTileBytes;      // two buffers of K and V
@@ -1283,7 +1289,14 @@ hipError_t launch_cross_attn(const void* q, const void* enc_k, const void* enc_v
                          (const uint16_t*)enc_v, enc_off, (uint16_t*)out, B, M, H, sum_L, n_ms, c); \
       return hipGetLastError();                                                               \
     }                                                                                         \
-    hipLaunchKernelGGL(cross_attn_bf16_kernel<DD>, dim3((unsigned)grid),                 \
+    const int32_t n_mh = (M + 127) / 128;                                                     \
+    if (DD != 128 && (M <= 128 || (int64_t)B * H * n_mh <= kCus)) {                           \
+      hipLaunchKernelGGL((cross_attn_bf16_kernel<DD, 1>), dim3((unsigned)(B * H * n_mh)),     \
+                         dim3(256), 0, stream, (const uint16_t*)q, (const uint16_t*)enc_k,    \
+                         (const uint16_t*)enc_v, enc_off, (uint16_t*)out, B, M, H, sum_L, n_mh, c); \
+      return hipGetLastError();                                                               \
+    }                                                                                         \
+    hipLaunchKernelGGL((cross_attn_bf16_kernel<DD, Cfg<DD>::kMB>), dim3((unsigned)grid),     \
                        dim3(Cfg<DD>::kThreads), 0, stream, (const uint16_t*)q,               \
                        (const uint16_t*)enc_k, (const uint16_t*)enc_v, enc_off, (uint16_t*)out, \
                        B, M, H, sum_L, n_mt, c);                                              \
