@@ -52,24 +52,36 @@ __device__ __forceinline__ void request_span(const int32_t* off, int32_t b, int3
 // starting at request x*B/8, so that at any time the XCDs read different
 // requests' rows.  All beam tiles of one (request, head) run back to back on
 // one XCD, whose L2 then serves that head's K/V to all of them.
-__device__ __forceinline__ void work_item(uint32_t i, uint32_t n, int32_t n_mt, int32_t B,
-                                          int32_t H, int32_t& mt, int32_t& b, int32_t& h) {
-  constexpr uint32_t kXcds = 8;
-  if (H % kXcds != 0) {
-    const uint32_t tile = xcd_remap(i, n);
-    mt = (int32_t)(tile % (uint32_t)n_mt);
-    const uint32_t bh = tile / (uint32_t)n_mt;
-    h = (int32_t)(bh % (uint32_t)H);
-    b = (int32_t)(bh / (uint32_t)H);
+//
+// The divisors are the launch's own: as plain divisions they took some 1000
+// cycles of every workgroup before its first load.
+struct WorkMap {
+  static constexpr uint32_t kXcds = 8;
+  uint32_t grid, n_mt, H, hpx, B, shift;   // hpx: heads per XCD and request, 0 where H % 8 != 0
+  FastDiv by_mt, by_h, by_b;               // by n_mt, by hpx (H where hpx is 0), by B
+  WorkMap() = default;
+  __host__ WorkMap(int32_t B_, int32_t H_, int32_t n_mt_)
+      : grid((uint32_t)((int64_t)B_ * H_ * n_mt_)), n_mt((uint32_t)n_mt_), H((uint32_t)H_),
+        hpx(H_ % (int32_t)kXcds == 0 ? (uint32_t)H_ / kXcds : 0u), B((uint32_t)B_),
+        shift(((uint32_t)B_ + kXcds - 1) / kXcds), by_mt(n_mt), by_h(hpx ? hpx : H), by_b(B) {}
+};
+
+__device__ __forceinline__ void work_item(uint32_t i, const WorkMap& w, int32_t& mt, int32_t& b,
+                                          int32_t& h) {
+  if (w.hpx == 0) {
+    const uint32_t tile = xcd_remap(i, w.grid);
+    const uint32_t bh = w.by_mt.div(tile);
+    mt = (int32_t)(tile - bh * w.n_mt);
+    b = (int32_t)w.by_h.div(bh);
+    h = (int32_t)(bh - (uint32_t)b * w.H);
     return;
   }
-  const uint32_t x = i % kXcds, k = i / kXcds;
-  const uint32_t hpx = (uint32_t)H / kXcds;            // heads per XCD and request
-  const uint32_t p = k / (uint32_t)n_mt;                // (request, head) pair of this XCD
-  mt = (int32_t)(k % (uint32_t)n_mt);
-  const uint32_t shift = x * (((uint32_t)B + kXcds - 1) / kXcds);
-  b = (int32_t)((p / hpx + shift) % (uint32_t)B);
-  h = (int32_t)((p % hpx) * kXcds + x);
+  const uint32_t x = i % WorkMap::kXcds, k = i / WorkMap::kXcds;
+  const uint32_t p = w.by_mt.div(k);                    // (request, head) pair of this XCD
+  mt = (int32_t)(k - p * w.n_mt);
+  const uint32_t r = w.by_h.div(p), s = r + x * w.shift;
+  b = (int32_t)(s - w.by_b.div(s) * w.B);
+  h = (int32_t)((p - r * w.hpx) * WorkMap::kXcds + x);
 }
 
 // ---------------------------------------------------------------------------
@@ -101,15 +113,15 @@ template <int D, int NS>
 __global__ void __launch_bounds__(kF32Waves * 64, D == 128 ? 1 : 2)
 cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                       const float* __restrict__ v, const int32_t* __restrict__ off,
-                      float* __restrict__ out, int32_t B, int32_t M, int32_t H, int32_t sum_L,
-                      int32_t n_mt, float c) {
+                      float* __restrict__ out, WorkMap map, int32_t M, int32_t H, int32_t sum_L,
+                      float c) {
   constexpr int kGroups = kF32Waves / NS;   // 32-beam groups per workgroup
   constexpr int kJ = D / 8, kDB = D / 32;
   constexpr int kStride = D + 4;            // floats per beam row in LDS
   __shared__ __attribute__((aligned(16))) float o_lds[kF32Waves][32][kStride];
   __shared__ float ml_lds[kF32Waves][2][32];
   int32_t mt, b, h;
-  work_item(blockIdx.x, gridDim.x, n_mt, B, H, mt, b, h);
+  work_item(blockIdx.x, map, mt, b, h);
   int32_t o0, L;
   request_span(off, b, sum_L, o0, L);
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
@@ -424,17 +436,17 @@ template <int D, int MB>
 __global__ void __launch_bounds__(256, 2)
 cross_attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                             const uint16_t* __restrict__ v, const int32_t* __restrict__ off,
-                            uint16_t* __restrict__ out, int32_t B, int32_t M, int32_t H,
-                            int32_t sum_L, int32_t n_mt, float c) {
+                            uint16_t* __restrict__ out, WorkMap map, int32_t M, int32_t H,
+                            int32_t sum_L, float c) {
   using C = Cfg<D, MB>;
   __shared__ __attribute__((aligned(16))) char lds[C::kLdsBytes];
   char* const kbuf0 = lds;                              // K ring: 4 tiles
   char* const vbuf0 = lds + C::kNBuf * C::kTileBytes;   // V ring: 4 tiles
 
   int32_t mt, b, h;
-  work_item(blockIdx.x, gridDim.x, n_mt, B, H, mt, b, h);
+  work_item(blockIdx.x, map, mt, b, h);
   if (threadIdx.x == 0)
-    GRACE_DCHECK(0 <= b && b < B && 0 <= h && h < H && 0 <= mt && mt < n_mt, kDbgRow);
+    GRACE_DCHECK(0 <= b && b < (int32_t)map.B && 0 <= h && h < H && 0 <= mt && mt < (int32_t)map.n_mt, kDbgRow);
   int32_t o0, L;
   request_span(off, b, sum_L, o0, L);
 
@@ -998,7 +1010,7 @@ cross_attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
       const int ch = ln % C::kCPR;
       const u32x4 u = *(const u32x4*)(obuf + C::out_slot(row, ch) * 16);
       const int32_t m = m_base + row;
-      GRACE_DCHECK(b * M + m < B * M || m >= M, kDbgRow);
+      GRACE_DCHECK(b * M + m < (int32_t)map.B * M || m >= M, kDbgRow);
       if (m < M) __builtin_nontemporal_store(u, (u32x4*)(out + (b * M + m) * E + h * D + ch * 8));
     }
   }
@@ -1033,8 +1045,8 @@ template <int D>
 __global__ void __launch_bounds__(256, kSplitPerCu<D>)
 cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                              const uint16_t* __restrict__ v, const int32_t* __restrict__ off,
-                             uint16_t* __restrict__ out, int32_t B, int32_t M, int32_t H,
-                             int32_t sum_L, int32_t n_mt, float c) {
+                             uint16_t* __restrict__ out, WorkMap map, int32_t M, int32_t H,
+                             int32_t sum_L, float c) {
   using C = Cfg<D>;
   constexpr int NS = 4, MB = 1;                   // waves; 32-beam blocks
   constexpr int kTileBytes = 32 * C::kRowBytes;
@@ -1046,7 +1058,7 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
   __shared__ float part_shift[NS][kRows], part_l[NS][kRows];
 
   int32_t mt, b, h;
-  work_item(blockIdx.x, gridDim.x, n_mt, B, H, mt, b, h);
+  work_item(blockIdx.x, map, mt, b, h);
   int32_t o0, L;
   request_span(off, b, sum_L, o0, L);
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
@@ -1253,7 +1265,7 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
     const float inv = l > 0.f ? 1.0f / l : 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] *= inv;
-    GRACE_DCHECK(b * M + m0 + row < B * M, kDbgRow);
+    GRACE_DCHECK(b * M + m0 + row < (int32_t)map.B * M, kDbgRow);
     *(u32x4_a2*)(out + (b * M + m0 + row) * E + h * D + col) = Chunk<BF16>::pack(acc);
   }
 }
@@ -1286,20 +1298,20 @@ hipError_t launch_cross_attn(const void* q, const void* enc_k, const void* enc_v
     if ((int64_t)B * H * n_ms <= kCus * kSplitPerCu<DD>) {                                    \
       hipLaunchKernelGGL(cross_attn_bf16_split_kernel<DD>, dim3((unsigned)(B * H * n_ms)),    \
                          dim3(256), 0, stream, (const uint16_t*)q, (const uint16_t*)enc_k,    \
-                         (const uint16_t*)enc_v, enc_off, (uint16_t*)out, B, M, H, sum_L, n_ms, c); \
+                         (const uint16_t*)enc_v, enc_off, (uint16_t*)out, WorkMap(B, H, n_ms), M, H, sum_L, c); \
       return hipGetLastError();                                                               \
     }                                                                                         \
     const int32_t n_mh = (M + 127) / 128;                                                     \
     if (DD != 128 && (M <= 128 || (int64_t)B * H * n_mh <= kCus)) {                           \
       hipLaunchKernelGGL((cross_attn_bf16_kernel<DD, 1>), dim3((unsigned)(B * H * n_mh)),     \
                          dim3(256), 0, stream, (const uint16_t*)q, (const uint16_t*)enc_k,    \
-                         (const uint16_t*)enc_v, enc_off, (uint16_t*)out, B, M, H, sum_L, n_mh, c); \
+                         (const uint16_t*)enc_v, enc_off, (uint16_t*)out, WorkMap(B, H, n_mh), M, H, sum_L, c); \
       return hipGetLastError();                                                               \
     }                                                                                         \
     hipLaunchKernelGGL((cross_attn_bf16_kernel<DD, Cfg<DD>::kMB>), dim3((unsigned)grid),     \
                        dim3(Cfg<DD>::kThreads), 0, stream, (const uint16_t*)q,               \
                        (const uint16_t*)enc_k, (const uint16_t*)enc_v, enc_off, (uint16_t*)out, \
-                       B, M, H, sum_L, n_mt, c);                                              \
+                       WorkMap(B, H, n_mt), M, H, sum_L, c);                                              \
     return hipGetLastError();                                                                 \
   }
     if (d == 32) GRACE_X(32)
@@ -1316,7 +1328,7 @@ hipError_t launch_cross_attn(const void* q, const void* enc_k, const void* enc_v
 #define GRACE_XN(DD, NS)                                                                          \
   hipLaunchKernelGGL((cross_attn_f32_kernel<DD, NS>), dim3((unsigned)grid), dim3(kF32Waves * 64), \
                      0, stream, (const float*)q, (const float*)enc_k, (const float*)enc_v,        \
-                     enc_off, (float*)out, B, M, H, sum_L, n_mt, c)
+                     enc_off, (float*)out, WorkMap(B, H, n_mt), M, H, sum_L, c)
 #define GRACE_X(DD)              \
   {                              \
     if (ns == 1) GRACE_XN(DD, 1); \
