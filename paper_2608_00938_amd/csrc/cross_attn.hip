@@ -86,21 +86,21 @@ __device__ __forceinline__ void work_item(uint32_t i, const WorkMap& w, int32_t&
 
 // ---------------------------------------------------------------------------
 // fp32 kernel.  Each wave owns 32 beams and computes, per 32-key tile,
-//   S^T = K Q^T       A: lane = key l % 32, dims 8j + 4 (l / 32) + 0..3 of step j
-//                     (one 16-byte load each); B: the same dims of beam l % 32,
-//                     held in registers;
+//   S^T = K Q^T       A: lane = key l % 32, dims 8j + 4 (l / 32) + 0..3 of step j;
+//                     B: the same dims of beam l % 32, held in registers;
 //   P = exp2(c (S^T - m))  with the running maximum m of the beam (lane l % 32
 //                     of both halves), O and the row sum rescaled when it moves;
 //   O^T += V^T P^T    B = P^T as the S^T registers hold it: register 4g + i of
 //                     half hi is key 8g + 4hi + i; A: that key's value, dim l % 32
 //                     of each 32-wide block (one 128-byte row piece per half wave).
-// Bound by the matrix core's fp32 rate (a 32x32x2 product takes 64 cycles for two
-// 256-byte operand registers), so operands come from memory without LDS: 16 KiB
-// per wave and 4096 cycles at d = 64.  A tile's values are loaded before its
-// score products and the next tile's keys before its value products.  8 requests
-// x 250 beams x 8 heads x 64, 33..300 keys: the VALU kernel this replaces, one LDS
-// read per FMA, 89 us, this 19 us; 32 x 1024 x 8 x 64, 512 keys: 1198 and
-// 353 us (97 of the 157 TFLOP/s peak).
+// Bound by the matrix core's fp32 rate (a 32x32x2 product takes 64 cycles) and by
+// the latency of what feeds it.  The values come from memory in operand layout;
+// queries and keys as whole rows, which take operand layout in LDS of the wave's
+// own.  A tile's values are loaded before its score products and the next tile's
+// keys before its value products.  GPU time, 8 x 250 x 8 x 64 with 33..300 keys:
+// the VALU kernel this replaces, one LDS read per FMA, 104 us; this with keys
+// straight from memory 22.4, keys through LDS 19.8, queries too 18.7.  32 x 1024 x 8
+// x 64, 512 keys: 1198, 377, 332, 335 us (103 of the 157 TFLOP/s peak).
 //
 // NS waves share 32 beams, wave s taking the key tiles s, s + NS, ...; their
 // partial results meet in LDS.
@@ -108,6 +108,15 @@ __device__ __forceinline__ void work_item(uint32_t i, const WorkMap& w, int32_t&
 constexpr int kF32Waves = 4;
 // four floats in memory, which need not lie on a 16-byte boundary
 typedef f32x4 __attribute__((aligned(4))) f32x4_a4;
+
+// Orders a wave's own LDS writes before its later reads of them by other lanes
+// (and reads before later writes): the wave's LDS operations run in order, so
+// only the compiler has to be told.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 template <int D, int NS>
 __global__ void __launch_bounds__(kF32Waves * 64, D == 128 ? 1 : 2)
@@ -117,7 +126,8 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                       float c) {
   constexpr int kGroups = kF32Waves / NS;   // 32-beam groups per workgroup
   constexpr int kJ = D / 8, kDB = D / 32;
-  constexpr int kStride = D + 4;            // floats per beam row in LDS
+  constexpr int kStride = D + 4;            // floats per row in LDS: keys, then results
+  constexpr int kLanesPerRow = D / 4, kRowsPerPass = 64 / kLanesPerRow;
   __shared__ __attribute__((aligned(16))) float o_lds[kF32Waves][32][kStride];
   __shared__ float ml_lds[kF32Waves][2][32];
   int32_t mt, b, h;
@@ -131,7 +141,7 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
   const bool active = m0 < M;
   const int64_t E = (int64_t)H * D;
   const int32_t n = (L + 31) / 32;
-  const float* const kh = k + (int64_t)o0 * E + h * D + 4 * hi;   // + key * E + 8 j
+  const float* const kh = k + (int64_t)o0 * E + h * D;            // + key * E + dim
   const float* const vh = v + (int64_t)o0 * E + h * D;            // + key * E + 32 db + l32
 
   f32x16 o[kDB];
@@ -141,20 +151,36 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
     for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   if (active && split < n) {
-    const int32_t m = min(m0 + l32, M - 1);   // beams past M repeat the last, never stored
-    f32x4 qf[kJ], kf[kJ];
-    const float* const qrow = q + ((int64_t)b * M + m) * E + h * D + 4 * hi;
+    // Rows come from memory whole, kLanesPerRow lanes each, and take operand
+    // layout in this wave's rows of LDS: an operand load straight from memory (32
+    // bytes of each of 32 rows) occupies the address path for some 64 cycles.
+    f32x4 qf[kJ], kraw[kJ];
+    auto to_lds = [&](const f32x4 (&raw)[kJ]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < kJ; ++j) qf[j] = *(const f32x4_a4*)(qrow + 8 * j);
+      for (int i = 0; i < kJ; ++i)
+        *(f32x4*)&o_lds[wave][i * kRowsPerPass + lane / kLanesPerRow][4 * (lane % kLanesPerRow)] = raw[i];
+      wave_sync();
+    };
+#pragma unroll
+    for (int i = 0; i < kJ; ++i) {
+      // beams past M repeat the last, never stored
+      const int32_t m = min(m0 + i * kRowsPerPass + lane / kLanesPerRow, M - 1);
+      qf[i] = *(const f32x4_a4*)(q + ((int64_t)b * M + m) * E + h * D + 4 * (lane % kLanesPerRow));
+    }
     // keys past L repeat the last and get weight 0
     auto load_k = [&](int32_t t) __attribute__((always_inline)) {
-      const int32_t key = min(t * 32 + l32, L - 1);
-      GRACE_DCHECK(o0 + key < sum_L, kDbgRow);
-      const float* const row = kh + (int64_t)key * E;
 #pragma unroll
-      for (int j = 0; j < kJ; ++j) kf[j] = *(const f32x4_a4*)(row + 8 * j);
+      for (int i = 0; i < kJ; ++i) {
+        const int32_t key = min(t * 32 + i * kRowsPerPass + lane / kLanesPerRow, L - 1);
+        GRACE_DCHECK(o0 + key < sum_L, kDbgRow);
+        kraw[i] = *(const f32x4_a4*)(kh + (int64_t)key * E + 4 * (lane % kLanesPerRow));
+      }
     };
     load_k(split);
+    to_lds(qf);
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) qf[j] = *(const f32x4*)&o_lds[wave][l32][8 * j + 4 * hi];
+    wave_sync();
     for (int32_t t = split; t < n; t += NS) {
       const int32_t t0 = t * 32;
       float vf[16][kDB];
@@ -175,16 +201,19 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
           for (int db = 0; db < kDB; ++db) vf[r][db] = row[32 * db];
         }
       }
+      to_lds(kraw);
       // two chains of products
       f32x16 s0 = {}, s1 = {};
 #pragma unroll
       for (int j = 0; j < kJ; ++j) {
+        const f32x4 kf = *(const f32x4*)&o_lds[wave][l32][8 * j + 4 * hi];
 #pragma unroll
         for (int e = 0; e < 4; e += 2) {
-          s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e + 1], qf[j][e + 1], s1, 0, 0, 0);
+          s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[j][e], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e + 1], qf[j][e + 1], s1, 0, 0, 0);
         }
       }
+      wave_sync();
       if (t + NS < n) load_k(t + NS);
       float mx = -INFINITY;
 #pragma unroll
@@ -237,7 +266,6 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
   }
   __syncthreads();
   // the group's NS waves share out its 32 rows
-  constexpr int kLanesPerRow = D / 4, kRowsPerPass = 64 / kLanesPerRow;
   constexpr int kRows = 32 / NS;
 #pragma unroll
   for (int i = 0; i < kRows / kRowsPerPass; ++i) {
@@ -1021,12 +1049,13 @@ cross_attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 // split the keys, wave s taking the 32-key tiles s, s + 4, ...  Bound by latency:
 // with 256-beam tiles a few requests leave most CUs idle and each workgroup a
 // serial chain of all the key tiles; here there are 4 to 8 times the workgroups
-// and a quarter of the chain.  8 requests x 256 beams x 8 heads x 64: 8.8 -> 6.6 us
-// at 256 keys, 20.8 -> 12.8 at 1024; 1 x 100 x 8 x 64, 256 keys: 7.8 -> 4.7 (64 beams
-// per workgroup instead of 32: 6.9, 13.3 and 6.5).  Each wave streams its own tiles into LDS of its own (two
-// buffers, no barrier before the end) and runs the safe pass of the kernel above
-// step by step: the same products, the same exponent shift, which stays at zero
-// for ordinary scores.  The waves' partial O and row sums meet in LDS in fp32.
+// and a quarter of the chain.  8 requests x 256 beams x 8 heads x 64: 8.8 -> 6.1 us
+// at 256 keys, 20.8 -> 12.5 at 1024 (6.7 and 13.3 with the queries loaded in
+// operand layout instead of whole rows; 64 beams per workgroup: 6.9 and 13.3).
+// Each wave streams its own tiles into LDS of its own (two buffers, no barrier
+// before the end) and runs the safe pass of the kernel above step by step: the
+// same products, the same exponent shift, which stays at zero for ordinary
+// scores.  The waves' partial O and row sums meet in LDS in fp32.
 // ---------------------------------------------------------------------------
 template <int N>
 __device__ __forceinline__ void wait_vmem() {
@@ -1068,18 +1097,7 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
   const int32_t n = (L + 31) / 32;
   char* const mine = lds + wave * kWaveBytes;
 
-  // queries (B of S^T): 8 consecutive d of beam l32 of block mb per 16-wide step
   typedef u32x4 __attribute__((aligned(2))) u32x4_a2;
-  bf16x8 qf[MB][C::kKS];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int32_t m = min(m0 + mb * 32 + l32, M - 1);   // beams past M repeat the last, never stored
-    const uint16_t* const row = q + (b * M + m) * E + h * D + 8 * hi;
-#pragma unroll
-    for (int ks = 0; ks < C::kKS; ++ks)
-      qf[mb][ks] = __builtin_bit_cast(bf16x8, *(const u32x4_a2*)(row + 16 * ks));
-  }
-
   // tile t of K and V into buffer buf of this wave
   uint32_t dma_off[kLoads];
 #pragma unroll
@@ -1103,6 +1121,32 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
       load_to_lds(vt, o, dst + kTileBytes + i * 1024);
     }
   };
+
+  // Queries as whole rows into the K part of buffer 1 (the second tile's, issued
+  // after they are read), then the first tile.  B of S^T: 8 consecutive d of beam
+  // l32 per 16-wide step; beams past M repeat the last, never stored.
+  static_assert(MB == 1, "32 query rows fill one K tile");
+  {
+    const uint16_t* const qbase = q + __builtin_amdgcn_readfirstlane((b * M + m0) * E + h * D);
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int sl = i * 64 + lane, row = sl / C::kCPR;
+      const int chunk = (sl % C::kCPR) ^ tile_swizzle<D>(row);
+      load_to_lds<true>(qbase, (uint32_t)(min(row, M - 1 - m0) * E + chunk * 8) * 2u,
+                        lds0 + 2 * kTileBytes + i * 1024);
+    }
+  }
+  if (wave < n) {
+    issue(wave, 0);
+    wait_vmem<2 * kLoads>();   // the queries have landed
+  } else {
+    wait_vmem<0>();
+  }
+  bf16x8 qf[MB][C::kKS];
+#pragma unroll
+  for (int ks = 0; ks < C::kKS; ++ks)
+    qf[0][ks] = __builtin_bit_cast(
+        bf16x8, *(const u32x4*)(mine + 2 * kTileBytes + C::slot(l32, 2 * ks + hi) * 16));
 
   bf16x8 sum_a[MB];   // row-sum operands, as in the kernel above
 #pragma unroll
@@ -1138,7 +1182,6 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
       for (int r = 0; r < 16; ++r) o[db][mb][r] = 0.f;
   }
 
-  if (wave < n) issue(wave, 0);
   for (int32_t t = wave, buf = 0; t < n; t += NS, buf ^= 1) {
     // the buffer filled next was read a tile ago: those reads are complete
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
