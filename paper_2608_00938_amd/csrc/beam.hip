@@ -111,7 +111,7 @@ constexpr int kGatherCap = 8192;   // gathered candidates a request can rank
 // Workspace of one call.  Per request: the gathered list [kGatherCap] of
 // composites, S sample areas of kSampleArea fp16 (the last one doubles as the
 // select workgroups' common histogram), info [kInfo] = {threshold (float bits),
-// gathered count, unused, select workgroups done, unused...}.  S grows with the
+// gathered count, unused, workgroups done, unused...}.  S grows with the
 // candidates of a request, one area per 32768 up to 64.
 constexpr int kMaxSlices = 64;
 constexpr uint32_t kSliceTarget = 32768;
@@ -148,12 +148,12 @@ struct TopkWs {
   }
 };
 
-// Clears what the select workgroups of a request share (the score pass does it
-// where there is one).
+// Clears what several workgroups of a request's selection share (the score pass
+// does it where there is one).
 __device__ __forceinline__ void clear_shared(const TopkWs& ws, int64_t b, uint32_t first, uint32_t step) {
   uint32_t* sum = ws.hist(b);
   for (uint32_t i = first; i < (uint32_t)kHistBins; i += step) sum[i] = 0u;
-  if (first == 0) ws.info[b * kInfo + 3] = 0;
+  if (first == 0) ws.info[b * kInfo + 1] = ws.info[b * kInfo + 3] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -171,8 +171,7 @@ constexpr int kScoreThreads = 256;
 struct SampleOut {
   uint16_t* p = nullptr;     // [B][stride], request b's rows in order; null: no sample
   int64_t stride = 0;
-  bool clear = false;        // also clear what the select workgroups share
-  TopkWs ws;
+  TopkWs ws;                 // what the selection's workgroups share is cleared too
   uint32_t per_row = 0;
   int32_t lp = 0, M = 1;
   FastDiv per_request{1};    // row -> request
@@ -246,7 +245,7 @@ beam_scores_kernel(const T* __restrict__ logits, const float* __restrict__ prev,
       out[i] = (uint16_t)pack_f16x2(v < (uint32_t)V ? score((int)v) - ref : -INFINITY, 0.f);
     }
     if (m == (uint32_t)smp.M - 1 && lane < 3) out[smp.per_row + lane] = 0xfc00u;
-    if (smp.clear) clear_shared(smp.ws, b, m * 64 + lane, (uint32_t)smp.M * 64);
+    clear_shared(smp.ws, b, m * 64 + lane, (uint32_t)smp.M * 64);
   }
 }
 
@@ -425,7 +424,7 @@ beam_scores_reg_kernel(const T* __restrict__ logits, const float* __restrict__ p
       const uint32_t h = sample_offset(m, smp.lp);
       uint16_t* out = smp.p + b * smp.stride + (int64_t)m * smp.per_row;
       if (m == (uint32_t)smp.M - 1 && lane < 3) out[smp.per_row + lane] = 0xfc00u;
-    if (smp.clear) clear_shared(smp.ws, b, m * 64 + lane, (uint32_t)smp.M * 64);
+    clear_shared(smp.ws, b, m * 64 + lane, (uint32_t)smp.M * 64);
       if constexpr (RUN) {
         // one element of every 2^(lp-3)-th run; the RPW rows of a wave share
         // out the eight elements, so that two (four, eight) remain to pick from
@@ -1179,26 +1178,21 @@ struct ChunkSample {
 constexpr float kBelow = 112.0f, kAbove = 16.0f;
 constexpr uint32_t kSelectSamples = 16384;
 
-template <class Smp>
-__global__ void __launch_bounds__(kTopkThreads)
-topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
-  __shared__ uint32_t hist[kHistBins];
-  __shared__ uint32_t scan[64];
-  __shared__ float fscan[kTopkThreads / 64];
-  __shared__ int32_t ipar[2];
+constexpr float kSelectInvW = (float)kHistBins / (kBelow + kAbove);
+
+// hist: the counts of samples j0 .. j0 + kSelectSamples - 1 in the bins from the
+// want-th best of the threads' own best samples up.
+template <class Row>
+__device__ __forceinline__ void sample_hist(const Row& sample, uint32_t j0, float ref, uint32_t want,
+                                            uint32_t* hist, uint32_t* scan, int32_t* ipar) {
   constexpr int U = kSelectSamples / (4 * kTopkThreads);   // loads of four samples per thread
-  constexpr float kInvW = (float)kHistBins / (kBelow + kAbove);
   const int tid = threadIdx.x;
-  const int64_t b = blockIdx.y;
-  const auto sample = smp.request(b, N);
-  const float ref = smp.ref(sample, b, fscan);
   float x[U][4];
   float mx = -INFINITY;
   {
     u32x2 w[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      w[u] = sample.load4(blockIdx.x * kSelectSamples + 4 * (u * kTopkThreads + tid), ref);
+    for (int u = 0; u < U; ++u) w[u] = sample.load4(j0 + 4 * (u * kTopkThreads + tid), ref);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const f16x2 lo = __builtin_bit_cast(f16x2, w[u].x), hi = __builtin_bit_cast(f16x2, w[u].y);
@@ -1212,7 +1206,7 @@ topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
   }
   clear_bins(hist);
   __syncthreads();
-  const int own = step_bin(mx, -kBelow, kInvW);
+  const int own = step_bin(mx, -kBelow, kSelectInvW);
   if (own > 0) atomicAdd(&hist[own], 1u);
   __syncthreads();
   const int first = max(1, boundary_bin(hist, want, scan, ipar));   // 1: the whole window
@@ -1223,11 +1217,29 @@ topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int bin = step_bin(x[u][e], -kBelow, kInvW);
+        const int bin = step_bin(x[u][e], -kBelow, kSelectInvW);
         if (bin >= first) atomicAdd(&hist[bin], 1u);
       }
   }
   __syncthreads();
+}
+// about the bin's lower edge
+__device__ __forceinline__ float bin_threshold(int bin, float ref) {
+  return bin > 0 ? ref + ((float)bin / kSelectInvW - kBelow) : -FLT_MAX;
+}
+
+template <class Smp>
+__global__ void __launch_bounds__(kTopkThreads)
+topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
+  __shared__ uint32_t hist[kHistBins];
+  __shared__ uint32_t scan[64];
+  __shared__ float fscan[kTopkThreads / 64];
+  __shared__ int32_t ipar[2];
+  const int tid = threadIdx.x;
+  const int64_t b = blockIdx.y;
+  const auto sample = smp.request(b, N);
+  const float ref = smp.ref(sample, b, fscan);
+  sample_hist(sample, blockIdx.x * kSelectSamples, ref, want, hist, scan, ipar);
   int32_t* info = ws.info + b * kInfo;
   if (gridDim.x > 1) {
     // every workgroup's bins from the request's threshold up are complete, as
@@ -1252,8 +1264,7 @@ topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
   }
   const int bin = boundary_bin(hist, want, scan, ipar);
   if (tid == 0) {
-    // about the bin's lower edge
-    info[0] = __float_as_int(bin > 0 ? ref + ((float)bin / kInvW - kBelow) : -FLT_MAX);
+    info[0] = __float_as_int(bin_threshold(bin, ref));
     info[1] = 0;   // gathered count
   }
 }
@@ -1265,41 +1276,53 @@ __global__ void __launch_bounds__(kTopkThreads) topk_clear_kernel(TopkWs ws) {
 constexpr int kGatherThreads = 256;
 constexpr int kStage = 1024;   // LDS entries of a gather workgroup
 
+// Into a request's gathered list; SHARED: other workgroups of this launch read it.
+template <bool SHARED>
+__device__ __forceinline__ void put_list(uint64_t* at, uint64_t v) {
+  if constexpr (SHARED)
+    (void)__hip_atomic_exchange(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *at = v;
+}
+
 // A workgroup's staged candidates: flushed with one global atomic (same-address
 // global atomics serialise); what does not fit the stage goes to the list directly.
+template <int STAGE>
 struct GatherStage {
-  uint64_t entry[kStage];
+  uint64_t entry[STAGE];
   uint32_t n, base;
 };
+template <int STAGE, bool SHARED = false>
 struct PutStage {
-  GatherStage& st;
+  GatherStage<STAGE>& st;
   uint64_t* list;
   uint32_t* count;
   uint32_t pos = 0, direct = 0;
   __device__ __forceinline__ void reserve(uint32_t n) {
     pos = atomicAdd(&st.n, n);
-    const uint32_t first = max(pos, (uint32_t)kStage);
+    const uint32_t first = max(pos, (uint32_t)STAGE);
     if (pos + n > first) direct = atomicAdd(count, pos + n - first);
   }
   __device__ __forceinline__ void operator()(uint64_t v) {
-    if (pos < (uint32_t)kStage) {
+    if (pos < (uint32_t)STAGE) {
       st.entry[pos] = v;
     } else {
-      if (direct < (uint32_t)kGatherCap) list[direct] = v;
+      if (direct < (uint32_t)kGatherCap) put_list<SHARED>(list + direct, v);
       ++direct;
     }
     ++pos;
   }
 };
-__device__ __forceinline__ void gather_flush(GatherStage& st, uint64_t* list, uint32_t* count) {
+template <int THREADS, bool SHARED = false, int STAGE>
+__device__ __forceinline__ void gather_flush(GatherStage<STAGE>& st, uint64_t* list, uint32_t* count) {
   __syncthreads();
-  const uint32_t n = min(st.n, (uint32_t)kStage);
+  const uint32_t n = min(st.n, (uint32_t)STAGE);
   if (n == 0) return;   // whole workgroup
   if (threadIdx.x == 0) st.base = atomicAdd(count, n);
   __syncthreads();
   const uint32_t b0 = st.base;
-  for (uint32_t j = threadIdx.x; j < n; j += kGatherThreads)
-    if (b0 + j < (uint32_t)kGatherCap) list[b0 + j] = st.entry[j];
+  for (uint32_t j = threadIdx.x; j < n; j += THREADS)
+    if (b0 + j < (uint32_t)kGatherCap) put_list<SHARED>(list + b0 + j, st.entry[j]);
 }
 
 // Gather over a written candidate array (16 x 1000 x 509 fp32, 33 MB: 31 -> 12
@@ -1310,7 +1333,7 @@ __device__ __forceinline__ void gather_flush(GatherStage& st, uint64_t* list, ui
 template <bool VEC>
 __global__ void __launch_bounds__(kGatherThreads)
 topk_gather_array_kernel(CandArray src, uint32_t N, uint32_t per, TopkWs ws) {
-  __shared__ GatherStage st;
+  __shared__ GatherStage<kStage> st;
   const int64_t b = blockIdx.y;
   const int32_t* info = ws.info + b * kInfo;
   const float thr = __int_as_float(info[0]);
@@ -1334,7 +1357,7 @@ topk_gather_array_kernel(CandArray src, uint32_t N, uint32_t per, TopkWs ws) {
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         for_hits<4>(x[u], (uint32_t)(j0 + 4 * (u * kGatherThreads + threadIdx.x)), thr,
-                    PutStage{st, list, count});
+                    PutStage<kStage>{st, list, count});
     }
   } else {
     for (uint64_t j0 = i0; j0 < i1; j0 += 8 * kGatherThreads) {
@@ -1347,10 +1370,10 @@ topk_gather_array_kernel(CandArray src, uint32_t N, uint32_t per, TopkWs ws) {
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         for_hits<1>(x[u], (uint32_t)(j0 + u * kGatherThreads + threadIdx.x), thr,
-                    PutStage{st, list, count});
+                    PutStage<kStage>{st, list, count});
     }
   }
-  gather_flush(st, list, count);
+  gather_flush<kGatherThreads>(st, list, count);
 }
 
 // Gather over candidates recomputed from the logits.  A wave takes up to 64
@@ -1363,35 +1386,25 @@ topk_gather_array_kernel(CandArray src, uint32_t N, uint32_t per, TopkWs ws) {
 // 512: reading every row 136 us, these rows 51, with the queue 27).
 constexpr int kQueue = 2048;
 
-template <class T, bool RUN>
-__global__ void __launch_bounds__(kGatherThreads)
-topk_gather_rows_kernel(CandFromLogits<T> src, const float* __restrict__ row_max, int32_t rows_per_wave,
-                        int32_t ll, uint32_t N, TopkWs ws) {
-  constexpr int kWaves = kGatherThreads / 64, E = RUN ? 8 : 1, U = 4;
-  __shared__ GatherStage st;
-  __shared__ uint32_t queue[RUN ? kQueue : 1];
-  __shared__ uint32_t n_queue;
-  __shared__ uint8_t rows[kWaves][64];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t b = blockIdx.y;
-  const int32_t* info = ws.info + b * kInfo;
-  const int64_t m0 = ((int64_t)blockIdx.x * kWaves + wave) * rows_per_wave;
-  const float bound = lane < rows_per_wave && m0 + lane < src.M ? row_max[b * src.M + m0 + lane] : -INFINITY;
-  const float thr = __int_as_float(info[0]);
-  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
-  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 1];
+// rows: 64 bytes of LDS of the wave's own; m0, bound: the wave's first row, the
+// lane's row's upper bound.  Ends without a barrier, st ready to be flushed.
+template <bool RUN, int THREADS, int QUEUE, bool SHARED, int STAGE, class Row>
+__device__ __forceinline__ void gather_rows(const Row& c, int64_t m0, float bound, float thr, int32_t ll,
+                                            GatherStage<STAGE>& st, uint32_t* queue, uint32_t& n_queue,
+                                            uint8_t* rows, uint64_t* list, uint32_t* count) {
+  constexpr int E = RUN ? 8 : 1, U = 4;
+  const int lane = threadIdx.x & 63;
   if (threadIdx.x == 0) st.n = n_queue = 0u;
   const uint64_t act = __ballot(bound >= thr);
-  if (bound >= thr) rows[wave][__popcll(act & ((1ull << lane) - 1ull))] = (uint8_t)lane;
+  if (bound >= thr) rows[__popcll(act & ((1ull << lane) - 1ull))] = (uint8_t)lane;
   __syncthreads();
   const int n_act = (int)__popcll(act);
-  const auto c = src.request(b, N);
-  const int32_t V = src.V;
+  const int32_t V = c.V;
   const int lpr = 1 << ll, rpp = 64 >> ll;             // lanes per row, rows per piece
   const int sub = lane >> ll, sl = lane & (lpr - 1);
   int idx0 = 0, v0 = 0;   // the next piece: first row (index into rows), first token
   while (idx0 < n_act) {
-    typename CandFromLogits<T>::Row::template Raw<E> raw[U];
+    typename Row::template Raw<E> raw[U];
     uint32_t at[U], m[U];
     bool live[U];
 #pragma unroll
@@ -1399,7 +1412,7 @@ topk_gather_rows_kernel(CandFromLogits<T> src, const float* __restrict__ row_max
       const int idx = idx0 + sub, v = v0 + sl * E;
       live[u] = idx < n_act && v < V;
       if (live[u]) {
-        m[u] = (uint32_t)m0 + rows[wave][idx];
+        m[u] = (uint32_t)m0 + rows[idx];
         at[u] = m[u] * (uint32_t)V + (uint32_t)v;
         c.template load_raw<E>(at[u], m[u], raw[u]);
       }
@@ -1424,56 +1437,141 @@ topk_gather_rows_kernel(CandFromLogits<T> src, const float* __restrict__ row_max
       if (!(raw[u].p + (top - raw[u].l) >= thr)) continue;
       if constexpr (RUN) {
         const uint32_t pos = atomicAdd(&n_queue, 1u);
-        if (pos < (uint32_t)kQueue) {
+        if (pos < (uint32_t)QUEUE) {
           queue[pos] = at[u];
           continue;
         }
       }
       float x[E];
       c.template finish<E>(at[u], m[u], raw[u], x);
-      for_hits<E>(x, at[u], thr, PutStage{st, list, count});
+      for_hits<E>(x, at[u], thr, PutStage<STAGE, SHARED>{st, list, count});
     }
   }
   if constexpr (RUN) {
     __syncthreads();
-    const uint32_t n = min(n_queue, (uint32_t)kQueue);
-    for (uint32_t j = threadIdx.x; j < n; j += kGatherThreads) {
+    const uint32_t n = min(n_queue, (uint32_t)QUEUE);
+    for (uint32_t j = threadIdx.x; j < n; j += THREADS) {
       float x[8];
       c.load8(queue[j], x);
-      for_hits<8>(x, queue[j], thr, PutStage{st, list, count});
+      for_hits<8>(x, queue[j], thr, PutStage<STAGE, SHARED>{st, list, count});
     }
   }
-  gather_flush(st, list, count);
 }
 
-// Final selection: rank the gathered candidates, or the exact selection over
-// all the request's candidates.
-template <class Src, bool VEC8>
-__global__ void __launch_bounds__(kTopkThreads)
-topk_final_kernel(Src src, uint32_t N, int32_t k, TopkWs ws, TopkOut out) {
-  __shared__ TopkShared sh;
-  constexpr int kPer = kGatherCap / kTopkThreads;
-  const int tid = threadIdx.x;
-  const int64_t b = blockIdx.x, out0 = b * k;
-  const auto c = src.request(b, N);
+template <class T, bool RUN>
+__global__ void __launch_bounds__(kGatherThreads)
+topk_gather_rows_kernel(CandFromLogits<T> src, const float* __restrict__ row_max, int32_t rows_per_wave,
+                        int32_t ll, uint32_t N, TopkWs ws) {
+  constexpr int kWaves = kGatherThreads / 64;
+  __shared__ GatherStage<kStage> st;
+  __shared__ uint32_t queue[RUN ? kQueue : 1];
+  __shared__ uint32_t n_queue;
+  __shared__ uint8_t rows[kWaves][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t b = blockIdx.y;
   const int32_t* info = ws.info + b * kInfo;
+  const int64_t m0 = ((int64_t)blockIdx.x * kWaves + wave) * rows_per_wave;
+  const float bound = lane < rows_per_wave && m0 + lane < src.M ? row_max[b * src.M + m0 + lane] : -INFINITY;
   const float thr = __int_as_float(info[0]);
-  const uint32_t n = (uint32_t)info[1];
+  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
+  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 1];
+  gather_rows<RUN, kGatherThreads, kQueue, false>(src.request(b, N), m0, bound, thr, ll, st, queue, n_queue,
+                                                  rows[wave], list, count);
+  gather_flush<kGatherThreads>(st, list, count);
+}
+
+// Final selection: rank the n gathered candidates at or above thr (entry(i) reads
+// the list), or the exact selection over all the request's candidates.
+template <bool VEC8, class Row, class Entry>
+__device__ __forceinline__ void final_select(TopkShared& sh, float thr, uint32_t n, uint32_t N, int32_t k,
+                                             int64_t out0, const Row& c, const TopkOut& out, Entry entry) {
+  constexpr int kPer = kGatherCap / kTopkThreads;
   // all candidates at or above thr are in the list; it holds the k best when
   // they are at least k, or when they are all there are above -inf
   if (n <= (uint32_t)kGatherCap && (n >= (uint32_t)k || thr == -FLT_MAX)) {
-    const uint64_t* list = ws.list + b * (int64_t)kGatherCap;
     uint64_t v[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const uint32_t i = (uint32_t)(tid + j * kTopkThreads);
-      v[j] = i < n ? list[i] : 0ull;
+      const uint32_t i = (uint32_t)(threadIdx.x + j * kTopkThreads);
+      v[j] = i < n ? entry(i) : 0ull;
     }
     rank_and_emit(sh, v, n, k, out0, c, out);
     if (n < (uint32_t)k) fill_dead<VEC8>(sh, n, k, N, out0, c, out);
     return;
   }
   exact_select<VEC8>(sh, k, N, out0, c, out);
+}
+
+template <class Src, bool VEC8>
+__global__ void __launch_bounds__(kTopkThreads)
+topk_final_kernel(Src src, uint32_t N, int32_t k, TopkWs ws, TopkOut out) {
+  __shared__ TopkShared sh;
+  const int64_t b = blockIdx.x;
+  const int32_t* info = ws.info + b * kInfo;
+  const uint64_t* list = ws.list + b * (int64_t)kGatherCap;
+  final_select<VEC8>(sh, __int_as_float(info[0]), (uint32_t)info[1], N, k, b * k, src.request(b, N), out,
+                     [=](uint32_t i) { return list[i]; });
+}
+
+// Select, gather and final in one launch, for few rows: bound by the latency of
+// each stage's chain and by the launches between them.  Every workgroup derives the
+// threshold from the whole sample (at most kSelectSamples, 32 KiB), gathers its
+// rows, one per wave, and the last of a request to finish ranks the list.  12 x 300
+// x 500 tokens, k = 1000: score pass and selection 33.7 us with three launches of
+// the selection, 26.2 with one; 8 x 512 x 1024, k = 1024: 30.7 and 26.0; 1 x 300 x 509,
+// k = 100: 23.3 and 22.6; 1 x 16 x 20000, k = 50: 110 and 95.
+// Only where the workgroups (one fits a CU, by its LDS) all run at once: with two
+// rows per wave 16 x 1000 x 509, k = 1000 took 39.5 against 37.5.  And up to 32 of
+// them per request, which all read its sample: 1 x 1024 x 512 25.9 against 25.6, 2 x
+// 2048 x 512 26.7 against 26.6.
+constexpr int kFusedStage = 4096, kFusedQueue = 4096;
+constexpr uint32_t kFusedRows = kTopkThreads / 64;     // beam rows per workgroup, one per wave
+constexpr uint32_t kFusedMaxPerRequest = 32, kFusedMaxBlocks = 256;
+
+template <class T, bool RUN>
+__global__ void __launch_bounds__(kTopkThreads)
+topk_fused_rows_kernel(CandFromLogits<T> src, StoredSample smp, const float* __restrict__ row_max,
+                       int32_t ll, uint32_t N, uint32_t want, int32_t k, TopkWs ws, TopkOut out) {
+  constexpr int kWaves = kTopkThreads / 64;
+  __shared__ TopkShared sh;
+  __shared__ uint32_t n_queue;
+  __shared__ uint8_t rows[kWaves][64];
+  typedef GatherStage<kFusedStage> Stage;
+  static_assert(sizeof(Stage) + kFusedQueue * sizeof(uint32_t) <= sizeof(sh.list), "in the ranking's list");
+  Stage& st = *(Stage*)sh.list;
+  uint32_t* const queue = (uint32_t*)((char*)sh.list + sizeof(Stage));
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t b = blockIdx.y;
+  const int64_t m0 = (int64_t)blockIdx.x * kWaves + wave;
+  const float bound = lane == 0 && m0 < src.M ? row_max[b * src.M + m0] : -INFINITY;
+  const auto sample = smp.request(b, N);
+  const float ref = smp.ref(sample, b, nullptr);
+  sample_hist(sample, 0, ref, want, sh.bin_count, sh.scan, sh.ipar);
+  const float thr = bin_threshold(boundary_bin(sh.bin_count, want, sh.scan, sh.ipar), ref);
+  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
+  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 1];
+  const auto c = src.request(b, N);
+  gather_rows<RUN, kTopkThreads, kFusedQueue, true>(c, m0, bound, thr, ll, st, queue, n_queue, rows[wave],
+                                                    list, count);
+  gather_flush<kTopkThreads, true>(st, list, count);
+  // the list and its count see device-scope read-modify-writes only, as the
+  // select workgroups' counts do
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    const int32_t done = __hip_atomic_fetch_add(&ws.info[b * kInfo + 3], 1, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+    sh.ipar[0] = done;
+    if (done == (int32_t)gridDim.x - 1)
+      sh.ipar[1] = (int32_t)__hip_atomic_fetch_add(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (sh.ipar[0] != (int32_t)gridDim.x - 1) return;   // whole workgroup
+  const uint32_t n = (uint32_t)sh.ipar[1];
+  __syncthreads();
+  final_select<RUN>(sh, thr, n, N, k, b * k, c, out, [=](uint32_t i) {
+    return __hip_atomic_fetch_add(list + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  });
 }
 
 // The score kernels; with CAND = false they write lse_out, the rows' upper
@@ -1648,21 +1746,28 @@ static hipError_t launch_step(const void* logits, const float* prev, const uint3
   for (int lp = 3; lp <= 9 && V >= (1 << lp); ++lp) {
     const uint64_t per_row = ((uint64_t)V + (1u << lp) - 1) >> lp, n = per_row * M;
     if (n + 3 > (uint64_t)ws.sample_room()) continue;
-    smp = SampleOut{ws.sample, ws.sample_stride(), select_blocks((uint32_t)n) > 1, ws, (uint32_t)per_row, lp,
+    smp = SampleOut{ws.sample, ws.sample_stride(), ws, (uint32_t)per_row, lp,
                     M, FastDiv((uint32_t)M)};
     if (n <= kSelectSamples || (n <= kSampleTarget && !sample_suffices(k, lp + 1))) break;
   }
-  launch_scores_mode<false>(logits, prev, mask, nullptr, row_max, lse, R, V, bf16, smp, stream);
-  if (smp.p != nullptr)
-    launch_select(StoredSample{smp.p, smp.stride, smp.per_row * (uint32_t)M, prev, M}, B, N, k, smp.lp, ws,
-                  stream);
-  else
-    launch_select_chunks(src, B, N, k, ws, stream);
-  // lanes per row: as many as its runs (tokens) need, at most a wave; rows per
-  // wave: up to 64, fewer while that leaves the chip without waves
+  // lanes per row: as many as its runs (tokens) need, at most a wave
   constexpr int E = RUN ? 8 : 1;
   int ll = 0;
   while (ll < 6 && (E << ll) < V) ++ll;
+  launch_scores_mode<false>(logits, prev, mask, nullptr, row_max, lse, R, V, bf16, smp, stream);
+  const StoredSample stored{smp.p, smp.stride, smp.per_row * (uint32_t)M, prev, M};
+  const uint32_t fused_blocks = ((uint32_t)M + kFusedRows - 1) / kFusedRows;
+  if (smp.p != nullptr && stored.n <= kSelectSamples && fused_blocks <= kFusedMaxPerRequest &&
+      fused_blocks * (uint32_t)B <= kFusedMaxBlocks) {
+    hipLaunchKernelGGL((topk_fused_rows_kernel<T, RUN>), dim3(fused_blocks, (unsigned)B), dim3(kTopkThreads),
+                       0, stream, src, stored, row_max, ll, N, samples_wanted(k, smp.lp), k, ws, out);
+    return hipGetLastError();
+  }
+  if (smp.p != nullptr)
+    launch_select(stored, B, N, k, smp.lp, ws, stream);
+  else
+    launch_select_chunks(src, B, N, k, ws, stream);
+  // rows per wave: up to 64, fewer while that leaves the chip without waves
   int32_t rpw = 64;
   while (rpw > 4 && (int64_t)B * ((M + rpw - 1) / rpw) < 8192) rpw >>= 1;
   const int32_t per_block = rpw * (kGatherThreads / 64);

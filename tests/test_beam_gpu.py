@@ -191,6 +191,12 @@ SELECT_CASES = [
     (2, 300, 512, 64, "chunk"),         # the k best where the sample does not see them
     (2, 300, 512, 1000, "equal"),       # all tied: more than the list holds
     (2, 300, 512, 1000, "inf"),
+    (8, 512, 200, 900, "normal"),       # one launch after the score pass: the most rows
+    (8, 513, 200, 900, "normal"),       # of a request, and one more
+    (42, 96, 700, 50, "normal"),        # 252 workgroups of it
+    (43, 96, 700, 50, "normal"),        # 258 would not all run at once
+    (1, 16, 20000, 50, "normal"),       # one workgroup per request
+    (3, 400, 512, 4096, "normal"),      # more gathered than its stage in LDS takes
 ]
 
 
