@@ -99,8 +99,9 @@ __device__ __forceinline__ void work_item(uint32_t i, const WorkMap& w, int32_t&
 // own.  A tile's values are loaded before its score products and the next tile's
 // keys before its value products.  GPU time, 8 x 250 x 8 x 64 with 33..300 keys:
 // the VALU kernel this replaces, one LDS read per FMA, 104 us; this with keys
-// straight from memory 22.4, keys through LDS 19.8, queries too 18.7.  32 x 1024 x 8
-// x 64, 512 keys: 1198, 377, 332, 335 us (103 of the 157 TFLOP/s peak).
+// straight from memory 22.4, keys through LDS 19.8, queries too 18.7, four chains
+// of score products instead of two 18.9.  32 x 1024 x 8 x 64, 512 keys: 1198, 377,
+// 332, 335, 346 us (99 of the 157 TFLOP/s peak).
 //
 // NS waves share 32 beams, wave s taking the key tiles s, s + NS, ...; their
 // partial results meet in LDS.
@@ -202,23 +203,26 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
         }
       }
       to_lds(kraw);
-      // two chains of products
-      f32x16 s0 = {}, s1 = {};
+      // Chains of 16 or 32 products.  Error against 64 bits relative to the VALU
+      // kernel's: two chains 1.15-1.23 at d = 128 and up to 32 keys (sums of 64),
+      // 1.01 at d = 64 and 1-2 keys; four 0.97 and 0.91, and less with more keys.
+      constexpr int kChains = D == 32 ? 2 : 4;
+      f32x16 sc[kChains] = {};
 #pragma unroll
       for (int j = 0; j < kJ; ++j) {
         const f32x4 kf = *(const f32x4*)&o_lds[wave][l32][8 * j + 4 * hi];
 #pragma unroll
-        for (int e = 0; e < 4; e += 2) {
-          s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[j][e], s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e + 1], qf[j][e + 1], s1, 0, 0, 0);
-        }
+        for (int e = 0; e < 4; ++e)
+          sc[e % kChains] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[j][e], sc[e % kChains], 0, 0, 0);
       }
+      f32x16& s0 = sc[0];
       wave_sync();
       if (t + NS < n) load_k(t + NS);
       float mx = -INFINITY;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        s0[r] += s1[r];
+        if constexpr (kChains == 4) s0[r] = (s0[r] + sc[1][r]) + (sc[2][r] + sc[3][r]);
+        else s0[r] += sc[1][r];
         if (t0 + 32 > L && t0 + 8 * (r >> 2) + 4 * hi + (r & 3) >= L) s0[r] = -INFINITY;
         mx = fmaxf(mx, s0[r]);
       }
