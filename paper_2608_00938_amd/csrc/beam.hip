@@ -156,6 +156,31 @@ __device__ __forceinline__ void clear_shared(const TopkWs& ws, int64_t b, uint32
   if (first == 0) ws.info[b * kInfo + 1] = ws.info[b * kInfo + 3] = 0;
 }
 
+// How the workgroups of one request hand what they share (counts, list entries)
+// to the last of them to finish; nobody waits for anybody.  Writers use relaxed
+// agent-scope read-modify-writes only, which every XCD sees in one order per
+// location.  Then every wave waits until its own are performed (publish_shared,
+// in the place of a release: no plain store is handed over, and a release fence
+// writes back the whole L2, 170 against 11 us for the threshold kernel in 512
+// workgroups), and one thread takes a ticket.  The thread with the last ticket
+// acquires at agent scope, so that what its workgroup reads after the next
+// barrier is read after all the tickets and from no older copy in a cache of its
+// XCD; those reads are relaxed agent-scope loads.
+__device__ __forceinline__ void publish_shared() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+// One thread, after publish_shared: 1 in the last of n workgroups, else 0.
+__device__ __forceinline__ int32_t last_to_finish(int32_t* done, int32_t n) {
+  if (__hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != n - 1) return 0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return 1;
+}
+template <class T>
+__device__ __forceinline__ T load_shared(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---------------------------------------------------------------------------
 // candidate scores
 // ---------------------------------------------------------------------------
@@ -1244,22 +1269,15 @@ topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
   if (gridDim.x > 1) {
     // every workgroup's bins from the request's threshold up are complete, as
     // its `first` is at or below the threshold
-    // The shared counts are touched by device-scope read-modify-writes only,
-    // which all XCDs perform at one place, so a wait for this workgroup's own
-    // to be done orders them before its ticket; a device-wide fence here, which
-    // writes back the L2, made the kernel 20 times slower.
     uint32_t* sum = ws.hist(b);
     for (int i = tid; i < kHistBins; i += kTopkThreads)
       if (hist[i] != 0u)
         (void)__hip_atomic_fetch_add(&sum[i], hist[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    publish_shared();
+    if (tid == 0) ipar[0] = last_to_finish(&info[3], (int32_t)gridDim.x);
     __syncthreads();
-    if (tid == 0)
-      ipar[0] = __hip_atomic_fetch_add(&info[3], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (ipar[0] != (int32_t)gridDim.x - 1) return;   // whole workgroup
-    for (int i = tid; i < kHistBins; i += kTopkThreads)
-      hist[i] = __hip_atomic_fetch_add(&sum[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (ipar[0] == 0) return;   // whole workgroup
+    for (int i = tid; i < kHistBins; i += kTopkThreads) hist[i] = load_shared(&sum[i]);
     __syncthreads();
   }
   const int bin = boundary_bin(hist, want, scan, ipar);
@@ -1554,24 +1572,13 @@ topk_fused_rows_kernel(CandFromLogits<T> src, StoredSample smp, const float* __r
   gather_rows<RUN, kTopkThreads, kFusedQueue, true>(c, m0, bound, thr, ll, st, queue, n_queue, rows[wave],
                                                     list, count);
   gather_flush<kTopkThreads, true>(st, list, count);
-  // the list and its count see device-scope read-modify-writes only, as the
-  // select workgroups' counts do
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  publish_shared();
+  if (tid == 0) sh.ipar[0] = last_to_finish(&ws.info[b * kInfo + 3], (int32_t)gridDim.x);
   __syncthreads();
-  if (tid == 0) {
-    const int32_t done = __hip_atomic_fetch_add(&ws.info[b * kInfo + 3], 1, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-    sh.ipar[0] = done;
-    if (done == (int32_t)gridDim.x - 1)
-      sh.ipar[1] = (int32_t)__hip_atomic_fetch_add(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (sh.ipar[0] == 0) return;   // whole workgroup
+  const uint32_t n = load_shared(count);
   __syncthreads();
-  if (sh.ipar[0] != (int32_t)gridDim.x - 1) return;   // whole workgroup
-  const uint32_t n = (uint32_t)sh.ipar[1];
-  __syncthreads();
-  final_select<RUN>(sh, thr, n, N, k, b * k, c, out, [=](uint32_t i) {
-    return __hip_atomic_fetch_add(list + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  });
+  final_select<RUN>(sh, thr, n, N, k, b * k, c, out, [=](uint32_t i) { return load_shared(list + i); });
 }
 
 // The score kernels; with CAND = false they write lse_out, the rows' upper
