@@ -13,10 +13,12 @@
 //   More: a sample of the candidates picks a threshold above which somewhat
 //   more than k are expected (select), one pass over the candidates gathers
 //   everything at or above it (gather), and the gathered set, which holds the k
-//   best exactly when it has at least k members, is ranked (final).
+//   best exactly when it has at least k members, is ranked (final).  A set that
+//   does not fit the list, of crowded scores or from a coarse sample, goes on
+//   behind the sample and is narrowed to the list by digits of its entries.
 //   When fewer than k candidates are above -inf (dead beams), the rest are the
 //   -inf candidates of lowest index.  When the gathered set is too small or
-//   does not fit the list, an exact radix select on the key (digits of 12, 12
+//   does not fit the workspace, an exact radix select on the key (digits of 12, 12
 //   and 8 bits) and an index-ordered collection of the tied candidates take over.
 //   Ranking: a counting sort over bins of the gathered range and a comparison
 //   inside each bin, or a bitonic sort in LDS when a bin is crowded.
@@ -110,13 +112,16 @@ constexpr int kGatherCap = 8192;   // gathered candidates a request can rank
 
 // Workspace of one call.  Per request: the gathered list [kGatherCap] of
 // composites, S sample areas of kSampleArea fp16 (the last one doubles as the
-// select workgroups' common histogram), info [kInfo] = {threshold (float bits),
-// gathered count, unused, workgroups done, unused...}.  S grows with the
-// candidates of a request, one area per 32768 up to 64.
+// select workgroups' common histogram; what the sample leaves of them takes the
+// gathered composites past the list), info [kInfo] = {threshold (float bits),
+// gathered count, how the selection ended (kRanked, kNarrowed, kExact), workgroups
+// done, unused...}.  S grows with the candidates of a request, one area per 32768
+// up to 64.
 constexpr int kMaxSlices = 64;
 constexpr uint32_t kSliceTarget = 32768;
 constexpr int kInfo = 8;
 constexpr int kSampleArea = 2 * kHistBins;
+constexpr int32_t kRanked = 0, kNarrowed = 1, kExact = 2;
 
 __host__ __device__ inline int topk_slices(uint32_t N) {
   const uint32_t s = (N + kSliceTarget - 1) / kSliceTarget;
@@ -128,6 +133,7 @@ struct TopkWs {
   uint16_t* sample = nullptr;
   int32_t* info = nullptr;
   int S = 0;
+  int32_t spill = 0;   // fp16 of the sample areas that the sample takes, a multiple of 4
   TopkWs() = default;
   __host__ __device__ TopkWs(void* ws, int B, int S_) : S(S_) {
     char* p = (char*)ws;
@@ -143,6 +149,10 @@ struct TopkWs {
   }
   __host__ __device__ int64_t sample_stride() const { return (int64_t)S * kSampleArea; }
   __host__ __device__ int64_t sample_room() const { return (int64_t)(S - 1) * kSampleArea; }
+  // composites a request can hold: the list and behind the sample
+  __host__ __device__ uint32_t gather_room() const {
+    return (uint32_t)kGatherCap + (uint32_t)(sample_stride() - spill) / 4;
+  }
   __device__ __forceinline__ uint32_t* hist(int64_t b) const {
     return (uint32_t*)(sample + b * sample_stride() + sample_room());
   }
@@ -710,8 +720,8 @@ __device__ __forceinline__ void clear_bins(uint32_t* bins) {
 }
 
 // The highest bin b >= 1 of hist with at least `want` counts in bins >= b, or 0
-// when bins >= 1 hold fewer.  hist is complete (a barrier since its last update).
-// Ends with a barrier.
+// when bins >= 1 hold fewer; ipar[1] gets the counts in the bins above it, ipar[2]
+// its own.  hist is complete (a barrier since its last update).  Ends with a barrier.
 __device__ int boundary_bin(const uint32_t* hist, uint32_t want, uint32_t* scan, int32_t* ipar) {
   const int tid = threadIdx.x;
   if (tid == 0) ipar[0] = 0;
@@ -729,9 +739,17 @@ __device__ int boundary_bin(const uint32_t* hist, uint32_t want, uint32_t* scan,
     uint32_t run = before;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      if (run < want && run + own[e] >= want) ipar[0] = 4 * t_rev + 3 - e;
+      if (run < want && run + own[e] >= want) {
+        ipar[0] = 4 * t_rev + 3 - e;
+        ipar[1] = (int32_t)run;
+        ipar[2] = (int32_t)own[e];
+      }
       run += own[e];
     }
+  }
+  if (tid == 0 && total < want) {
+    ipar[1] = (int32_t)total;
+    ipar[2] = (int32_t)hist[0];
   }
   __syncthreads();
   const int b = ipar[0];
@@ -948,6 +966,91 @@ __device__ void fill_dead(TopkShared& sh, uint32_t n, int32_t k, uint32_t N, int
   }
 }
 
+// The digit (bin of sh.bin_count, complete) that holds the `want`-th best, counted
+// from the highest digit down: ipar[0]; ipar[1] gets the counts of the higher
+// digits, ipar[2] its own.  Ends with a barrier.
+__device__ __forceinline__ void digit_of_rank(TopkShared& sh, uint32_t want) {
+  // 4 digits per thread, thread 0 owns the highest
+  uint32_t own[4], s4 = 0, total;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    own[j] = sh.bin_count[kHistBins - 1 - 4 * threadIdx.x - j];
+    s4 += own[j];
+  }
+  const uint32_t before = block_exclusive_scan(s4, sh.scan, &total);
+  if (before < want && before + s4 >= want) {
+    uint32_t run = before;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (run < want && run + own[j] >= want) {
+        sh.ipar[0] = kHistBins - 1 - 4 * (int)threadIdx.x - j;
+        sh.ipar[1] = (int32_t)run;
+        sh.ipar[2] = (int32_t)own[j];
+      }
+      run += own[j];
+    }
+  }
+  __syncthreads();
+}
+
+// More gathered composites than the list holds (k < n <= entry.room): brings those
+// down to the digit of 12 bits that holds the k-th, taken from the top until they
+// fit, into sh.list and returns their number.  Composites differ, so at the
+// latest the last digit does.  Bound by reading the entries, eight in flight per
+// thread, once per digit (at most six; crowded scores need two or three).
+template <class Entries>
+__device__ uint32_t narrow(TopkShared& sh, uint32_t n, int32_t k, const Entries& entry) {
+  constexpr int U = 8;
+  constexpr uint32_t kStep = U * kTopkThreads;
+  const int tid = threadIdx.x;
+  uint64_t prefix = 0;
+  uint32_t above = 0, fit;
+  int shift = 64;
+  do {
+    const int top = shift, bits = min(12, shift);
+    shift -= bits;
+    __syncthreads();
+    clear_bins(sh.bin_count);
+    if (tid == 0) sh.n_list = 0u;
+    __syncthreads();
+    for (uint32_t i0 = 0; i0 < n; i0 += kStep) {
+      uint64_t v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = i0 + u * kTopkThreads + tid < n ? entry(i0 + u * kTopkThreads + tid) : 0ull;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        hist_add(sh.bin_count, (int)(v[u] >> shift) & ((1 << bits) - 1),
+                 i0 + u * kTopkThreads + tid < n && (top == 64 || (v[u] >> top) == (prefix >> top)));
+    }
+    __syncthreads();
+    digit_of_rank(sh, (uint32_t)k - above);
+    prefix |= (uint64_t)(uint32_t)sh.ipar[0] << shift;
+    above += (uint32_t)sh.ipar[1];
+    fit = above + (uint32_t)sh.ipar[2];
+  } while (fit > (uint32_t)kGatherCap);
+  for (uint32_t i0 = 0; i0 < n; i0 += kStep) {
+    uint64_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i0 + u * kTopkThreads + tid < n ? entry(i0 + u * kTopkThreads + tid) : 0ull;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * kTopkThreads + tid < n && v[u] >= prefix) sh.list[atomicAdd(&sh.n_list, 1u)] = v[u];
+  }
+  __syncthreads();
+  return fit;
+}
+
+// sh.list[0, n), n <= kGatherCap, into registers, number t + 1024 j to thread t.
+__device__ __forceinline__ void take_list(const TopkShared& sh, uint32_t n,
+                                          uint64_t (&v)[kGatherCap / kTopkThreads]) {
+#pragma unroll
+  for (int j = 0; j < kGatherCap / kTopkThreads; ++j) {
+    const uint32_t i = (uint32_t)(threadIdx.x + j * kTopkThreads);
+    v[j] = i < n ? sh.list[i] : 0ull;
+  }
+  __syncthreads();
+}
+
 // Exact selection of any request: a radix select on the key (digits of 12, 12
 // and 8 bits) over all the candidates, an index-ordered collection of the ties with
 // the k-th, and a bitonic sort.  Eight candidates per thread and step.
@@ -975,26 +1078,7 @@ __device__ void exact_select(TopkShared& sh, int32_t k, uint32_t N, int64_t out0
       }
     }
     __syncthreads();
-    // digits from the top down: 4 per thread, thread 0 owns the highest
-    uint32_t own[4], s4 = 0, total;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      own[j] = hist[kHistBins - 1 - 4 * tid - j];
-      s4 += own[j];
-    }
-    const uint32_t before = block_exclusive_scan(s4, sh.scan, &total);
-    if (before < remaining && before + s4 >= remaining) {
-      uint32_t run = before;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (run < remaining && run + own[j] >= remaining) {
-          sh.ipar[0] = kHistBins - 1 - 4 * tid - j;
-          sh.ipar[1] = (int32_t)run;
-        }
-        run += own[j];
-      }
-    }
-    __syncthreads();
+    digit_of_rank(sh, remaining);
     prefix |= (uint32_t)sh.ipar[0] << shift;
     remaining -= (uint32_t)sh.ipar[1];
   }
@@ -1114,10 +1198,7 @@ topk_small_kernel(Src src, uint32_t N, int32_t k, TopkOut out) {
     const uint32_t n = sh.n_list;
     if (n <= (uint32_t)kGatherCap) {
       uint64_t v[kGatherCap / kTopkThreads];
-#pragma unroll
-      for (int j = 0; j < kGatherCap / kTopkThreads; ++j)
-        v[j] = (uint32_t)(tid + j * kTopkThreads) < n ? sh.list[tid + j * kTopkThreads] : 0ull;
-      __syncthreads();
+      take_list(sh, n, v);
       rank_and_emit(sh, v, n, k, out0, c, out);
       if (n < (uint32_t)k) fill_dead<VEC8>(sh, n, k, N, out0, c, out);
       return;
@@ -1199,39 +1280,54 @@ struct ChunkSample {
 // of a request to finish sums the workgroups' histograms.  The want-th best of
 // the threads' own best samples bounds the threshold from below, so that only
 // the few samples above that are counted.  A request with fewer than `want`
-// samples in the window gathers everything above -inf.
+// samples in the window gathers everything above -inf, if that can fit.
 constexpr float kBelow = 112.0f, kAbove = 16.0f;
 constexpr uint32_t kSelectSamples = 16384;
 
 constexpr float kSelectInvW = (float)kHistBins / (kBelow + kAbove);
+// Bin of a sample.  A sample v below 0 was rounded up, from (v - q, v], q its fp16
+// step; bins that take their upper edge in and not their lower one hold that whole
+// range above the edge below, as edges are fp16 values from -64 up.
+constexpr float kEdge = 0x1p-14f;
+__device__ __forceinline__ int sample_bin(float x) { return step_bin(x, kEdge - kBelow, kSelectInvW); }
+
+// Samples j0 .. j0 + kSelectSamples - 1 (-inf past the last), kSampleLoads loads of
+// four per thread.
+constexpr int kSampleLoads = kSelectSamples / (4 * kTopkThreads);
+template <class Row>
+__device__ __forceinline__ void load_samples(const Row& sample, uint32_t j0, float ref,
+                                             float (&x)[kSampleLoads][4]) {
+  u32x2 w[kSampleLoads];
+#pragma unroll
+  for (int u = 0; u < kSampleLoads; ++u) w[u] = sample.load4(j0 + 4 * (u * kTopkThreads + threadIdx.x), ref);
+#pragma unroll
+  for (int u = 0; u < kSampleLoads; ++u) {
+    const f16x2 lo = __builtin_bit_cast(f16x2, w[u].x), hi = __builtin_bit_cast(f16x2, w[u].y);
+    x[u][0] = (float)lo.x;
+    x[u][1] = (float)lo.y;
+    x[u][2] = (float)hi.x;
+    x[u][3] = (float)hi.y;
+  }
+}
 
 // hist: the counts of samples j0 .. j0 + kSelectSamples - 1 in the bins from the
-// want-th best of the threads' own best samples up.
+// want-th best of the threads' own best samples up; where those are all the
+// window's, bin 0 counts the finite samples below it.
 template <class Row>
 __device__ __forceinline__ void sample_hist(const Row& sample, uint32_t j0, float ref, uint32_t want,
                                             uint32_t* hist, uint32_t* scan, int32_t* ipar) {
-  constexpr int U = kSelectSamples / (4 * kTopkThreads);   // loads of four samples per thread
+  constexpr int U = kSampleLoads;
   const int tid = threadIdx.x;
   float x[U][4];
+  load_samples(sample, j0, ref, x);
   float mx = -INFINITY;
-  {
-    u32x2 w[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) w[u] = sample.load4(j0 + 4 * (u * kTopkThreads + tid), ref);
+  for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const f16x2 lo = __builtin_bit_cast(f16x2, w[u].x), hi = __builtin_bit_cast(f16x2, w[u].y);
-      x[u][0] = (float)lo.x;
-      x[u][1] = (float)lo.y;
-      x[u][2] = (float)hi.x;
-      x[u][3] = (float)hi.y;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, x[u][e]);
-    }
-  }
+    for (int e = 0; e < 4; ++e) mx = fmaxf(mx, x[u][e]);
   clear_bins(hist);
   __syncthreads();
-  const int own = step_bin(mx, -kBelow, kSelectInvW);
+  const int own = sample_bin(mx);
   if (own > 0) atomicAdd(&hist[own], 1u);
   __syncthreads();
   const int first = max(1, boundary_bin(hist, want, scan, ipar));   // 1: the whole window
@@ -1242,24 +1338,76 @@ __device__ __forceinline__ void sample_hist(const Row& sample, uint32_t j0, floa
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int bin = step_bin(x[u][e], -kBelow, kSelectInvW);
+        const int bin = sample_bin(x[u][e]);
         if (bin >= first) atomicAdd(&hist[bin], 1u);
       }
   }
+  if (first == 1) {
+    uint32_t low = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        low += x[u][e] > -INFINITY && sample_bin(x[u][e]) == 0 ? 1u : 0u;
+    low = wave_scan(low);
+    if ((tid & 63) == 63 && low != 0u) atomicAdd(&hist[0], low);
+  }
   __syncthreads();
 }
-// about the bin's lower edge
-__device__ __forceinline__ float bin_threshold(int bin, float ref) {
-  return bin > 0 ? ref + ((float)bin / kSelectInvW - kBelow) : -FLT_MAX;
+// The threshold of a request whose samples, one of 2^lp, hist counts (complete):
+// the lower edge of the bin with the `want`-th best.  Where that bin is so crowded
+// that what is expected at or above it comes near the room for gathered candidates,
+// it is cut in 4096 by reading all the samples again; a smaller crowd costs less to
+// gather and narrow (64 x 4096 x 512, k = 4096: the cut 13-47 us, 15000 candidates
+// past the list 10).  Where even one value's crowd would not fit, what is above it
+// may still be k: 5000 allowed tokens over a floor of equal scores.  That shape with
+// equal prefixes and N(0, s^2) logits, against the exact selection by one workgroup
+// for everything past the list: s = 0.3 3189 and 139 us, 0.1 2075 and 149, 0.02 2211
+// and 155; 5000 tokens over a floor 2222 and 270.
+template <class Row>
+__device__ __forceinline__ float threshold(const Row& sample, uint32_t* hist, uint32_t want, int32_t lp,
+                                           float ref, uint32_t room, uint32_t* scan, int32_t* ipar) {
+  const int bin = boundary_bin(hist, want, scan, ipar);
+  uint32_t above = (uint32_t)ipar[1];
+  const bool crowded = ((uint64_t)(above + (uint32_t)ipar[2]) << lp) > min(room / 4 * 3, 3u * kGatherCap);
+  float edge = (float)bin / kSelectInvW - kBelow;
+  const float slack = fabsf(ref) * 0x1p-22f;   // the rounding of the differences
+  if (!crowded)   // below -64 an fp16 step is wider than a bin
+    return bin == 0 ? -FLT_MAX : ref + (edge < -64.f ? edge - 1.0f / kSelectInvW : edge) - slack;
+  // the outer bins, open below and above, in as many steps of a bin's width
+  const float inv_w = bin == 0 || bin == kHistBins - 1 ? kSelectInvW : kSelectInvW * (float)kHistBins;
+  if (bin == 0) edge -= kBelow + kAbove;
+  __syncthreads();
+  clear_bins(hist);
+  __syncthreads();
+  for (uint32_t j0 = 0; j0 < sample.n; j0 += kSelectSamples) {
+    float x[kSampleLoads][4];
+    load_samples(sample, j0, ref, x);
+#pragma unroll
+    for (int u = 0; u < kSampleLoads; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        hist_add(hist, step_bin(x[u][e], edge, inv_w), x[u][e] > -INFINITY && sample_bin(x[u][e]) == bin);
+  }
+  __syncthreads();
+  const int part = boundary_bin(hist, want - above, scan, ipar);
+  above += (uint32_t)ipar[1];
+  const bool fits = ((uint64_t)(above + (uint32_t)ipar[2]) << lp) <= room || above == 0u;
+  __syncthreads();
+  if (fits && bin == 0 && part == 0) return -FLT_MAX;
+  // a sample v < 0 stands for (v - q, v], one of 0 and above for [v, v + q)
+  edge += (float)part / inv_w;
+  const float q = fmaxf(__uint_as_float(__float_as_uint(edge) & 0x7f800000u) * 0x1p-10f, 0x1p-24f);
+  return fits ? ref + edge - (edge < 0.f ? q : 0.f) - slack : ref + edge + 1.0f / inv_w + (edge < 0.f ? 0.f : q);
 }
 
 template <class Smp>
 __global__ void __launch_bounds__(kTopkThreads)
-topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
+topk_select_kernel(Smp smp, uint32_t N, uint32_t want, int32_t lp, TopkWs ws) {
   __shared__ uint32_t hist[kHistBins];
   __shared__ uint32_t scan[64];
   __shared__ float fscan[kTopkThreads / 64];
-  __shared__ int32_t ipar[2];
+  __shared__ int32_t ipar[4];
   const int tid = threadIdx.x;
   const int64_t b = blockIdx.y;
   const auto sample = smp.request(b, N);
@@ -1280,9 +1428,9 @@ topk_select_kernel(Smp smp, uint32_t N, uint32_t want, TopkWs ws) {
     for (int i = tid; i < kHistBins; i += kTopkThreads) hist[i] = load_shared(&sum[i]);
     __syncthreads();
   }
-  const int bin = boundary_bin(hist, want, scan, ipar);
+  const float thr = threshold(sample, hist, want, lp, ref, ws.gather_room(), scan, ipar);
   if (tid == 0) {
-    info[0] = __float_as_int(bin_threshold(bin, ref));
+    info[0] = __float_as_int(thr);
     info[1] = 0;   // gathered count
   }
 }
@@ -1294,14 +1442,36 @@ __global__ void __launch_bounds__(kTopkThreads) topk_clear_kernel(TopkWs ws) {
 constexpr int kGatherThreads = 256;
 constexpr int kStage = 1024;   // LDS entries of a gather workgroup
 
-// Into a request's gathered list; SHARED: other workgroups of this launch read it.
+// A request's gathered composites: kGatherCap in the list, the rest behind the
+// sample.  SHARED: other workgroups of this launch read them.
 template <bool SHARED>
-__device__ __forceinline__ void put_list(uint64_t* at, uint64_t v) {
-  if constexpr (SHARED)
-    (void)__hip_atomic_exchange(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else
-    *at = v;
-}
+struct Gathered {
+  uint64_t *list, *more;   // more: where number 0 would lie, if it were there
+  uint32_t* count;
+  uint32_t room;
+  __device__ __forceinline__ Gathered(const TopkWs& ws, int64_t b)
+      : list(ws.list + b * (int64_t)kGatherCap),
+        more((uint64_t*)(ws.sample + b * ws.sample_stride() + ws.spill) - kGatherCap),
+        count((uint32_t*)&ws.info[b * kInfo + 1]), room(ws.gather_room()) {}
+  __device__ __forceinline__ uint64_t* at(uint32_t i) const {
+    return (i < (uint32_t)kGatherCap ? list : more) + i;
+  }
+  __device__ __forceinline__ static void store(uint64_t* p, uint64_t v) {
+    if constexpr (SHARED)
+      (void)__hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+      *p = v;
+  }
+  __device__ __forceinline__ void put(uint32_t i, uint64_t v) const {
+    if (i < room) store(at(i), v);
+  }
+  __device__ __forceinline__ static uint64_t load(const uint64_t* p) {
+    if constexpr (SHARED) return load_shared(p);
+    else return *p;
+  }
+  __device__ __forceinline__ uint64_t operator()(uint32_t i) const { return load(at(i)); }
+  __device__ __forceinline__ uint64_t in_list(uint32_t i) const { return load(list + i); }   // i < kGatherCap
+};
 
 // A workgroup's staged candidates: flushed with one global atomic (same-address
 // global atomics serialise); what does not fit the stage goes to the list directly.
@@ -1310,37 +1480,38 @@ struct GatherStage {
   uint64_t entry[STAGE];
   uint32_t n, base;
 };
-template <int STAGE, bool SHARED = false>
+template <int STAGE, bool SHARED>
 struct PutStage {
   GatherStage<STAGE>& st;
-  uint64_t* list;
-  uint32_t* count;
+  const Gathered<SHARED>& to;
   uint32_t pos = 0, direct = 0;
   __device__ __forceinline__ void reserve(uint32_t n) {
     pos = atomicAdd(&st.n, n);
     const uint32_t first = max(pos, (uint32_t)STAGE);
-    if (pos + n > first) direct = atomicAdd(count, pos + n - first);
+    if (pos + n > first) direct = atomicAdd(to.count, pos + n - first);
   }
   __device__ __forceinline__ void operator()(uint64_t v) {
     if (pos < (uint32_t)STAGE) {
       st.entry[pos] = v;
     } else {
-      if (direct < (uint32_t)kGatherCap) put_list<SHARED>(list + direct, v);
-      ++direct;
+      to.put(direct++, v);
     }
     ++pos;
   }
 };
-template <int THREADS, bool SHARED = false, int STAGE>
-__device__ __forceinline__ void gather_flush(GatherStage<STAGE>& st, uint64_t* list, uint32_t* count) {
+template <int THREADS, bool SHARED, int STAGE>
+__device__ __forceinline__ void gather_flush(GatherStage<STAGE>& st, const Gathered<SHARED>& to) {
   __syncthreads();
   const uint32_t n = min(st.n, (uint32_t)STAGE);
   if (n == 0) return;   // whole workgroup
-  if (threadIdx.x == 0) st.base = atomicAdd(count, n);
+  if (threadIdx.x == 0) st.base = atomicAdd(to.count, n);
   __syncthreads();
   const uint32_t b0 = st.base;
-  for (uint32_t j = threadIdx.x; j < n; j += THREADS)
-    if (b0 + j < (uint32_t)kGatherCap) put_list<SHARED>(list + b0 + j, st.entry[j]);
+  if (b0 + n <= (uint32_t)kGatherCap) {
+    for (uint32_t j = threadIdx.x; j < n; j += THREADS) to.store(to.list + b0 + j, st.entry[j]);
+  } else {
+    for (uint32_t j = threadIdx.x; j < n; j += THREADS) to.put(b0 + j, st.entry[j]);
+  }
 }
 
 // Gather over a written candidate array (16 x 1000 x 509 fp32, 33 MB: 31 -> 12
@@ -1353,11 +1524,9 @@ __global__ void __launch_bounds__(kGatherThreads)
 topk_gather_array_kernel(CandArray src, uint32_t N, uint32_t per, TopkWs ws) {
   __shared__ GatherStage<kStage> st;
   const int64_t b = blockIdx.y;
-  const int32_t* info = ws.info + b * kInfo;
-  const float thr = __int_as_float(info[0]);
+  const float thr = __int_as_float(ws.info[b * kInfo]);
   const auto c = src.request(b, N);
-  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
-  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 1];
+  const Gathered<false> to(ws, b);
   if (threadIdx.x == 0) st.n = 0u;
   __syncthreads();
   const uint64_t i0 = (uint64_t)blockIdx.x * per;
@@ -1375,7 +1544,7 @@ topk_gather_array_kernel(CandArray src, uint32_t N, uint32_t per, TopkWs ws) {
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         for_hits<4>(x[u], (uint32_t)(j0 + 4 * (u * kGatherThreads + threadIdx.x)), thr,
-                    PutStage<kStage>{st, list, count});
+                    PutStage<kStage, false>{st, to});
     }
   } else {
     for (uint64_t j0 = i0; j0 < i1; j0 += 8 * kGatherThreads) {
@@ -1388,10 +1557,10 @@ topk_gather_array_kernel(CandArray src, uint32_t N, uint32_t per, TopkWs ws) {
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         for_hits<1>(x[u], (uint32_t)(j0 + u * kGatherThreads + threadIdx.x), thr,
-                    PutStage<kStage>{st, list, count});
+                    PutStage<kStage, false>{st, to});
     }
   }
-  gather_flush<kGatherThreads>(st, list, count);
+  gather_flush<kGatherThreads>(st, to);
 }
 
 // Gather over candidates recomputed from the logits.  A wave takes up to 64
@@ -1409,7 +1578,7 @@ constexpr int kQueue = 2048;
 template <bool RUN, int THREADS, int QUEUE, bool SHARED, int STAGE, class Row>
 __device__ __forceinline__ void gather_rows(const Row& c, int64_t m0, float bound, float thr, int32_t ll,
                                             GatherStage<STAGE>& st, uint32_t* queue, uint32_t& n_queue,
-                                            uint8_t* rows, uint64_t* list, uint32_t* count) {
+                                            uint8_t* rows, const Gathered<SHARED>& to) {
   constexpr int E = RUN ? 8 : 1, U = 4;
   const int lane = threadIdx.x & 63;
   if (threadIdx.x == 0) st.n = n_queue = 0u;
@@ -1462,7 +1631,7 @@ __device__ __forceinline__ void gather_rows(const Row& c, int64_t m0, float boun
       }
       float x[E];
       c.template finish<E>(at[u], m[u], raw[u], x);
-      for_hits<E>(x, at[u], thr, PutStage<STAGE, SHARED>{st, list, count});
+      for_hits<E>(x, at[u], thr, PutStage<STAGE, SHARED>{st, to});
     }
   }
   if constexpr (RUN) {
@@ -1471,7 +1640,7 @@ __device__ __forceinline__ void gather_rows(const Row& c, int64_t m0, float boun
     for (uint32_t j = threadIdx.x; j < n; j += THREADS) {
       float x[8];
       c.load8(queue[j], x);
-      for_hits<8>(x, queue[j], thr, PutStage<STAGE, SHARED>{st, list, count});
+      for_hits<8>(x, queue[j], thr, PutStage<STAGE, SHARED>{st, to});
     }
   }
 }
@@ -1487,37 +1656,44 @@ topk_gather_rows_kernel(CandFromLogits<T> src, const float* __restrict__ row_max
   __shared__ uint8_t rows[kWaves][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t b = blockIdx.y;
-  const int32_t* info = ws.info + b * kInfo;
   const int64_t m0 = ((int64_t)blockIdx.x * kWaves + wave) * rows_per_wave;
   const float bound = lane < rows_per_wave && m0 + lane < src.M ? row_max[b * src.M + m0 + lane] : -INFINITY;
-  const float thr = __int_as_float(info[0]);
-  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
-  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 1];
+  const float thr = __int_as_float(ws.info[b * kInfo]);
+  const Gathered<false> to(ws, b);
   gather_rows<RUN, kGatherThreads, kQueue, false>(src.request(b, N), m0, bound, thr, ll, st, queue, n_queue,
-                                                  rows[wave], list, count);
-  gather_flush<kGatherThreads>(st, list, count);
+                                                  rows[wave], to);
+  gather_flush<kGatherThreads>(st, to);
 }
 
-// Final selection: rank the n gathered candidates at or above thr (entry(i) reads
-// the list), or the exact selection over all the request's candidates.
-template <bool VEC8, class Row, class Entry>
+// Final selection from the n gathered candidates at or above thr, or the exact
+// selection over all the request's candidates; *how says which it was.
+template <bool VEC8, class Row, class Entries>
 __device__ __forceinline__ void final_select(TopkShared& sh, float thr, uint32_t n, uint32_t N, int32_t k,
-                                             int64_t out0, const Row& c, const TopkOut& out, Entry entry) {
+                                             int64_t out0, const Row& c, const TopkOut& out,
+                                             const Entries& entry, int32_t* how) {
   constexpr int kPer = kGatherCap / kTopkThreads;
-  // all candidates at or above thr are in the list; it holds the k best when
+  // all candidates at or above thr are gathered; the k best are among them when
   // they are at least k, or when they are all there are above -inf
-  if (n <= (uint32_t)kGatherCap && (n >= (uint32_t)k || thr == -FLT_MAX)) {
-    uint64_t v[kPer];
+  const bool enough = n >= (uint32_t)k || thr == -FLT_MAX;
+  const int32_t way = !enough || n > entry.room ? kExact : (n > (uint32_t)kGatherCap ? kNarrowed : kRanked);
+  if (threadIdx.x == 0) *how = way;
+  if (way == kExact) {
+    exact_select<VEC8>(sh, k, N, out0, c, out);
+    return;
+  }
+  uint64_t v[kPer];
+  if (way == kRanked) {
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       const uint32_t i = (uint32_t)(threadIdx.x + j * kTopkThreads);
-      v[j] = i < n ? entry(i) : 0ull;
+      v[j] = i < n ? entry.in_list(i) : 0ull;
     }
-    rank_and_emit(sh, v, n, k, out0, c, out);
-    if (n < (uint32_t)k) fill_dead<VEC8>(sh, n, k, N, out0, c, out);
-    return;
+  } else {
+    n = narrow(sh, n, k, entry);
+    take_list(sh, n, v);
   }
-  exact_select<VEC8>(sh, k, N, out0, c, out);
+  rank_and_emit(sh, v, n, k, out0, c, out);
+  if (n < (uint32_t)k) fill_dead<VEC8>(sh, n, k, N, out0, c, out);
 }
 
 template <class Src, bool VEC8>
@@ -1525,10 +1701,9 @@ __global__ void __launch_bounds__(kTopkThreads)
 topk_final_kernel(Src src, uint32_t N, int32_t k, TopkWs ws, TopkOut out) {
   __shared__ TopkShared sh;
   const int64_t b = blockIdx.x;
-  const int32_t* info = ws.info + b * kInfo;
-  const uint64_t* list = ws.list + b * (int64_t)kGatherCap;
+  int32_t* info = ws.info + b * kInfo;
   final_select<VEC8>(sh, __int_as_float(info[0]), (uint32_t)info[1], N, k, b * k, src.request(b, N), out,
-                     [=](uint32_t i) { return list[i]; });
+                     Gathered<false>(ws, b), &info[2]);
 }
 
 // Select, gather and final in one launch, for few rows: bound by the latency of
@@ -1549,7 +1724,7 @@ constexpr uint32_t kFusedMaxPerRequest = 32, kFusedMaxBlocks = 256;
 template <class T, bool RUN>
 __global__ void __launch_bounds__(kTopkThreads)
 topk_fused_rows_kernel(CandFromLogits<T> src, StoredSample smp, const float* __restrict__ row_max,
-                       int32_t ll, uint32_t N, uint32_t want, int32_t k, TopkWs ws, TopkOut out) {
+                       int32_t ll, uint32_t N, uint32_t want, int32_t lp, int32_t k, TopkWs ws, TopkOut out) {
   constexpr int kWaves = kTopkThreads / 64;
   __shared__ TopkShared sh;
   __shared__ uint32_t n_queue;
@@ -1565,20 +1740,18 @@ topk_fused_rows_kernel(CandFromLogits<T> src, StoredSample smp, const float* __r
   const auto sample = smp.request(b, N);
   const float ref = smp.ref(sample, b, nullptr);
   sample_hist(sample, 0, ref, want, sh.bin_count, sh.scan, sh.ipar);
-  const float thr = bin_threshold(boundary_bin(sh.bin_count, want, sh.scan, sh.ipar), ref);
-  uint64_t* list = ws.list + b * (int64_t)kGatherCap;
-  uint32_t* count = (uint32_t*)&ws.info[b * kInfo + 1];
+  const float thr = threshold(sample, sh.bin_count, want, lp, ref, ws.gather_room(), sh.scan, sh.ipar);
+  const Gathered<true> to(ws, b);
   const auto c = src.request(b, N);
-  gather_rows<RUN, kTopkThreads, kFusedQueue, true>(c, m0, bound, thr, ll, st, queue, n_queue, rows[wave],
-                                                    list, count);
-  gather_flush<kTopkThreads, true>(st, list, count);
+  gather_rows<RUN, kTopkThreads, kFusedQueue, true>(c, m0, bound, thr, ll, st, queue, n_queue, rows[wave], to);
+  gather_flush<kTopkThreads>(st, to);
   publish_shared();
   if (tid == 0) sh.ipar[0] = last_to_finish(&ws.info[b * kInfo + 3], (int32_t)gridDim.x);
   __syncthreads();
   if (sh.ipar[0] == 0) return;   // whole workgroup
-  const uint32_t n = load_shared(count);
+  const uint32_t n = load_shared(to.count);
   __syncthreads();
-  final_select<RUN>(sh, thr, n, N, k, b * k, c, out, [=](uint32_t i) { return load_shared(list + i); });
+  final_select<RUN>(sh, thr, n, N, k, b * k, c, out, to, &ws.info[b * kInfo + 2]);
 }
 
 // The score kernels; with CAND = false they write lse_out, the rows' upper
@@ -1657,12 +1830,15 @@ static hipError_t launch_topk_small(const Src& src, int32_t B, uint32_t N, int32
 
 // Candidates to expect above the threshold, from samples of one in 2^lp: k and
 // eight standard deviations of a sampled count of k, at most 3/4 of the list (as
-// many deviations are left above that).
-static double gather_target(int32_t k, int lp) {
-  return (double)k + 8.0 * sqrt((double)k * (double)(1u << lp));
+// many deviations are left above that).  From lp = 5 on that is fewer than six for
+// k = 4096, so there it is six deviations and the rest of the workspace takes
+// what the list does not: reading all candidates again in one workgroup, which a set
+// short of k needs, takes 14 ms for 16.8e6 of them.
+static double gather_target(int32_t k, int lp, double deviations = 8.0) {
+  return (double)k + deviations * sqrt((double)k * (double)(1u << lp));
 }
 static uint32_t samples_wanted(int32_t k, int lp) {
-  const uint32_t t = (uint32_t)fmin(gather_target(k, lp), 0.75 * kGatherCap);
+  const uint32_t t = (uint32_t)fmin(gather_target(k, lp), fmax(0.75 * kGatherCap, gather_target(k, lp, 6.0)));
   const uint32_t w = (t + (1u << lp) - 1) >> lp;
   return w < 1 ? 1 : w;
 }
@@ -1682,7 +1858,7 @@ template <class Smp>
 static void launch_select(const Smp& smp, int32_t B, uint32_t N, int32_t k, int lp, const TopkWs& ws,
                           hipStream_t stream) {
   hipLaunchKernelGGL(topk_select_kernel<Smp>, dim3(select_blocks(smp.n), (unsigned)B), dim3(kTopkThreads),
-                     0, stream, smp, N, samples_wanted(k, lp), ws);
+                     0, stream, smp, N, samples_wanted(k, lp), lp, ws);
 }
 
 template <class Src>
@@ -1737,7 +1913,7 @@ static hipError_t launch_step(const void* logits, const float* prev, const uint3
   const int32_t R = B * M;
   const uint32_t N = (uint32_t)M * (uint32_t)V;
   const int S = topk_slices(N);
-  const TopkWs ws(workspace, B, S);
+  TopkWs ws(workspace, B, S);
   // after the top-k workspace: the rows' log-sum-exp and upper bounds
   float* lse = (float*)((char*)workspace + TopkWs::bytes(B, S));
   float* row_max = lse + R;
@@ -1757,6 +1933,7 @@ static hipError_t launch_step(const void* logits, const float* prev, const uint3
                     M, FastDiv((uint32_t)M)};
     if (n <= kSelectSamples || (n <= kSampleTarget && !sample_suffices(k, lp + 1))) break;
   }
+  if (smp.p != nullptr) ws.spill = (int32_t)(((uint64_t)smp.per_row * (uint32_t)M + 3 + 3) / 4 * 4);
   // lanes per row: as many as its runs (tokens) need, at most a wave
   constexpr int E = RUN ? 8 : 1;
   int ll = 0;
@@ -1767,7 +1944,7 @@ static hipError_t launch_step(const void* logits, const float* prev, const uint3
   if (smp.p != nullptr && stored.n <= kSelectSamples && fused_blocks <= kFusedMaxPerRequest &&
       fused_blocks * (uint32_t)B <= kFusedMaxBlocks) {
     hipLaunchKernelGGL((topk_fused_rows_kernel<T, RUN>), dim3(fused_blocks, (unsigned)B), dim3(kTopkThreads),
-                       0, stream, src, stored, row_max, ll, N, samples_wanted(k, smp.lp), k, ws, out);
+                       0, stream, src, stored, row_max, ll, N, samples_wanted(k, smp.lp), smp.lp, k, ws, out);
     return hipGetLastError();
   }
   if (smp.p != nullptr)

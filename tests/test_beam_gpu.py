@@ -249,6 +249,60 @@ def test_beam_selection_paths_bit_exact(gpu, case, dtype):
             assert same.all(), (what, name, "scores (bitwise)")
 
 
+# Requests whose sampled threshold takes in more than the ranking's list holds, or
+# would: (B, M, V, k, kind).  How the selection ended is the third word of each
+# request's info, at the end of the top-k workspace: 2 is the pass of one
+# workgroup over all the candidates, 20 to 60 times slower at these sizes.
+CROWDED_CASES = [
+    (2, 4096, 512, 4096, "s0.3"), (2, 4096, 512, 4096, "s0.1"), (2, 4096, 512, 4096, "s0.05"),
+    (2, 4096, 512, 4096, "floor5000"), (2, 4096, 512, 4096, "floor5500"), (3, 4096, 512, 4096, "wide"),
+    (2, 512, 512, 1024, "s0.02"), (3, 140, 509, 4000, "s0.05"), (1, 4096, 4096, 4096, "s3"),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", CROWDED_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_beam_selection_of_crowded_scores_stays_on_the_chip(gpu, case, dtype):
+    """Scores so close together that a bin of the threshold histogram holds
+    thousands of them, a floor of equal scores under little more than k allowed
+    tokens, prefixes far apart, and samples too thin to aim within the list: bit
+    for bit the oracle's order, and without the one-workgroup pass."""
+    B, M, V, k, kind = case
+    R = B * M
+    _log(f"[beam crowded] {dtype} B={B} M={M} V={V} k={k} {kind}")
+    gen = torch.Generator(device=gpu)
+    gen.manual_seed(17)
+    logits = torch.randn((R, V), generator=gen, device=gpu)
+    prev = torch.full((R,), -7.25, device=gpu)
+    if kind[0] == "s":
+        logits *= float(kind[1:])
+        if V > 512:
+            prev = torch.from_numpy(W.beam_prev_scores(17, 2, R)).to(gpu)
+    elif kind == "wide":
+        prev = 30.0 * torch.randn((R,), generator=gen, device=gpu)
+    else:
+        allowed = torch.rand((R, V), generator=gen, device=gpu) < int(kind[5:]) / (M * V)
+        logits = torch.where(allowed, 3.0 * logits, torch.full_like(logits, -1e4))
+    logits = logits.to(W.TORCH_DTYPES[dtype])
+    cand, rmax = G.grace_beam_scores(logits, prev)
+    topk_bytes = G.grace_beam_topk_workspace_bytes(B, M, V)
+    runs = {}
+    for name, n, call in (
+            ("step", G.grace_beam_step_workspace_bytes(B, M, V),
+             lambda ws: G.grace_beam_step(logits, prev, B, M, k, workspace=ws)),
+            ("topk", topk_bytes, lambda ws: G.grace_beam_topk(cand, B, M, k, row_max=rmax, workspace=ws))):
+        ws = torch.full((n,), 0x7f, dtype=torch.uint8, device=gpu)
+        runs[name] = [x.cpu().numpy() for x in call(ws)]
+        info = ws[topk_bytes - 32 * B:topk_bytes].view(torch.int32).view(B, 8).cpu().numpy()
+        _log(f"  {name}: gathered {info[:, 1].tolist()}, ended {info[:, 2].tolist()}")
+        assert set(info[:, 2].tolist()) <= {0, 1}, name
+    rp, rt, rs = BO.beam_topk(cand.cpu().numpy(), B, M, V, k)
+    for name, (par, tok, sc) in runs.items():
+        assert np.array_equal(par, rp), (name, "parents")
+        assert np.array_equal(tok, rt), (name, "tokens")
+        assert np.array_equal(sc.view(np.uint32), rs.view(np.uint32)), (name, "scores (bitwise)")
+
+
 DYN = [
     dict(dtype="bf16", B=3, H=2, d=64, widths=(1, 5, 12, 12)),
     dict(dtype="f32", B=2, H=3, d=32, widths=(1, 4, 9, 7, 9)),
