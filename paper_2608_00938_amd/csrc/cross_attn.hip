@@ -237,9 +237,11 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
           for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
         m_run = m_new;
       }
+      // while every score is -inf (masked keys), they get weight 0
+      const float base = m_run > -INFINITY ? m_run : 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = fast_exp2((s0[r] - m_run) * c);
+        const float p = fast_exp2((s0[r] - base) * c);
         l_run += p;   // this half's keys
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
@@ -251,8 +253,12 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 
   // Output through LDS as beam rows: lane holds dims 32 db + 8 g + 4 hi + 0..3
   // of beam l32.  With one wave per beam group it only reads back its own rows.
+  // 1 / row sum; 0 without keys, NaN (the definition's 0 / 0) with masked keys only
+  auto inverse = [=](float l, float m) __attribute__((always_inline)) {
+    return l > 0.f ? 1.0f / l : (n > 0 && m == -INFINITY ? NAN : 0.f);
+  };
   if (NS == 1) {
-    const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
+    const float inv = inverse(l_run, m_run);
 #pragma unroll
     for (int db = 0; db < kDB; ++db)
 #pragma unroll
@@ -290,7 +296,7 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
         ll += f * l_w;
         acc += f * *(const f32x4*)&o_lds[group * NS + w][row][col];
       }
-      acc *= ll > 0.f ? 1.0f / ll : 0.f;
+      acc *= inverse(ll, mm);
     }
     if (m0 + row < M) *(f32x4_a4*)(out + ((int64_t)b * M + m0 + row) * E + h * D + col) = acc;
   }
@@ -1177,9 +1183,11 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
   f32x16 o[C::kDB][MB];
   f32x4 lsum = {0.f, 0.f, 0.f, 0.f};
   float shift[MB];
+  bool fresh[MB];   // no score above -inf yet (only masked keys)
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     shift[mb] = 0.f;
+    fresh[mb] = true;
 #pragma unroll
     for (int db = 0; db < C::kDB; ++db)
 #pragma unroll
@@ -1222,15 +1230,15 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
 #pragma unroll
       for (int r = 3; r + 1 < 16; r += 2) m1 = max3(m1, sc[mb][r], sc[mb][r + 1]);
       mx[mb] = max_with_other_half(max3(m1, sc[mb][15], sc[mb][15]));
-      move |= mx[mb] > C::kShiftHi || (t < NS && mx[mb] < C::kShiftLo);
+      move |= mx[mb] > C::kShiftHi || (fresh[mb] && mx[mb] < C::kShiftLo && mx[mb] > -INFINITY);
     }
     if (__any(move)) {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
-        const bool need = mx[mb] > C::kShiftHi || (t < NS && mx[mb] < C::kShiftLo);
+        const bool need = mx[mb] > C::kShiftHi || (fresh[mb] && mx[mb] < C::kShiftLo && mx[mb] > -INFINITY);
         const float delta = need ? mx[mb] : 0.f;
-        // nothing to rescale at the wave's first tile (where 2^-delta may overflow)
-        const float alpha = t < NS ? 0.f : fast_exp2(-delta);
+        // nothing to rescale at the beam's first score (where 2^-delta may overflow)
+        const float alpha = fresh[mb] ? 0.f : fast_exp2(-delta);
         shift[mb] += delta;
         const float alpha_hi = __shfl_xor(alpha, 16);
         lsum[2 * mb] *= alpha;
@@ -1243,6 +1251,8 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
           for (int r = 0; r < 16; ++r) o[db][mb][r] *= alpha;
       }
     }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) fresh[mb] = fresh[mb] && !(mx[mb] > -INFINITY);
 #pragma unroll
     for (int kc = 0; kc < 2; ++kc) {
       bf16x8 vf[C::kDB];
@@ -1278,7 +1288,7 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
   for (int mb = 0; mb < MB; ++mb) {
     const float s_lo = __shfl(lsum[2 * mb], l32 & 15), s_hi = __shfl(lsum[2 * mb + 1], l32 & 15);
     if (hi == 0) {
-      part_shift[wave][mb * 32 + l32] = shift[mb];
+      part_shift[wave][mb * 32 + l32] = fresh[mb] ? -INFINITY : shift[mb];
       part_l[wave][mb * 32 + l32] = l32 < 16 ? s_lo : s_hi;
     }
 #pragma unroll

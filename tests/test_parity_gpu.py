@@ -387,6 +387,31 @@ def test_cross_bf16_both_kernels(gpu, H, d, kind):
     _check_close(_np(out), ref, "bf16", f"cross H={H} d={d} {kind}")
 
 
+@pytest.mark.parametrize("dtype,H", [("bf16", 2), ("bf16", 48), ("f32", 2), ("f32", 48)],
+                         ids=["bf16_split", "bf16_whole", "f32_split", "f32_whole"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_cross_masked_key_tiles(gpu, d, dtype, H):
+    """Keys whose scores overflow to -inf (the type's lowest value in a key, as a
+    mask) get weight 0 wherever they lie: whole 32-key tiles, so that a wave
+    that takes every fourth tile sees nothing else, first or last; the first
+    tile; all but one key.  A request with nothing but masked keys has no softmax."""
+    lengths = [200, 130, 64, 97, 70]
+    masked = [np.r_[32:64, 160:192], np.r_[0:128], np.r_[0:32], np.r_[0:96], np.r_[0:70]]
+    B, M = len(lengths), 40 if H == 2 else 300
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    g = torch.Generator().manual_seed(900 + d)
+    q, k, v = (torch.randn((n, H, d), generator=g).to(W.TORCH_DTYPES[dtype])
+               for n in (B * M, int(off[-1]), int(off[-1])))
+    q[:, :, 0] = 2.0
+    for b in range(B):
+        k[off[b] + masked[b], :, 0] = torch.finfo(k.dtype).min
+    _log(f"[cross masked] {dtype} H={H} d={d}")
+    out = _np(G.grace_cross_attn(q.to(gpu), k.to(gpu), v.to(gpu), torch.from_numpy(off).to(gpu), M))
+    assert np.isnan(out[4 * M:]).all()
+    ref = oracle.cross_attn(_np(q[:4 * M]), _np(k[:off[4]]), _np(v[:off[4]]), off[:5], M, 1 / math.sqrt(d))
+    _check_close(out[:4 * M], ref, dtype, f"cross masked {dtype} H={H} d={d}")
+
+
 def _random_shape(i):
     """Seeded random small workload: any dtype, head dim, ragged or fixed encoder
     lengths (including tails shorter than a key tile), beam counts off the tile
