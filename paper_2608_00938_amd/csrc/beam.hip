@@ -459,7 +459,7 @@ beam_scores_reg_kernel(const T* __restrict__ logits, const float* __restrict__ p
       const uint32_t h = sample_offset(m, smp.lp);
       uint16_t* out = smp.p + b * smp.stride + (int64_t)m * smp.per_row;
       if (m == (uint32_t)smp.M - 1 && lane < 3) out[smp.per_row + lane] = 0xfc00u;
-    clear_shared(smp.ws, b, m * 64 + lane, (uint32_t)smp.M * 64);
+      clear_shared(smp.ws, b, m * 64 + lane, (uint32_t)smp.M * 64);
       if constexpr (RUN) {
         // one element of every 2^(lp-3)-th run; the RPW rows of a wave share
         // out the eight elements, so that two (four, eight) remain to pick from
@@ -805,7 +805,7 @@ struct TopkOut {
 // The selected composites sh.list[0, n), n >= k or all there are, sorted best
 // first; the first min(n, k) are emitted.
 template <class Row>
-__device__ void sort_and_emit(TopkShared& sh, uint32_t n, int32_t k, int64_t out0, const Row& c,
+__device__ __forceinline__ void sort_and_emit(TopkShared& sh, uint32_t n, int32_t k, int64_t out0, const Row& c,
                               const TopkOut& out) {
   uint32_t n2 = 1;
   while (n2 < n) n2 <<= 1;
@@ -826,7 +826,7 @@ __device__ void sort_and_emit(TopkShared& sh, uint32_t n, int32_t k, int64_t out
 // equal steps of their range, then each candidate's place inside its bin from
 // the bin's other members.
 template <class Row>
-__device__ void rank_and_emit(TopkShared& sh, uint64_t (&v)[kGatherCap / kTopkThreads], uint32_t n,
+__device__ __forceinline__ void rank_and_emit(TopkShared& sh, uint64_t (&v)[kGatherCap / kTopkThreads], uint32_t n,
                               int32_t k, int64_t out0, const Row& c, const TopkOut& out) {
   constexpr int kPer = kGatherCap / kTopkThreads;
   const int tid = threadIdx.x;
@@ -939,7 +939,7 @@ __device__ __forceinline__ void load_run(const Row& c, uint32_t i, uint32_t N, f
 // Fills positions n .. k-1 with the candidates that are not above -inf: the
 // -inf ones by index, then the NaN ones by index.
 template <bool VEC8, class Row>
-__device__ void fill_dead(TopkShared& sh, uint32_t n, int32_t k, uint32_t N, int64_t out0,
+__device__ __forceinline__ void fill_dead(TopkShared& sh, uint32_t n, int32_t k, uint32_t N, int64_t out0,
                           const Row& c, const TopkOut& out) {
   for (int pass = 0; pass < 2 && n < (uint32_t)k; ++pass) {
     for (uint32_t i0 = 0; i0 < N && n < (uint32_t)k; i0 += 8 * kTopkThreads) {
@@ -999,7 +999,7 @@ __device__ __forceinline__ void digit_of_rank(TopkShared& sh, uint32_t want) {
 // latest the last digit does.  Bound by reading the entries, eight in flight per
 // thread, once per digit (at most six; crowded scores need two or three).
 template <class Entries>
-__device__ uint32_t narrow(TopkShared& sh, uint32_t n, int32_t k, const Entries& entry) {
+__device__ __forceinline__ uint32_t narrow(TopkShared& sh, uint32_t n, int32_t k, const Entries& entry) {
   constexpr int U = 8;
   constexpr uint32_t kStep = U * kTopkThreads;
   const int tid = threadIdx.x;
@@ -1055,7 +1055,7 @@ __device__ __forceinline__ void take_list(const TopkShared& sh, uint32_t n,
 // and 8 bits) over all the candidates, an index-ordered collection of the ties with
 // the k-th, and a bitonic sort.  Eight candidates per thread and step.
 template <bool VEC8, class Row>
-__device__ void exact_select(TopkShared& sh, int32_t k, uint32_t N, int64_t out0, const Row& c,
+__device__ __forceinline__ void exact_select(TopkShared& sh, int32_t k, uint32_t N, int64_t out0, const Row& c,
                              const TopkOut& out) {
   const int tid = threadIdx.x;
   uint32_t* hist = sh.bin_count;
@@ -1210,30 +1210,72 @@ topk_small_kernel(Src src, uint32_t N, int32_t k, TopkOut out) {
 
 // ---- more candidates: select, gather, final ----
 
+// Threshold of each request: the score above which about `want` samples lie, by
+// a histogram of the differences from ref in [-kBelow, kAbove).  A workgroup
+// takes kSelectSamples samples (one CU reads from beyond its L2 at some 20 GB/s,
+// so a sample of 256 KiB takes 27 us on one CU and 8 us on eight); the last one
+// of a request to finish sums the workgroups' histograms.  The want-th best of
+// the threads' own best samples bounds the threshold from below, so that only
+// the few samples above that are counted.  A request with fewer than `want`
+// samples in the window gathers everything above -inf, if that can fit.
+constexpr float kBelow = 112.0f, kAbove = 16.0f;
+constexpr uint32_t kSelectSamples = 16384;
+
+constexpr float kSelectInvW = (float)kHistBins / (kBelow + kAbove);
+// Bin of a sample.  A sample v below 0 was rounded up, from (v - q, v], q its fp16
+// step; bins that take their upper edge in and not their lower one hold that whole
+// range above the edge below, as edges are fp16 values from -64 up.
+constexpr float kEdge = 0x1p-14f;
+__device__ __forceinline__ int sample_bin(float x) { return step_bin(x, kEdge - kBelow, kSelectInvW); }
+__device__ __forceinline__ bool in_top_bin(float x) { return sample_bin(x) == kHistBins - 1; }
+
 // Samples of a request, four at a time as packed fp16 differences from ref(b):
 // as the score pass stored them, or one 32-candidate chunk of every 2^lp
 // consecutive ones (picked by a hash of the group index, so that neither a
 // row's token order nor the row length biases it), read from the candidates.
+// scores4: the scores of samples j .. j+3, -inf past the last, for samples that lie
+// so far above ref(b) that they meet in the top bin; the stored ones' may be those
+// of a neighbour, and are -inf below that bin (their scattered reads of the logits
+// are what such a pass costs).
+template <class Src>
 struct StoredSample {
+  Src src;
   const uint16_t* p;
   int64_t stride;
   uint32_t n;
-  const float* prev;
-  int32_t M;
+  int32_t lp;
+  FastDiv per_row;   // sample -> beam
   struct Row {
+    typename Src::Row c;
     const u32x2* p;
-    uint32_t n;
+    uint32_t n, samples_per_row;
+    int32_t lp;
+    FastDiv per_row;
+    __device__ __forceinline__ float at(uint32_t j) const {
+      if (j >= n) return -INFINITY;
+      const uint32_t m = per_row.div(j), v = ((j - m * samples_per_row) << lp) + sample_offset(m, lp);
+      return v < (uint32_t)c.V ? c[m * (uint32_t)c.V + v] : -INFINITY;
+    }
+    __device__ __forceinline__ void scores4(uint32_t j, float (&x)[4]) const {
+      const u32x2 w = load4(j, 0.f);
+      const f16x2 lo = __builtin_bit_cast(f16x2, w.x), hi = __builtin_bit_cast(f16x2, w.y);
+      const bool top[4] = {in_top_bin((float)lo.x), in_top_bin((float)lo.y), in_top_bin((float)hi.x),
+                           in_top_bin((float)hi.y)};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = top[e] ? at(j + e) : -INFINITY;
+    }
     // the score pass put -inf behind the last sample, up to a whole four
     __device__ __forceinline__ u32x2 load4(uint32_t j, float) const {
       const u32x2 w = p[min(j, n - 1) >> 2];
       return j < n ? w : u32x2{0xfc00fc00u, 0xfc00fc00u};   // -inf
     }
   };
-  __device__ __forceinline__ Row request(int64_t b, uint32_t) const {
-    return Row{(const u32x2*)(p + b * stride), n};
+  __device__ __forceinline__ Row request(int64_t b, uint32_t N) const {
+    return Row{src.request(b, N), (const u32x2*)(p + b * stride), n, ((uint32_t)src.V + (1u << lp) - 1) >> lp,
+               lp, per_row};
   }
   __device__ __forceinline__ float ref(const Row&, int64_t b, float*) const {
-    return sample_ref(prev + b * M, M);
+    return sample_ref(src.prev + b * src.M, src.M);
   }
 };
 template <class Src>
@@ -1254,6 +1296,10 @@ struct ChunkSample {
       const uint64_t i = index(j);
       return j < n && i < N ? c.nt((uint32_t)i) : -INFINITY;
     }
+    __device__ __forceinline__ void scores4(uint32_t j, float (&x)[4]) const {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = at(j + e);
+    }
     __device__ __forceinline__ u32x2 load4(uint32_t j, float ref) const {
       const uint64_t i = index(j);   // j a multiple of 4: one chunk
       float x[4];
@@ -1265,31 +1311,15 @@ struct ChunkSample {
   __device__ __forceinline__ Row request(int64_t b, uint32_t N) const {
     return Row{src.request(b, N), lp, n, N};
   }
-  // the best of the first samples, 0 if none is finite
+  // the best of 8 samples each from 128 chunks all over the request, 0 if none is
+  // finite
   __device__ __forceinline__ float ref(const Row& row, int64_t, float* scratch) const {
-    const float x = row.at(threadIdx.x);
+    const uint32_t chunk = (uint32_t)((uint64_t)(threadIdx.x >> 3) * (n >> 5) / 128);
+    const float x = row.at(32 * chunk + (threadIdx.x & 7));
     const float m = block_max(fabsf(x) < INFINITY ? x : -INFINITY, scratch);
     return m > -INFINITY ? m : 0.f;
   }
 };
-
-// Threshold of each request: the score above which about `want` samples lie, by
-// a histogram of the differences from ref in [-kBelow, kAbove).  A workgroup
-// takes kSelectSamples samples (one CU reads from beyond its L2 at some 20 GB/s,
-// so a sample of 256 KiB takes 27 us on one CU and 8 us on eight); the last one
-// of a request to finish sums the workgroups' histograms.  The want-th best of
-// the threads' own best samples bounds the threshold from below, so that only
-// the few samples above that are counted.  A request with fewer than `want`
-// samples in the window gathers everything above -inf, if that can fit.
-constexpr float kBelow = 112.0f, kAbove = 16.0f;
-constexpr uint32_t kSelectSamples = 16384;
-
-constexpr float kSelectInvW = (float)kHistBins / (kBelow + kAbove);
-// Bin of a sample.  A sample v below 0 was rounded up, from (v - q, v], q its fp16
-// step; bins that take their upper edge in and not their lower one hold that whole
-// range above the edge below, as edges are fp16 values from -64 up.
-constexpr float kEdge = 0x1p-14f;
-__device__ __forceinline__ int sample_bin(float x) { return step_bin(x, kEdge - kBelow, kSelectInvW); }
 
 // Samples j0 .. j0 + kSelectSamples - 1 (-inf past the last), kSampleLoads loads of
 // four per thread.
@@ -1354,6 +1384,31 @@ __device__ __forceinline__ void sample_hist(const Row& sample, uint32_t j0, floa
   }
   __syncthreads();
 }
+// Calls f(difference from ref) for all of a request's samples, a whole wave at a
+// time: in fp16, or (SCORES) of their scores in fp32.
+template <bool SCORES, class Row, class F>
+__device__ __forceinline__ void for_samples(const Row& sample, float ref, const F& f) {
+  if constexpr (SCORES) {
+    const uint32_t own = 4 * threadIdx.x;
+#pragma unroll 1
+    for (uint32_t j0 = 0; j0 < sample.n; j0 += 4 * kTopkThreads) {
+      float x[4];
+      sample.scores4(j0 + own, x);
+#pragma unroll 1
+      for (int e = 0; e < 4; ++e) f((e == 0 ? x[0] : e == 1 ? x[1] : e == 2 ? x[2] : x[3]) - ref);
+    }
+  } else {
+    for (uint32_t j0 = 0; j0 < sample.n; j0 += kSelectSamples) {
+      float x[kSampleLoads][4];
+      load_samples(sample, j0, ref, x);
+#pragma unroll
+      for (int u = 0; u < kSampleLoads; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f(x[u][e]);
+    }
+  }
+}
+
 // The threshold of a request whose samples, one of 2^lp, hist counts (complete):
 // the lower edge of the bin with the `want`-th best.  Where that bin is so crowded
 // that what is expected at or above it comes near the room for gathered candidates,
@@ -1364,45 +1419,70 @@ __device__ __forceinline__ void sample_hist(const Row& sample, uint32_t j0, floa
 // equal prefixes and N(0, s^2) logits, against the exact selection by one workgroup
 // for everything past the list: s = 0.3 3189 and 139 us, 0.1 2075 and 149, 0.02 2211
 // and 155; 5000 tokens over a floor 2222 and 270.
+// Scores far above ref (a few live beams, that ref's few prefixes missed, over dead
+// ones at -1e9) meet in the top bin's last cut, and the slack of so large a ref may
+// reach below all the bins: the differences are then taken anew, from the best
+// sample, for the samples of the top bin, which are enough.  16 x 1000 x 509 fp32, k = 1024, one beam in 20 live: 1218 us by the exact
+// selection, 49 so; two calls at 4 x 4096 x 4096, k = 4096: 13679 and 185.
 template <class Row>
 __device__ __forceinline__ float threshold(const Row& sample, uint32_t* hist, uint32_t want, int32_t lp,
-                                           float ref, uint32_t room, uint32_t* scan, int32_t* ipar) {
-  const int bin = boundary_bin(hist, want, scan, ipar);
-  uint32_t above = (uint32_t)ipar[1];
-  const bool crowded = ((uint64_t)(above + (uint32_t)ipar[2]) << lp) > min(room / 4 * 3, 3u * kGatherCap);
-  float edge = (float)bin / kSelectInvW - kBelow;
-  const float slack = fabsf(ref) * 0x1p-22f;   // the rounding of the differences
-  if (!crowded)   // below -64 an fp16 step is wider than a bin
-    return bin == 0 ? -FLT_MAX : ref + (edge < -64.f ? edge - 1.0f / kSelectInvW : edge) - slack;
-  // the outer bins, open below and above, in as many steps of a bin's width
-  const float inv_w = bin == 0 || bin == kHistBins - 1 ? kSelectInvW : kSelectInvW * (float)kHistBins;
-  if (bin == 0) edge -= kBelow + kAbove;
-  __syncthreads();
-  clear_bins(hist);
-  __syncthreads();
-  for (uint32_t j0 = 0; j0 < sample.n; j0 += kSelectSamples) {
-    float x[kSampleLoads][4];
-    load_samples(sample, j0, ref, x);
-#pragma unroll
-    for (int u = 0; u < kSampleLoads; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        hist_add(hist, step_bin(x[u][e], edge, inv_w), x[u][e] > -INFINITY && sample_bin(x[u][e]) == bin);
+                                           float ref, uint32_t room, uint32_t* scan, float* fscan,
+                                           int32_t* ipar) {
+  constexpr int kTop = kHistBins - 1;
+  for (bool anew = false;; anew = true) {
+    const int bin = boundary_bin(hist, want, scan, ipar);
+    uint32_t above = (uint32_t)ipar[1];
+    const bool crowded = ((uint64_t)(above + (uint32_t)ipar[2]) << lp) > min(room / 4 * 3, 3u * kGatherCap);
+    float edge = (float)bin / kSelectInvW - kBelow;
+    const float slack = fabsf(ref) * 0x1p-22f;   // the rounding of the differences
+    bool far = !anew && bin == kTop && slack > 1.0f;
+    if (!crowded && !far)   // below -64 an fp16 step is wider than a bin
+      return bin == 0 ? -FLT_MAX : ref + (edge < -64.f ? edge - 1.0f / kSelectInvW : edge) - slack;
+    if (!far) {
+      // the outer bins, open below and above, in as many steps of a bin's width
+      const float inv_w = bin == 0 || bin == kTop ? kSelectInvW : kSelectInvW * (float)kHistBins;
+      if (bin == 0) edge -= kBelow + kAbove;
+      __syncthreads();
+      clear_bins(hist);
+      __syncthreads();
+      const auto cut = [&](float x) __attribute__((always_inline)) {
+        hist_add(hist, step_bin(x, edge, inv_w), x > -INFINITY && sample_bin(x) == bin);
+      };
+      if (anew) for_samples<true>(sample, ref, cut);
+      else for_samples<false>(sample, ref, cut);
+      __syncthreads();
+      const int part = boundary_bin(hist, want - above, scan, ipar);
+      far = !anew && bin == kTop && part == kTop;
+      if (!far) {
+        above += (uint32_t)ipar[1];
+        const bool fits = ((uint64_t)(above + (uint32_t)ipar[2]) << lp) <= room || above == 0u;
+        if (fits && bin == 0 && part == 0) return -FLT_MAX;
+        // a sample v < 0 stands for (v - q, v], one of 0 and above for [v, v + q)
+        edge += (float)part / inv_w;
+        const float q = fmaxf(__uint_as_float(__float_as_uint(edge) & 0x7f800000u) * 0x1p-10f, 0x1p-24f);
+        return fits ? ref + edge - (edge < 0.f ? q : 0.f) - slack
+                    : ref + edge + 1.0f / inv_w + (edge < 0.f ? 0.f : q);
+      }
+    }
+    float best = -INFINITY;
+    for_samples<true>(sample, 0.f, [&](float x) __attribute__((always_inline)) {
+      best = fmaxf(best, fabsf(x) < INFINITY ? x : -INFINITY);
+    });
+    best = block_max(best, fscan);
+    if (!(best > -INFINITY)) return -FLT_MAX;
+    ref = best;
+    clear_bins(hist);
+    __syncthreads();
+    for_samples<true>(sample, ref, [&](float x) __attribute__((always_inline)) {
+      hist_add(hist, sample_bin(x), x > -INFINITY);
+    });
+    __syncthreads();
   }
-  __syncthreads();
-  const int part = boundary_bin(hist, want - above, scan, ipar);
-  above += (uint32_t)ipar[1];
-  const bool fits = ((uint64_t)(above + (uint32_t)ipar[2]) << lp) <= room || above == 0u;
-  __syncthreads();
-  if (fits && bin == 0 && part == 0) return -FLT_MAX;
-  // a sample v < 0 stands for (v - q, v], one of 0 and above for [v, v + q)
-  edge += (float)part / inv_w;
-  const float q = fmaxf(__uint_as_float(__float_as_uint(edge) & 0x7f800000u) * 0x1p-10f, 0x1p-24f);
-  return fits ? ref + edge - (edge < 0.f ? q : 0.f) - slack : ref + edge + 1.0f / inv_w + (edge < 0.f ? 0.f : q);
 }
 
+// Two workgroups per CU.
 template <class Smp>
-__global__ void __launch_bounds__(kTopkThreads)
+__global__ void __launch_bounds__(kTopkThreads, 8)
 topk_select_kernel(Smp smp, uint32_t N, uint32_t want, int32_t lp, TopkWs ws) {
   __shared__ uint32_t hist[kHistBins];
   __shared__ uint32_t scan[64];
@@ -1428,7 +1508,7 @@ topk_select_kernel(Smp smp, uint32_t N, uint32_t want, int32_t lp, TopkWs ws) {
     for (int i = tid; i < kHistBins; i += kTopkThreads) hist[i] = load_shared(&sum[i]);
     __syncthreads();
   }
-  const float thr = threshold(sample, hist, want, lp, ref, ws.gather_room(), scan, ipar);
+  const float thr = threshold(sample, hist, want, lp, ref, ws.gather_room(), scan, fscan, ipar);
   if (tid == 0) {
     info[0] = __float_as_int(thr);
     info[1] = 0;   // gathered count
@@ -1723,7 +1803,7 @@ constexpr uint32_t kFusedMaxPerRequest = 32, kFusedMaxBlocks = 256;
 
 template <class T, bool RUN>
 __global__ void __launch_bounds__(kTopkThreads)
-topk_fused_rows_kernel(CandFromLogits<T> src, StoredSample smp, const float* __restrict__ row_max,
+topk_fused_rows_kernel(StoredSample<CandFromLogits<T>> smp, const float* __restrict__ row_max,
                        int32_t ll, uint32_t N, uint32_t want, int32_t lp, int32_t k, TopkWs ws, TopkOut out) {
   constexpr int kWaves = kTopkThreads / 64;
   __shared__ TopkShared sh;
@@ -1731,6 +1811,7 @@ topk_fused_rows_kernel(CandFromLogits<T> src, StoredSample smp, const float* __r
   __shared__ uint8_t rows[kWaves][64];
   typedef GatherStage<kFusedStage> Stage;
   static_assert(sizeof(Stage) + kFusedQueue * sizeof(uint32_t) <= sizeof(sh.list), "in the ranking's list");
+  const CandFromLogits<T>& src = smp.src;
   Stage& st = *(Stage*)sh.list;
   uint32_t* const queue = (uint32_t*)((char*)sh.list + sizeof(Stage));
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1740,7 +1821,7 @@ topk_fused_rows_kernel(CandFromLogits<T> src, StoredSample smp, const float* __r
   const auto sample = smp.request(b, N);
   const float ref = smp.ref(sample, b, nullptr);
   sample_hist(sample, 0, ref, want, sh.bin_count, sh.scan, sh.ipar);
-  const float thr = threshold(sample, sh.bin_count, want, lp, ref, ws.gather_room(), sh.scan, sh.ipar);
+  const float thr = threshold(sample, sh.bin_count, want, lp, ref, ws.gather_room(), sh.scan, sh.fscan, sh.ipar);
   const Gathered<true> to(ws, b);
   const auto c = src.request(b, N);
   gather_rows<RUN, kTopkThreads, kFusedQueue, true>(c, m0, bound, thr, ll, st, queue, n_queue, rows[wave], to);
@@ -1939,12 +2020,13 @@ static hipError_t launch_step(const void* logits, const float* prev, const uint3
   int ll = 0;
   while (ll < 6 && (E << ll) < V) ++ll;
   launch_scores_mode<false>(logits, prev, mask, nullptr, row_max, lse, R, V, bf16, smp, stream);
-  const StoredSample stored{smp.p, smp.stride, smp.per_row * (uint32_t)M, prev, M};
+  const StoredSample<CandFromLogits<T>> stored{src, smp.p, smp.stride, smp.per_row * (uint32_t)M, smp.lp,
+                                               FastDiv(smp.p != nullptr ? smp.per_row : 1u)};
   const uint32_t fused_blocks = ((uint32_t)M + kFusedRows - 1) / kFusedRows;
   if (smp.p != nullptr && stored.n <= kSelectSamples && fused_blocks <= kFusedMaxPerRequest &&
       fused_blocks * (uint32_t)B <= kFusedMaxBlocks) {
     hipLaunchKernelGGL((topk_fused_rows_kernel<T, RUN>), dim3(fused_blocks, (unsigned)B), dim3(kTopkThreads),
-                       0, stream, src, stored, row_max, ll, N, samples_wanted(k, smp.lp), smp.lp, k, ws, out);
+                       0, stream, stored, row_max, ll, N, samples_wanted(k, smp.lp), smp.lp, k, ws, out);
     return hipGetLastError();
   }
   if (smp.p != nullptr)
