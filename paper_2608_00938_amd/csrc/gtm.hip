@@ -263,8 +263,10 @@ hipError_t launch_gtm_mask(const grace_gtm_index& index, const grace_gtm_user& u
   // Beams per workgroup, as many as leave a chip full of workgroups: 2048 (eight
   // per CU), or 1024 of few beams, where starting a workgroup (5 ns) counts (8 x
   // 1024 beams at level 2: 7.4 us with 1024, 10.8 with 2048; 64 x 1024 at level 1:
-  // 58 and 38).  Their filter words have to fit.
-  const int32_t W = (index.vocab + 31) / 32, fill = R >= 32768 ? 2048 : 1024;
+  // 58 and 38), or 640 of fewer still, which keeps the grid within 1280 (3300 and
+  // 1561 beams at level 3: 8.9 and 8.6 us with 1024, 6.4 and 6.0 with 640; 13000 at
+  // level 1: 15.7 and 28).  Their filter words have to fit.
+  const int32_t W = (index.vocab + 31) / 32, fill = R >= 32768 ? 2048 : (R >= 4096 ? 1024 : 640);
   int32_t beams = 1;
   while (beams < kGtmMaxBeams && R / (2 * beams) >= fill && 2 * beams * W <= kGtmWordsCap) beams *= 2;
   const int64_t blocks = ((int64_t)R + beams - 1) / beams;

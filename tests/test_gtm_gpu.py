@@ -69,8 +69,8 @@ def test_gtm_mask_sampled_parity_medium(gpu, medium, level):
         assert np.array_equal(got[r], want), f"row {r}"
 
 
-@pytest.mark.parametrize("V,B,M", [(512, 8, 1), (512, 3, 2731), (512, 5, 27001), (4096, 2, 65537)],
-                         ids=["beam_per_group", "groups_of_4", "groups_of_64", "words_limit"])
+@pytest.mark.parametrize("V,B,M", [(512, 8, 1), (512, 3, 431), (512, 3, 2731), (512, 5, 27001), (4096, 2, 65537)],
+                         ids=["beam_per_group", "groups_of_2", "groups_of_8", "groups_of_64", "words_limit"])
 def test_gtm_mask_group_sizes(gpu, V, B, M):
     """Beams per workgroup from 1 to 64, workgroups that straddle requests, the
     root's many children beside leaves and dead beams: rows at the request
