@@ -417,8 +417,8 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // ---------------------------------------------------------------------------
 // MB: 32-beam blocks per wave.  Two where they fit the registers (d = 32, 64); one
 // halves a workgroup's beams to 128, for grids that then have at most a workgroup
-// per CU (8 x 512 x 8 x 64: 128 -> 256 workgroups, 9.1 -> 7.2 us at 256 keys, 21.4 ->
-// 16.2 at 1024) and for requests of at most 128 beams (128 x 64 x 8 x 64: 20.7 -> 18.8).
+// per CU (8 x 512 x 8 x 64: 128 -> 256 workgroups, 9.1 -> 7.1 us at 256 keys, 21.4 ->
+// 16.0 at 1024) and for requests of at most 128 beams (128 x 64 x 8 x 64: 20.7 -> 18.2).
 // With more workgroups two blocks per wave win, as each K or V fragment read from
 // LDS then feeds two products (16 x 1024 x 8 x 64, 256 keys: 14.5 against 18.4).
 template <int D, int MB = (D == 128 ? 1 : 2)>
@@ -436,6 +436,7 @@ struct Cfg {
   static constexpr int kSlots = kTileN * kCPR;
   static constexpr int kLoads = kSlots / kThreads;     // loads per thread per tile and tensor
   static constexpr int kTileBytes = kSlots * 16;
+  static constexpr int kQLoads = kMB * 32 * kRowBytes / 1024;   // loads per wave for its beams' queries
   static constexpr int kNBuf = 4;
   static constexpr int kLdsBytes = 2 * kNBuf * kTileBytes;
   static constexpr int kUnits = 2 * kMB;               // (16-key chunk, beam block) pairs per step
@@ -443,6 +444,7 @@ struct Cfg {
   static constexpr float kShiftHi = 32.0f;
   static constexpr float kShiftLo = -64.0f;
   static_assert(kSlots % kThreads == 0 && (kKS * kMB) % kUnits == 0, "even split");
+  static_assert(kQLoads * 1024 <= kTileBytes, "a wave's queries fit the tile buffer that stages them");
   static_assert(kLoads * 2 <= 8, "wait_vmem_upto covers up to eight loads per tile");
   __device__ __forceinline__ static int slot(int key, int chunk) {
     return key * kCPR + (chunk ^ tile_swizzle<D>(key));
@@ -585,7 +587,7 @@ cross_attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
     const uint32_t q_lds = __builtin_amdgcn_readfirstlane(lds_addr(qbuf));
     const int last = M - 1 - m_base;
 #pragma unroll
-    for (int i = 0; i < C::kTileBytes / 1024; ++i) {
+    for (int i = 0; i < C::kQLoads; ++i) {
       const int sl = i * 64 + lane;
       const int row = sl / C::kCPR;
       const int chunk = (sl % C::kCPR) ^ tile_swizzle<D>(row);
