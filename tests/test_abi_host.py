@@ -407,10 +407,23 @@ def test_binding_raises_without_library(monkeypatch, tmp_path):
         G.library()
 
 
-def test_host_tensors_are_refused():
+def test_host_tensors_are_refused(monkeypatch):
     """The stream lookup by raw handle has none for a tensor in host memory: the
-    call raises before it reaches the library."""
+    call raises before it reaches the library, and no handle is asked for."""
     torch = pytest.importorskip("torch")
+    calls, asked = [], []
+
+    class Library:
+        def __getattr__(self, name):
+            return lambda *args: calls.append(name) or 0
+
+    def no_stream(device=None):
+        raise ValueError(f"Expected a cuda device, but got: {device}")
+
+    monkeypatch.setattr(G, "library", Library)
+    monkeypatch.setattr(G, "_raw_stream", lambda index: asked.append(index) or 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", no_stream)
     q = torch.zeros((4, 2, 64))
-    with pytest.raises((ValueError, RuntimeError)):
+    with pytest.raises(ValueError, match="cuda device"):
         G.grace_cross_attn(q, q, q, torch.tensor([0, 4], dtype=torch.int32), 4)
+    assert calls == [] and asked == []
