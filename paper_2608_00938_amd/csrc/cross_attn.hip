@@ -84,6 +84,11 @@ __device__ __forceinline__ void work_item(uint32_t i, const WorkMap& w, int32_t&
   h = (int32_t)((p - r * w.hpx) * WorkMap::kXcds + x);
 }
 
+__device__ __forceinline__ void check_item(const WorkMap& w, int32_t mt, int32_t b, int32_t h) {
+  if (threadIdx.x == 0)
+    GRACE_DCHECK((uint32_t)b < w.B && (uint32_t)h < w.H && (uint32_t)mt < w.n_mt, kDbgRow);
+}
+
 // ---------------------------------------------------------------------------
 // fp32 kernel.  Each wave owns 32 beams and computes, per 32-key tile,
 //   S^T = K Q^T       A: lane = key l % 32, dims 8j + 4 (l / 32) + 0..3 of step j;
@@ -133,6 +138,7 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
   __shared__ float ml_lds[kF32Waves][2][32];
   int32_t mt, b, h;
   work_item(blockIdx.x, map, mt, b, h);
+  check_item(map, mt, b, h);
   int32_t o0, L;
   request_span(off, b, sum_L, o0, L);
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
@@ -166,6 +172,7 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
     for (int i = 0; i < kJ; ++i) {
       // beams past M repeat the last, never stored
       const int32_t m = min(m0 + i * kRowsPerPass + lane / kLanesPerRow, M - 1);
+      GRACE_DCHECK(0 <= m && m < M, kDbgRow);
       qf[i] = *(const f32x4_a4*)(q + ((int64_t)b * M + m) * E + h * D + 4 * (lane % kLanesPerRow));
     }
     // keys past L repeat the last and get weight 0
@@ -190,6 +197,7 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float* const row = vh + (int64_t)(t0 + 8 * (r >> 2) + (r & 3)) * E;   // uniform
+          GRACE_DCHECK(o0 + t0 + 8 * (r >> 2) + (r & 3) + 4 * hi < sum_L, kDbgRow);
 #pragma unroll
           for (int db = 0; db < kDB; ++db) vf[r][db] = row[lane_off + 32 * db];
         }
@@ -198,6 +206,7 @@ cross_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
         for (int r = 0; r < 16; ++r) {
           const int32_t key = min(t0 + 8 * (r >> 2) + 4 * hi + (r & 3), L - 1);
           const float* const row = vh + (int64_t)key * E + l32;
+          GRACE_DCHECK(0 <= key && o0 + key < sum_L, kDbgRow);
 #pragma unroll
           for (int db = 0; db < kDB; ++db) vf[r][db] = row[32 * db];
         }
@@ -485,8 +494,7 @@ cross_attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 
   int32_t mt, b, h;
   work_item(blockIdx.x, map, mt, b, h);
-  if (threadIdx.x == 0)
-    GRACE_DCHECK(0 <= b && b < (int32_t)map.B && 0 <= h && h < H && 0 <= mt && mt < (int32_t)map.n_mt, kDbgRow);
+  check_item(map, mt, b, h);
   int32_t o0, L;
   request_span(off, b, sum_L, o0, L);
 
@@ -1100,6 +1108,7 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
 
   int32_t mt, b, h;
   work_item(blockIdx.x, map, mt, b, h);
+  check_item(map, mt, b, h);
   int32_t o0, L;
   request_span(off, b, sum_L, o0, L);
   const int lane = threadIdx.x & 63, l32 = lane & 31, hi = lane >> 5;
@@ -1144,6 +1153,7 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
     for (int i = 0; i < kLoads; ++i) {
       const int sl = i * 64 + lane, row = sl / C::kCPR;
       const int chunk = (sl % C::kCPR) ^ tile_swizzle<D>(row);
+      GRACE_DCHECK(m0 < M && m0 + min(row, M - 1 - m0) < M, kDbgRow);
       load_to_lds<true>(qbase, (uint32_t)(min(row, M - 1 - m0) * E + chunk * 8) * 2u,
                         lds0 + 2 * kTileBytes + i * 1024);
     }

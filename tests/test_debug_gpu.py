@@ -16,6 +16,7 @@ import numpy as np
 import pytest
 import torch
 
+from cross_launch import bf16_kernel, f32_splits
 from paper_2608_00938_amd import grace as G
 from paper_2608_00938_amd import workloads as W
 
@@ -60,13 +61,23 @@ CASES = [
                          parents="zipf", zipf_s=1.2)),
     ("ragged_d32", dict(dtype="bf16", B=5, M=70, H=3, d=32, steps=4, L_lo=1, L_hi=90)),
     ("f32_d128", dict(dtype="f32", B=2, M=40, H=2, d=128, steps=3, L_lo=5, L_hi=60)),
+    # grids large enough that the keys are not split over a workgroup's waves
+    ("whole_d64", dict(dtype="bf16", B=3, M=300, H=30, d=64, steps=2, L_lo=1, L_hi=130)),
+    ("whole_d128", dict(dtype="bf16", B=2, M=513, H=8, d=128, steps=2, L_lo=63, L_hi=200)),
+    ("half_d32", dict(dtype="bf16", B=5, M=70, H=72, d=32, steps=2, L_lo=1, L_hi=90)),
+    ("f32_two", dict(dtype="f32", B=8, M=130, H=22, d=32, steps=2, L_lo=1, L_hi=70)),
+    ("f32_one", dict(dtype="f32", B=8, M=387, H=16, d=64, steps=2, L_lo=1, L_hi=70)),
 ]
+# the cross-attention kernel that each is there for
+KERNELS = ("split", "split", "split", "split", 4, "whole", "whole", "half", 2, 1)
 
 
 @pytest.mark.parametrize("fused", [False, True], ids=["split", "fused"])
 @pytest.mark.parametrize("name,kw", CASES, ids=[c[0] for c in CASES])
 def test_debug_build_clean_decode(gpu, monkeypatch, name, kw, fused):
     wl = W.WORKLOADS[name] if kw is None else W.custom(name=name, **kw)
+    kernel = bf16_kernel(wl.B, wl.M, wl.H, wl.d) if wl.dtype == "bf16" else f32_splits(wl.B, wl.M, wl.H)
+    assert kernel == KERNELS[CASES.index((name, kw))]
     _log(f"[debug build] {wl.name} fused={fused}")
     release = _decode(wl, 3, gpu, fused)
     dbg = G.debug_library()
