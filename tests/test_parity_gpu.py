@@ -20,6 +20,7 @@ import pytest
 import torch
 
 import oracle
+from cross_launch import bf16_kernel, f32_splits
 from paper_2608_00938_amd import grace as G
 from paper_2608_00938_amd import workloads as W
 
@@ -277,9 +278,9 @@ def test_paper_shape_sampled_parity(gpu, fused):
 
 EDGE = [
     # ragged tails: beams not a multiple of the 256-beam tile, keys not of the 64-token tile
-    dict(dtype="bf16", B=3, M=300, H=3, d=64, steps=3, L_lo=1, L_hi=130),
+    dict(dtype="bf16", B=3, M=300, H=30, d=64, steps=3, L_lo=1, L_hi=130),
     dict(dtype="bf16", B=2, M=17, H=1, d=32, steps=4, L_lo=60, L_hi=70),
-    dict(dtype="bf16", B=2, M=513, H=2, d=128, steps=5, L_lo=63, L_hi=200),
+    dict(dtype="bf16", B=2, M=513, H=8, d=128, steps=5, L_lo=63, L_hi=200),
     dict(dtype="f32", B=3, M=70, H=2, d=64, steps=3, L_lo=1, L_hi=100),
     dict(dtype="f32", B=1, M=5, H=3, d=128, steps=2, L=33),
     dict(dtype="f32", B=2, M=9, H=1, d=32, steps=8, L=1),
@@ -292,8 +293,8 @@ EDGE = [
     dict(dtype="bf16", B=9, M=200, H=8, d=128, steps=2, L_lo=30, L_hi=260),
     # d = 64 with more than 256 beams: several 256-beam tiles per (request, head),
     # the last one partly past M, ragged tails, single-tile requests
-    dict(dtype="bf16", B=3, M=700, H=8, d=64, steps=2, L_lo=1, L_hi=200),
-    dict(dtype="bf16", B=2, M=1536, H=2, d=64, steps=2, L_lo=60, L_hi=400, parents="zipf", zipf_s=1.1),
+    dict(dtype="bf16", B=3, M=700, H=16, d=64, steps=2, L_lo=1, L_hi=200),
+    dict(dtype="bf16", B=2, M=1536, H=12, d=64, steps=2, L_lo=60, L_hi=400, parents="zipf", zipf_s=1.1),
 ]
 
 
@@ -301,6 +302,8 @@ EDGE = [
 @pytest.mark.parametrize("i", range(len(EDGE)))
 def test_edge_shapes_full_parity(gpu, i, fused):
     kw = dict(EDGE[i])
+    if i in (0, 2, 11, 12):   # those that mean the tiles of whole workgroups
+        assert bf16_kernel(kw["B"], kw["M"], kw["H"], kw["d"]) == "whole"
     kw.setdefault("parents", "uniform")
     wl = W.custom(name=f"edge{i}", **kw)
     _log(f"[parity edge] {wl} fused={fused}")
@@ -312,14 +315,16 @@ def test_edge_shapes_full_parity(gpu, i, fused):
 
 
 @pytest.mark.parametrize("d", [32, 64, 128])
-@pytest.mark.parametrize("B,M,H", [(5, 33, 3), (8, 130, 12), (8, 387, 16)], ids=["split4", "split2", "whole"])
-def test_cross_f32_key_splits(gpu, B, M, H, d):
+@pytest.mark.parametrize("B,M,H,ns", [(5, 33, 3, 4), (8, 130, 22, 2), (8, 387, 16, 1)],
+                         ids=["split4", "split2", "whole"])
+def test_cross_f32_key_splits(gpu, B, M, H, ns, d):
     """The fp32 kernel with the keys of a beam group split over four, two or one
     of a workgroup's waves, against the fp64 oracle: lengths from none over a
     single key to several tiles (so that waves run out of tiles), beam counts off
     the 32-beam group, operands off the 16-byte alignment, and scores large enough
     that a maximum is needed.  Tolerance: fp32 rounding of sums of up to 200 terms
     and of exp2 arguments of magnitude up to 100 (2^-24 * 100 = 6e-6 relative)."""
+    assert f32_splits(B, M, H) == ns
     rng = np.random.default_rng(B * M + d)
     lengths = np.array(([0, 1, 31, 32, 33, 64, 130, 200] * 2)[:B])
     off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
@@ -358,14 +363,16 @@ def test_cross_bf16_both_kernels(gpu, H, d, kind):
     """The kernel that splits the keys over a workgroup's waves (grids that fit the
     chip at once) and the one that does not, at 128 (up to 256 workgroups) and
     256 beams per workgroup, on the same kinds of input: lengths
-    from none over a single key to several tiles of every wave, a beam count off
-    the tiles; ordinary scores, scores that need the exponent shift (wide),
+    from none over a single key and a whole tile to several tiles of every wave, a
+    beam count off the tiles; ordinary scores, scores that need the exponent shift (wide),
     scores that need it in some 32-key tiles only, so that the waves disagree
     (steps), and all far below zero (tiny)."""
-    lengths = [0, 1, 31, 33, 64, 97, 300] if H == 2 else [300, 1, 97]
+    lengths = [0, 1, 31, 33, 64, 97, 300] if H == 2 else [300, 1, 0, 64]
     B, M = len(lengths), 130 if H == 2 else 300
     if H == 20 and d == 32:                   # too many workgroups to split: few beams
         H, M = 90, 128
+    kernel = bf16_kernel(B, M, H, d)
+    assert kernel == ("split" if H == 2 else "whole" if d == 128 or H == 48 else "half")
     off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
     g = torch.Generator().manual_seed(700 + d + H)
     q = torch.randn((B * M, H, d), generator=g)
@@ -387,8 +394,8 @@ def test_cross_bf16_both_kernels(gpu, H, d, kind):
     _check_close(_np(out), ref, "bf16", f"cross H={H} d={d} {kind}")
 
 
-@pytest.mark.parametrize("dtype,H", [("bf16", 2), ("bf16", 48), ("f32", 2), ("f32", 48)],
-                         ids=["bf16_split", "bf16_whole", "f32_split", "f32_whole"])
+@pytest.mark.parametrize("dtype,H", [("bf16", 2), ("bf16", 48), ("f32", 2), ("f32", 24), ("f32", 48)],
+                         ids=["bf16_split", "bf16_whole", "f32_split", "f32_split2", "f32_whole"])
 @pytest.mark.parametrize("d", [32, 64, 128])
 def test_cross_masked_key_tiles(gpu, d, dtype, H):
     """Keys whose scores overflow to -inf (the type's lowest value in a key, as a
@@ -398,6 +405,8 @@ def test_cross_masked_key_tiles(gpu, d, dtype, H):
     lengths = [200, 130, 64, 97, 70]
     masked = [np.r_[32:64, 160:192], np.r_[0:128], np.r_[0:32], np.r_[0:96], np.r_[0:70]]
     B, M = len(lengths), 40 if H == 2 else 300
+    assert (bf16_kernel(B, M, H, d) == ("split" if H == 2 else "whole") if dtype == "bf16"
+            else f32_splits(B, M, H) == {2: 4, 24: 2, 48: 1}[H])
     off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
     g = torch.Generator().manual_seed(900 + d)
     q, k, v = (torch.randn((n, H, d), generator=g).to(W.TORCH_DTYPES[dtype])
@@ -429,6 +438,8 @@ def _random_shape(i):
         kw.update(parents="zipf", zipf_s=float(rng.uniform(0.8, 1.6)))
     else:
         kw.update(parents="uniform")
+    while i % 4 == 1 and bf16_kernel(kw["B"], kw["M"], kw["H"], d) == "split":
+        kw["H"] += 1   # enough heads for the kernel that does not split the keys
     return kw
 
 
@@ -625,16 +636,31 @@ def _extreme_case(gpu, kind, B=3, M=96, H=2, d=64, L=200, seed=13):
     return q, k, v, off
 
 
-@pytest.mark.parametrize("kind,M", [("huge", 96), ("tiny", 96), ("huge", 520), ("tiny", 520)])
-def test_cross_attn_extreme_scores_take_the_safe_pass(gpu, kind, M):
+def _cross_many_heads(gpu, q, k, v, off, M, H, kernel):
+    """Cross-attention with the inputs' heads repeated to H of them, so that the
+    grid is one of `kernel`; the repeated heads agree bit for bit, and the first
+    ones are returned."""
+    h, d = q.shape[1:]
+    B = off.numel() - 1
+    assert H % h == 0 and bf16_kernel(B, M, H, d) == kernel
+    many = [x.to(gpu).repeat(1, H // h, 1).contiguous() for x in (q, k, v)]
+    out = G.grace_cross_attn(*many, off.to(gpu), M)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out[:, :h].repeat(1, H // h, 1))
+    return out[:, :h]
+
+
+@pytest.mark.parametrize("kind,M,H,kernel", [(kind, *s) for kind in ("huge", "tiny") for s in
+                                             ((96, 2, "split"), (96, 60, "half"), (520, 18, "whole"))])
+def test_cross_attn_extreme_scores_take_the_safe_pass(gpu, kind, M, H, kernel):
     """Scores whose exp2 sums leave [2^-100, 2^64] fail the fast pass's check;
     the workgroup's safe pass (exponent shift) still matches the fp64 oracle
-    (M = 520: three 256-beam tiles, the last one mostly past M)."""
+    (M = 520: three 256-beam tiles, the last one mostly past M), as does the
+    kernel that splits the keys, which has that pass only."""
     q, k, v, off = _extreme_case(gpu, kind, M=M)
     M = q.shape[0] // (off.numel() - 1)
-    _log(f"[cross extreme] {kind}")
-    out = G.grace_cross_attn(q.to(gpu), k.to(gpu), v.to(gpu), off.to(gpu), M)
-    torch.cuda.synchronize()
+    _log(f"[cross extreme] {kind} {kernel}")
+    out = _cross_many_heads(gpu, q, k, v, off, M, H, kernel)
     ref = oracle.cross_attn(_np(q), _np(k), _np(v), off.numpy(), M, 1 / 8)
     _check_close(_np(out), ref, "bf16", f"cross {kind}")
 
@@ -665,8 +691,7 @@ def test_cross_attn_wide_scores(gpu, d, std, M):
     q, k, v, off = _wide_case(200 + d + int(10 * std) + M, B=3, M=M, H=2, d=d, L_lo=1, L_hi=300,
                               std=std)
     _log(f"[cross wide] d={d} std={std} M={M} L={np.diff(off.numpy()).tolist()}")
-    out = G.grace_cross_attn(q.to(gpu), k.to(gpu), v.to(gpu), off.to(gpu), M)
-    torch.cuda.synchronize()
+    out = _cross_many_heads(gpu, q, k, v, off, M, 36, "whole")
     ref = oracle.cross_attn(_np(q), _np(k), _np(v), off.numpy(), M, 1 / math.sqrt(d))
     _check_close(_np(out), ref, "bf16", f"cross wide d={d} std={std}")
 
@@ -690,8 +715,7 @@ def test_cross_attn_near_tied_large_scores(gpu, d, M):
     q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
     off = torch.arange(0, B * L + 1, L, dtype=torch.int32)
     _log(f"[cross near-tie] d={d} M={M}")
-    out = G.grace_cross_attn(q.to(gpu), k.to(gpu), v.to(gpu), off.to(gpu), M)
-    torch.cuda.synchronize()
+    out = _cross_many_heads(gpu, q, k, v, off, M, 104, "whole")
     ref, probs = oracle.cross_attn(_np(q), _np(k), _np(v), off.numpy(), M, 1 / math.sqrt(d),
                                    return_probs=True)
     # the case is what it claims: no key of a row holds most of the weight
