@@ -54,7 +54,9 @@ __device__ __forceinline__ void request_span(const int32_t* off, int32_t b, int3
 // one XCD, whose L2 then serves that head's K/V to all of them.
 //
 // The divisors are the launch's own: as plain divisions they took some 1000
-// cycles of every workgroup before its first load.
+// cycles of every workgroup before its first load (64 x 4096: 1.926e6 -> 1.902e6
+// cycles per XCD; the other workgroup on the CU covers them, and calls side by side
+// show no difference in time).
 struct WorkMap {
   static constexpr uint32_t kXcds = 8;
   uint32_t grid, n_mt, H, hpx, B, shift;   // hpx: heads per XCD and request, 0 where H % 8 != 0
@@ -1097,11 +1099,11 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
                              uint16_t* __restrict__ out, WorkMap map, int32_t M, int32_t H,
                              int32_t sum_L, float c) {
   using C = Cfg<D>;
-  constexpr int NS = 4, MB = 1;                   // waves; 32-beam blocks
+  constexpr int NS = 4;                         // waves
   constexpr int kTileBytes = 32 * C::kRowBytes;
   constexpr int kLoads = kTileBytes / 1024;       // loads per wave, tile and tensor
   constexpr int kWaveBytes = 4 * kTileBytes;      // two buffers of K and V
-  constexpr int kRows = MB * 32, kStride = D + 4; // floats per beam row of a partial O
+  constexpr int kRows = 32, kStride = D + 4;    // beams; floats per beam row of a partial O
   constexpr int kLdsBytes = NS * (kWaveBytes > kRows * kStride * 4 ? kWaveBytes : kRows * kStride * 4);
   __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
   __shared__ float part_shift[NS][kRows], part_l[NS][kRows];
@@ -1146,7 +1148,6 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
   // Queries as whole rows into the K part of buffer 1 (the second tile's, issued
   // after they are read), then the first tile.  B of S^T: 8 consecutive d of beam
   // l32 per 16-wide step; beams past M repeat the last, never stored.
-  static_assert(MB == 1, "32 query rows fill one K tile");
   {
     const uint16_t* const qbase = q + __builtin_amdgcn_readfirstlane((b * M + m0) * E + h * D);
 #pragma unroll
@@ -1164,18 +1165,15 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
   } else {
     wait_vmem<0>();
   }
-  bf16x8 qf[MB][C::kKS];
+  bf16x8 qf[C::kKS];
 #pragma unroll
   for (int ks = 0; ks < C::kKS; ++ks)
-    qf[0][ks] = __builtin_bit_cast(
+    qf[ks] = __builtin_bit_cast(
         bf16x8, *(const u32x4*)(mine + 2 * kTileBytes + C::slot(l32, 2 * ks + hi) * 16));
 
-  bf16x8 sum_a[MB];   // row-sum operands, as in the kernel above
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const uint32_t w = (lane & 15) == 2 * mb + ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
-    sum_a[mb] = __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
-  }
+  // row-sum operand, as in the kernel above
+  const uint32_t ones = (lane & 15) == ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
+  const bf16x8 sum_a = __builtin_bit_cast(bf16x8, u32x4{ones, ones, ones, ones});
   uint32_t k_rd[C::kKS], v_rd[2][C::kDB];
 #pragma unroll
   for (int ks = 0; ks < C::kKS; ++ks) k_rd[ks] = lds0 + C::slot(l32, 2 * ks + hi) * 16;
@@ -1192,19 +1190,14 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
   }
   typedef __attribute__((address_space(3))) char lds_char;
 
-  f32x16 o[C::kDB][MB];
+  f32x16 o[C::kDB];
   f32x4 lsum = {0.f, 0.f, 0.f, 0.f};
-  float shift[MB];
-  bool fresh[MB];   // no score above -inf yet (only masked keys)
+  float shift = 0.f;
+  bool fresh = true;   // no score above -inf yet (only masked keys)
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    shift[mb] = 0.f;
-    fresh[mb] = true;
+  for (int db = 0; db < C::kDB; ++db)
 #pragma unroll
-    for (int db = 0; db < C::kDB; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[db][mb][r] = 0.f;
-  }
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
 
   for (int32_t t = wave, buf = 0; t < n; t += NS, buf ^= 1) {
     // the buffer filled next was read a tile ago: those reads are complete
@@ -1216,55 +1209,41 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
       wait_vmem<0>();
     }
     const int base = buf * 2 * kTileBytes;
-    f32x16 sc[MB];
+    f32x16 sc;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sc[mb][r] = 0.f;
+    for (int r = 0; r < 16; ++r) sc[r] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < C::kKS; ++ks) {
       const bf16x8 kf = __builtin_bit_cast(
           bf16x8, *(const __attribute__((address_space(3))) u32x4*)((lds_char*)(uintptr_t)k_rd[ks] + base));
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-        sc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[mb][ks], sc[mb], 0, 0, 0);
-    }
-    float mx[MB];
-    bool move = false;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        sc[mb][r] = __builtin_fmaf(sc[mb][r], c, -shift[mb]);
-        if (t * 32 + 32 > L && t * 32 + 8 * (r >> 2) + 4 * hi + (r & 3) >= L) sc[mb][r] = -INFINITY;
-      }
-      float m1 = max3(sc[mb][0], sc[mb][1], sc[mb][2]);
-#pragma unroll
-      for (int r = 3; r + 1 < 16; r += 2) m1 = max3(m1, sc[mb][r], sc[mb][r + 1]);
-      mx[mb] = max_with_other_half(max3(m1, sc[mb][15], sc[mb][15]));
-      move |= mx[mb] > C::kShiftHi || (fresh[mb] && mx[mb] < C::kShiftLo && mx[mb] > -INFINITY);
-    }
-    if (__any(move)) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const bool need = mx[mb] > C::kShiftHi || (fresh[mb] && mx[mb] < C::kShiftLo && mx[mb] > -INFINITY);
-        const float delta = need ? mx[mb] : 0.f;
-        // nothing to rescale at the beam's first score (where 2^-delta may overflow)
-        const float alpha = fresh[mb] ? 0.f : fast_exp2(-delta);
-        shift[mb] += delta;
-        const float alpha_hi = __shfl_xor(alpha, 16);
-        lsum[2 * mb] *= alpha;
-        lsum[2 * mb + 1] *= alpha_hi;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sc[mb][r] -= delta;
-#pragma unroll
-        for (int db = 0; db < C::kDB; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[db][mb][r] *= alpha;
-      }
+      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], sc, 0, 0, 0);
     }
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) fresh[mb] = fresh[mb] && !(mx[mb] > -INFINITY);
+    for (int r = 0; r < 16; ++r) {
+      sc[r] = __builtin_fmaf(sc[r], c, -shift);
+      if (t * 32 + 32 > L && t * 32 + 8 * (r >> 2) + 4 * hi + (r & 3) >= L) sc[r] = -INFINITY;
+    }
+    float m1 = max3(sc[0], sc[1], sc[2]);
+#pragma unroll
+    for (int r = 3; r + 1 < 16; r += 2) m1 = max3(m1, sc[r], sc[r + 1]);
+    const float mx = max_with_other_half(max3(m1, sc[15], sc[15]));
+    const bool need = mx > C::kShiftHi || (fresh && mx < C::kShiftLo && mx > -INFINITY);
+    if (__any(need)) {
+      const float delta = need ? mx : 0.f;
+      // nothing to rescale at the beam's first score (where 2^-delta may overflow)
+      const float alpha = fresh ? 0.f : fast_exp2(-delta);
+      shift += delta;
+      const float alpha_hi = __shfl_xor(alpha, 16);
+      lsum[0] *= alpha;
+      lsum[1] *= alpha_hi;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sc[r] -= delta;
+#pragma unroll
+      for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    }
+    fresh = fresh && !(mx > -INFINITY);
 #pragma unroll
     for (int kc = 0; kc < 2; ++kc) {
       bf16x8 vf[C::kDB];
@@ -1278,38 +1257,32 @@ cross_attn_bf16_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __r
                                                            kc * 16 * C::kRowBytes));
         vf[db] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(half[0], half[1], 0, 1, 2, 3, 4, 5, 6, 7));
       }
+      u32x4 u;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        u32x4 u;
+      for (int w = 0; w < 4; ++w)
+        u[w] = pack_bf16x2(fast_exp2(sc[8 * kc + 2 * w]), fast_exp2(sc[8 * kc + 2 * w + 1]));
+      const bf16x8 p = __builtin_bit_cast(bf16x8, u);
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
-          u[w] = pack_bf16x2(fast_exp2(sc[mb][8 * kc + 2 * w]), fast_exp2(sc[mb][8 * kc + 2 * w + 1]));
-        const bf16x8 p = __builtin_bit_cast(bf16x8, u);
-#pragma unroll
-        for (int db = 0; db < C::kDB; ++db)
-          o[db][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], p, o[db][mb], 0, 0, 0);
-        lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sum_a[mb], p, lsum, 0, 0, 0);
-      }
+      for (int db = 0; db < C::kDB; ++db)
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], p, o[db], 0, 0, 0);
+      lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sum_a, p, lsum, 0, 0, 0);
     }
   }
 
   // partial results to LDS, over the tiles (every wave is past its last read)
   __syncthreads();
   float* const part = (float*)lds;
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const float s_lo = __shfl(lsum[2 * mb], l32 & 15), s_hi = __shfl(lsum[2 * mb + 1], l32 & 15);
-    if (hi == 0) {
-      part_shift[wave][mb * 32 + l32] = fresh[mb] ? -INFINITY : shift[mb];
-      part_l[wave][mb * 32 + l32] = l32 < 16 ? s_lo : s_hi;
-    }
-#pragma unroll
-    for (int db = 0; db < C::kDB; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *(f32x4*)(part + ((wave * kRows + mb * 32 + l32) * kStride + 32 * db + 8 * g + 4 * hi)) =
-            f32x4{o[db][mb][4 * g], o[db][mb][4 * g + 1], o[db][mb][4 * g + 2], o[db][mb][4 * g + 3]};
+  const float s_lo = __shfl(lsum[0], l32 & 15), s_hi = __shfl(lsum[1], l32 & 15);
+  if (hi == 0) {
+    part_shift[wave][l32] = fresh ? -INFINITY : shift;
+    part_l[wave][l32] = l32 < 16 ? s_lo : s_hi;
   }
+#pragma unroll
+  for (int db = 0; db < C::kDB; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *(f32x4*)(part + ((wave * kRows + l32) * kStride + 32 * db + 8 * g + 4 * hi)) =
+          f32x4{o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]};
   __syncthreads();
   for (int i = threadIdx.x; i < kRows * C::kCPR; i += 256) {
     const int row = i / C::kCPR, col = 8 * (i % C::kCPR);
