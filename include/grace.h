@@ -273,8 +273,8 @@ int64_t grace_beam_topk_workspace_bytes(int32_t B, int32_t M, int32_t V);
  * rest are filtered candidates (score -inf, dead beams).
  *
  *   cand       device, fp32 [B*M, V]
- *   row_max    device, fp32 [B*M] or NULL: a speed hint (grace_beam_scores'
- *              row maxima); any values give the same result
+ *   row_max    device, fp32 [B*M] or NULL: accepted and not read (the selection
+ *              reads all the candidates whatever the rows' maxima)
  *   B, M, V    requests, beams per request, vocabulary; M*V below 2^31 and
  *              B*M*V below 2^40
  *   k          1 <= k <= min(M*V, grace_beam_topk_max_k())
