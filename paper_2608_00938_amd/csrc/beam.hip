@@ -1461,7 +1461,7 @@ __device__ __forceinline__ float threshold(const Row& sample, uint32_t* hist, ui
         edge += (float)part / inv_w;
         const float q = fmaxf(__uint_as_float(__float_as_uint(edge) & 0x7f800000u) * 0x1p-10f, 0x1p-24f);
         return fits ? ref + edge - (edge < 0.f ? q : 0.f) - slack
-                    : ref + edge + 1.0f / inv_w + (edge < 0.f ? 0.f : q);
+                    : ref + edge + 1.0f / inv_w + (edge < 0.f ? 0.f : q) + slack;
       }
     }
     float best = -INFINITY;

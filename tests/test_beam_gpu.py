@@ -258,6 +258,7 @@ CROWDED_CASES = [
     (2, 4096, 512, 4096, "floor5000"), (2, 4096, 512, 4096, "floor5500"), (3, 4096, 512, 4096, "wide"),
     (2, 512, 512, 1024, "s0.02"), (3, 140, 509, 4000, "s0.05"), (1, 4096, 4096, 4096, "s3"),
     (2, 1000, 509, 1024, "dead"), (3, 512, 512, 1024, "dead"), (1, 4096, 512, 4096, "dead"),
+    (2, 278, 512, 2878, "few"), (2, 1000, 509, 1024, "few"),
 ]
 
 
@@ -268,8 +269,8 @@ def test_beam_selection_of_crowded_scores_stays_on_the_chip(gpu, case, dtype):
     thousands of them, a floor of equal scores under little more than k allowed
     tokens, prefixes far apart, samples too thin to aim within the list, and
     scores far from the prefixes that the sample is taken against (a few live beams
-    over dead ones at -1e9): bit for bit the oracle's order, and without the
-    one-workgroup pass."""
+    over dead ones at -1e9, and of few only as many as hold the k best): bit for
+    bit the oracle's order, and without the one-workgroup pass."""
     B, M, V, k, kind = case
     R = B * M
     _log(f"[beam crowded] {dtype} B={B} M={M} V={V} k={k} {kind}")
@@ -283,11 +284,13 @@ def test_beam_selection_of_crowded_scores_stays_on_the_chip(gpu, case, dtype):
             prev = torch.from_numpy(W.beam_prev_scores(17, 2, R)).to(gpu)
     elif kind == "wide":
         prev = 30.0 * torch.randn((R,), generator=gen, device=gpu)
-    elif kind == "dead":
+    elif kind in ("dead", "few"):
         # live: one beam in 16, all in the upper half, none among the 64 evenly spread ones
         beam = torch.arange(M, device=gpu)
         live = (beam >= M // 2) & (beam % 16 == 3)
         live[(M * torch.arange(64, device=gpu)) // 64] = False
+        if kind == "few":
+            live &= torch.cumsum(live, 0) <= k // V + 1
         prev = torch.from_numpy(W.beam_prev_scores(17, 2, R)).to(gpu)
         prev = torch.where(live.repeat(B), prev, torch.full_like(prev, -1e9))
         logits *= 3.0
