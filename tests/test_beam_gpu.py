@@ -197,6 +197,10 @@ SELECT_CASES = [
     (43, 96, 700, 50, "normal"),        # 258 would not all run at once
     (1, 16, 20000, 50, "normal"),       # one workgroup per request
     (3, 400, 512, 4096, "normal"),      # more gathered than its stage in LDS takes
+    # one beam in ten live, the range of the ranking stretched by the dead ones, which
+    # are left out of the sort; k past the live ones; a crowd of live ones
+    (5, 130, 46, 46, "stretched"), (5, 130, 46, 2000, "stretched"), (3, 150, 50, 600, "stretched_equal"),
+    (2, 140, 512, 3000, "stretched"),
 ]
 
 
@@ -228,6 +232,12 @@ def test_beam_selection_paths_bit_exact(gpu, case, dtype):
         prev[::M] = 0.0
     elif kind == "equal":
         logits[:], prev[:] = 0.5, -3.0
+    elif kind.startswith("stretched"):
+        live = rng.random(R) < 0.1
+        live[M // 3::M] = True
+        prev = np.where(live, prev, np.float32(-1e4)).astype(np.float32)
+        if kind == "stretched_equal":
+            logits[:], prev[live] = 0.5, -3.0
     elif kind == "inf":
         prev[::7] = np.inf
     logits, prev = logits.to(W.TORCH_DTYPES[dtype]).to(gpu), torch.from_numpy(prev).to(gpu)
