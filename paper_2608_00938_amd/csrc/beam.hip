@@ -888,17 +888,20 @@ __device__ __forceinline__ void rank_and_emit(TopkShared& sh, uint64_t (&v)[kGat
   __syncthreads();
   const bool crowded = sh.max_count > kRankBinCap;
   // members of a bin that starts at or past k are not among the k best
+  if (__builtin_expect(crowded, 0)) {
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const uint32_t i = (uint32_t)(tid + j * kTopkThreads);
-    if (i >= n || sh.bin_start[rb[j]] >= (uint32_t)k) continue;
-    sh.list[crowded ? atomicAdd(&sh.n_list, 1u) : sh.bin_start[rb[j]] + slot[j]] = v[j];
-  }
-  __syncthreads();
-  if (crowded) {
+    for (int j = 0; j < kPer; ++j)
+      if ((uint32_t)(tid + j * kTopkThreads) < n && sh.bin_start[rb[j]] < (uint32_t)k)
+        sh.list[atomicAdd(&sh.n_list, 1u)] = v[j];
+    __syncthreads();
     sort_and_emit(sh, sh.n_list, k, out0, c, out);   // all n, or k of them and more
     return;
   }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if ((uint32_t)(tid + j * kTopkThreads) < n && sh.bin_start[rb[j]] < (uint32_t)k)
+      sh.list[sh.bin_start[rb[j]] + slot[j]] = v[j];
+  __syncthreads();
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     slot[j] = 0xffffffffu;
@@ -1438,7 +1441,7 @@ __device__ __forceinline__ float threshold(const Row& sample, uint32_t* hist, ui
     float edge = (float)bin / kSelectInvW - kBelow;
     const float slack = fabsf(ref) * 0x1p-22f;   // the rounding of the differences
     bool far = !anew && bin == kTop && slack > 1.0f;
-    if (!crowded && !far)   // below -64 an fp16 step is wider than a bin
+    if (__builtin_expect(!crowded && !far, 1))   // below -64 an fp16 step is wider than a bin
       return bin == 0 ? -FLT_MAX : ref + (edge < -64.f ? edge - 1.0f / kSelectInvW : edge) - slack;
     if (!far) {
       // the outer bins, open below and above, in as many steps of a bin's width
@@ -1570,10 +1573,10 @@ struct PutStage {
   __device__ __forceinline__ void reserve(uint32_t n) {
     pos = atomicAdd(&st.n, n);
     const uint32_t first = max(pos, (uint32_t)STAGE);
-    if (pos + n > first) direct = atomicAdd(to.count, pos + n - first);
+    if (__builtin_expect(pos + n > first, 0)) direct = atomicAdd(to.count, pos + n - first);
   }
   __device__ __forceinline__ void operator()(uint64_t v) {
-    if (pos < (uint32_t)STAGE) {
+    if (__builtin_expect(pos < (uint32_t)STAGE, 1)) {
       st.entry[pos] = v;
     } else {
       to.put(direct++, v);
@@ -1589,7 +1592,7 @@ __device__ __forceinline__ void gather_flush(GatherStage<STAGE>& st, const Gathe
   if (threadIdx.x == 0) st.base = atomicAdd(to.count, n);
   __syncthreads();
   const uint32_t b0 = st.base;
-  if (b0 + n <= (uint32_t)kGatherCap) {
+  if (__builtin_expect(b0 + n <= (uint32_t)kGatherCap, 1)) {
     for (uint32_t j = threadIdx.x; j < n; j += THREADS) to.store(to.list + b0 + j, st.entry[j]);
   } else {
     for (uint32_t j = threadIdx.x; j < n; j += THREADS) to.put(b0 + j, st.entry[j]);
@@ -1759,12 +1762,12 @@ __device__ __forceinline__ void final_select(TopkShared& sh, float thr, uint32_t
   const bool enough = n >= (uint32_t)k || thr == -FLT_MAX;
   const int32_t way = !enough || n > entry.room ? kExact : (n > (uint32_t)kGatherCap ? kNarrowed : kRanked);
   if (threadIdx.x == 0) *how = way;
-  if (way == kExact) {
+  if (__builtin_expect(way == kExact, 0)) {
     exact_select<VEC8>(sh, k, N, out0, c, out);
     return;
   }
   uint64_t v[kPer];
-  if (way == kRanked) {
+  if (__builtin_expect(way == kRanked, 1)) {
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       const uint32_t i = (uint32_t)(threadIdx.x + j * kTopkThreads);
