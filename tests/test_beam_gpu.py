@@ -68,7 +68,7 @@ def _topk_case(gpu, cand, B, M, V, k, row_max=None):
 
 
 TOPK_SHAPES = [(3, 37, 64, 50), (2, 16, 600, 4096), (4, 200, 100, 1), (1, 3, 5, 15), (2, 64, 512, 777),
-               (2, 131, 257, 2000)]   # the last: M*V not a multiple of 4, over two slices
+               (2, 131, 257, 2000)]   # the last: M*V not a multiple of 4
 
 
 @pytest.mark.parametrize("shape", TOPK_SHAPES, ids=lambda s: "x".join(map(str, s)))
@@ -93,16 +93,21 @@ def test_beam_topk_row_max_hint_does_not_change_result(gpu, hint):
 
 def test_beam_topk_sampled_bin_too_low_falls_back(gpu):
     """The k best are not spread like the rest: in each request only the first
-    32 candidates (a chunk that the kernel's sixteenth-sample always holds) score
-    high, so the sampled bin has too few candidates above it (32 < k) and the
-    full histogram path must take over.  The result must not change."""
-    B, M, V, k = 2, 64, 512, 64
+    32 candidates (a chunk that the kernel's sample of one chunk in eight always
+    holds) score high, so the sampled threshold has too few candidates above it
+    (32 < k) and the exact selection must take over, which the third word of a
+    request's info in the workspace says.  The result must not change."""
+    B, M, V, k = 2, 160, 512, 64
     rng = np.random.default_rng(11)
     cand = (-20.0 - rng.random((B * M, V))).astype(np.float32)
     for b in range(B):
         cand[b * M, :32] = (-rng.random(32)).astype(np.float32)
     _log(f"[beam topk sample miss] B={B} M={M} V={V} k={k}")
     _topk_case(gpu, cand, B, M, V, k)
+    ws = torch.zeros((G.grace_beam_topk_workspace_bytes(B, M, V),), dtype=torch.uint8, device=gpu)
+    G.grace_beam_topk(torch.from_numpy(cand).to(gpu), B, M, k, workspace=ws)
+    info = ws[-32 * B:].view(torch.int32).view(B, 8).cpu().numpy()
+    assert (info[:, 1] <= 32).all() and info[:, 2].tolist() == [2] * B
 
 
 def test_beam_topk_large_fast_path(gpu):
@@ -139,7 +144,7 @@ def test_beam_scores_then_topk_is_a_valid_topk(gpu):
 
 STEP_CASES = [
     dict(dtype="bf16", B=3, M=128, V=512, k=300, mask=True),    # 8-token-run score kernel
-    dict(dtype="f32", B=2, M=40, V=100, k=50, mask=True),       # generic score kernel (V % 8 != 0)
+    dict(dtype="f32", B=2, M=40, V=100, k=50, mask=True),       # tokens 64 apart (V % 8 != 0)
     dict(dtype="bf16", B=2, M=16, V=600, k=4096, mask=False),   # two runs per lane, k = max
     dict(dtype="bf16", B=2, M=3, V=5, k=15, mask=False),        # k = M*V
     dict(dtype="bf16", B=8, M=1024, V=512, k=1024, mask=True),  # the paper's widths: sampled path
@@ -174,8 +179,9 @@ def test_beam_step_equals_scores_then_topk(gpu, i):
 
 # Selection paths of the top-k: (B, M, V, k, structure).  Up to 65536 candidates
 # per request stay in one workgroup's registers (8192 of them without a
-# threshold); beyond that a sampled threshold, a gather and a ranking, or the
-# exact selection when the gathered set is too small or too large.
+# threshold); beyond that a sampled threshold, a gather and a ranking (narrowed
+# first where the gathered set is past the list), or the exact selection when the
+# set is too small or past the workspace.
 SELECT_CASES = [
     (3, 16, 512, 100, "normal"),        # 8192: all gathered
     (2, 8200, 1, 4096, "normal"),       # just past it, one token per row
